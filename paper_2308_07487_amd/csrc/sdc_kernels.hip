@@ -415,7 +415,7 @@ __device__ inline void stage_mma(const Stage<PREC, NB>& s, Acc<PREC, SCHED, LW>&
 }
 
 int fused_lds_bytes(int win, int precision) {
-    return lag_group(precision) * win * (int)sizeof(double) + 1024 * (int)sizeof(float);
+    return hist_pitch(precision) * win * (int)sizeof(double) + 1024 * (int)sizeof(float);
 }
 
 // MFMA instructions one stage_mma call issues per wave.
@@ -504,6 +504,7 @@ template <int PREC, int RADIAL, int PAIRED, int SCHED, int LW, int OFF>
 __device__ __forceinline__ void pair_loop(const TaskCtx& c) {
     constexpr int LG = lag_group(PREC);
     constexpr int NB = win_blocks(LG);
+    constexpr int PITCH = hist_pitch(PREC);
     constexpr bool TWO = SCHED == kSchedTwoPass;
     constexpr bool FOLD = SCHED == kSchedFold;
     const FusedArgs& a = *c.a;
@@ -609,7 +610,10 @@ __device__ __forceinline__ void pair_loop(const TaskCtx& c) {
                 for (int r = 0; r < 16; ++r) bin[r] = gj - a.gtab[rowbase + 8 * (r / 4) + (r % 4)];
             }
         };
-        auto add_hist = [&](auto with_small) {
+        // One LDS add per element, at its bin's row plus the lag's constant
+        // offset (see hist_pitch).  The deterministic mode is a loop of its
+        // own: a test per element would cut the adds into basic blocks of one.
+        auto add_hist = [&](auto with_small, auto det) {
 #pragma unroll
             for (int m = 0; m < LW; ++m) {
                 if ((grp.mask >> (OFF + m)) & 1) {
@@ -617,14 +621,21 @@ __device__ __forceinline__ void pair_loop(const TaskCtx& c) {
                     for (int r = 0; r < 16; ++r) {
                         double v = (double)acc.v[m][r];
                         if constexpr (decltype(with_small)::value) v += (double)acc.s[m][r];
-                        if (a.det)
-                            atomicAdd(reinterpret_cast<unsigned long long*>(hist) + (OFF + m) * a.win + bin[r],
-                                      to_fixed(v));
+                        double* cell = hist + bin[r] * PITCH + (OFF + m);
+                        if constexpr (decltype(det)::value)
+                            atomicAdd(reinterpret_cast<unsigned long long*>(cell), to_fixed(v));
                         else
-                            atomicAdd(&hist[(OFF + m) * a.win + bin[r]], v);
+                            atomicAdd(cell, v);
                     }
                 }
             }
+        };
+        auto epilogue = [&](auto with_small) {
+            bins();
+            if (a.det)
+                add_hist(with_small, std::true_type{});
+            else
+                add_hist(with_small, std::false_type{});
         };
 
         if constexpr (TWO) {
@@ -632,22 +643,19 @@ __device__ __forceinline__ void pair_loop(const TaskCtx& c) {
             // large ones on top (see the pass constants)
             k_loop<PREC, kPassSmall, SCHED, NB, LW, OFF, kStagesTwoPassSmall>(nk, load, acc);
             k_loop<PREC, kPassLarge, SCHED, NB, LW, OFF, kStagesTwoPassLarge>(nk, load, acc);
-            bins();
-            add_hist(std::false_type{});
+            epilogue(std::false_type{});
         } else if constexpr (FOLD) {
             k_loop<PREC, kPassFold, SCHED, NB, LW, OFF, kStagesFold>(nk, load, acc);
-            bins();
-            add_hist(std::false_type{});
+            epilogue(std::false_type{});
         } else {
             k_loop<PREC, kPassAll, SCHED, NB, LW, OFF, kStagesOnePass>(nk, load, acc);
-            bins();
-            add_hist(std::integral_constant<bool, PREC != SDC_PREC_FP32>{});
+            epilogue(std::integral_constant<bool, PREC != SDC_PREC_FP32>{});
         }
     }
 }
 
 // One task of a plan: the stream's tile pairs for one lag group, histogram
-// in LDS (`hist`: [LG][win] FP64, then the radial edge table), merged into
+// in LDS (`hist`: [win][hist_pitch] FP64, then the radial edge table), merged into
 // the plan's global bins at the end.  Called by the whole workgroup.
 // PAIRED: O8 is even, so a K-step's two origin blocks always lie in one
 // component and the block offsets follow from the step with one scalar
@@ -659,7 +667,8 @@ template <int PREC, int RADIAL, int PAIRED, int SCHED>
 __device__ __forceinline__ void fused_task(const FusedArgs& a, int task, double* hist) {
     constexpr int LG = lag_group(PREC);
     constexpr int NT = threads_per_wg(SCHED);
-    float* e2s = (float*)(hist + LG * a.win);
+    constexpr int PITCH = hist_pitch(PREC);
+    float* e2s = (float*)(hist + PITCH * a.win);
     const int tid = threadIdx.x;
     const int wave = tid >> 6;
     TaskCtx c;
@@ -670,7 +679,7 @@ __device__ __forceinline__ void fused_task(const FusedArgs& a, int task, double*
     c.e2s = e2s;
     c.quadrant = wave & 3;
 
-    for (int x = tid; x < LG * a.win; x += NT) hist[x] = 0.0;
+    for (int x = tid; x < PITCH * a.win; x += NT) hist[x] = 0.0;
     if constexpr (RADIAL) {
         for (int x = tid; x < a.n_shells; x += NT) e2s[x] = a.e2[x];
     }
@@ -692,8 +701,8 @@ __device__ __forceinline__ void fused_task(const FusedArgs& a, int task, double*
     for (int x = tid; x < LG * a.win; x += NT) {
         const int m = x / a.win;
         const int w = x - m * a.win;
-        const double v = hist[x];
-        const unsigned long long vq = reinterpret_cast<const unsigned long long*>(hist)[x];
+        const double v = hist[w * PITCH + m];
+        const unsigned long long vq = reinterpret_cast<const unsigned long long*>(hist)[w * PITCH + m];
         if (vq != 0ull && ((grp.mask >> m) & 1)) {
             int64_t b;
             if constexpr (RADIAL) {
