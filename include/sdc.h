@@ -161,8 +161,10 @@ typedef struct {
     int32_t schedule;      /* sdc_schedule                                     */
     int32_t segment_pairs; /* tile pairs per fused task (pairs that share one  */
                            /* LDS histogram; one merge into the global bins    */
-                           /* per task): 0 = default (periodic kinds 96,       */
-                           /* radial all pairs of an i-tile), else [1, 2^20]   */
+                           /* per task): 0 = default (at most 96 for periodic  */
+                           /* kinds and all pairs of an i-tile for radial, cut */
+                           /* to fit the sample and the device), else          */
+                           /* [1, 2^20]                                        */
 } sdc_tuning;
 
 typedef struct sdc_plan sdc_plan;

@@ -433,7 +433,8 @@ sdc_status sdc_plan_create_tuned(const float* positions_host, int64_t n_sites, c
     sdc_status s = check_specs(bins, corr);
     if (s != SDC_OK) return s;
     sdc_tuning tu{};
-    s = sdc::resolve_tuning(tuning, n_sites, bins, corr, device, &tu);
+    bool default_segment = false;
+    s = sdc::resolve_tuning(tuning, n_sites, bins, corr, device, &tu, &default_segment);
     if (s != SDC_OK) return s;
     sdc_plan* p = nullptr;
     try {
@@ -442,7 +443,8 @@ sdc_status sdc_plan_create_tuned(const float* positions_host, int64_t n_sites, c
         p->corr = *corr;
         p->tuning = tu;
         std::string err;
-        s = sdc::build_layout(positions_host, n_sites, bins, tu.segment_pairs, &p->lay, &err);
+        s = sdc::build_layout(positions_host, n_sites, bins, default_segment ? sdc::kMaxSegmentPairs : tu.segment_pairs,
+                              &p->lay, &err);
         if (s != SDC_OK) {
             delete p;
             return set_err(s, err);
@@ -457,6 +459,22 @@ sdc_status sdc_plan_create_tuned(const float* positions_host, int64_t n_sites, c
         return s;
     }
     p->device = device;
+    if (default_segment) {
+        int n_cu = 0;
+        if (hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || n_cu < 1)
+            n_cu = 256;
+        // lag groups of the full selection, workgroups resident at once
+        const int64_t slots = (int64_t)n_cu * sdc::wg_per_cu(sdc::sched_index(tu.schedule));
+        try {
+            std::vector<int> lags((size_t)corr->n_lags);
+            for (int t = 0; t < corr->n_lags; ++t) lags[t] = t;
+            const int n_groups = (int)make_groups(lags, corr->origin_stride, sdc::lag_group(corr->precision)).size();
+            sdc::split_streams(&p->lay, sdc::fitted_segment(p->lay, n_groups, slots, tu.segment_pairs));
+        } catch (const std::bad_alloc&) {
+            delete p;
+            return set_err(SDC_ERR_OOM, "host allocation failed");
+        }
+    }
     const Layout& L = p->lay;
     const int sstr = corr->origin_stride;
     p->O8 = (corr->n_origins + sdc::kOriginBlock - 1) / sdc::kOriginBlock;

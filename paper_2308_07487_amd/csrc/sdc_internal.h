@@ -141,8 +141,17 @@ constexpr int default_segment_pairs(int kind) {
 // Tuning a plan runs with (sdc_tune.cpp): the caller's fields where set,
 // else the entry of the tuning file named by SDC_TUNING_FILE for the plan's
 // size class, else the defaults.  Every field of *out is set (no zeros).
+// *default_segment (may be null): the segment length is the default one,
+// below which fitted_segment() may go.
 sdc_status resolve_tuning(const sdc_tuning* given, int64_t n_sites, const sdc_bin_spec* bins,
-                          const sdc_corr_spec* corr, int device, sdc_tuning* out);
+                          const sdc_corr_spec* corr, int device, sdc_tuning* out, bool* default_segment = nullptr);
+
+// Cuts every stream into consecutive, about equal segments of at most seg
+// tile pairs.
+void split_streams(Layout* lay, int seg);
+// Tile pairs per task that suit a layout of whole streams run with n_groups
+// lag groups by `slots` workgroups at a time (at most cap).
+int fitted_segment(const Layout& lay, int n_groups, int64_t slots, int cap);
 
 // Global bin of window coordinate w of stream s (periodic kinds).
 int64_t window_bin(const Layout& lay, const KStream& s, int w);

@@ -83,27 +83,6 @@ uint64_t spread3(uint64_t v) {
     return v;
 }
 
-// Cut every stream into consecutive segments of at most `seg` pairs (same
-// window, same bins).  The lag groups of a segment run as neighbouring tasks
-// on one XCD and share its operands in L2 only while they are in step; over
-// a whole stream (up to ~1000 pairs) they drift apart and the operand
-// re-reads miss L2.  Shorter segments keep them in step at the price of
-// more histogram merges (one per segment, lag group and window bin).
-void split_streams(Layout* lay, int seg) {
-    std::vector<KStream> out;
-    for (const KStream& s : lay->streams) {
-        const int len = s.p1 - s.p0;
-        const int nseg = (len + seg - 1) / seg;
-        for (int k = 0; k < nseg; ++k) {
-            KStream t = s;
-            t.p0 = s.p0 + (int)((int64_t)k * len / nseg);
-            t.p1 = s.p0 + (int)((int64_t)(k + 1) * len / nseg);
-            out.push_back(t);
-        }
-    }
-    lay->streams.swap(out);
-}
-
 sdc_status build_periodic(const float* pos, int64_t n, const sdc_bin_spec* spec, int seg, Layout* lay,
                           std::string* err) {
     const bool bcc = spec->kind == SDC_BINS_PERIODIC_BCC;
@@ -300,6 +279,68 @@ sdc_status build_radial(const float* pos, int64_t n, const sdc_bin_spec* spec, i
 }
 
 }  // namespace
+
+// Cut every stream into consecutive segments of at most `seg` pairs (same
+// window, same bins).  The lag groups of a segment run as neighbouring tasks
+// on one XCD and share its operands in L2 only while they are in step; over
+// a whole stream (up to ~1000 pairs) they drift apart and the operand
+// re-reads miss L2.  Shorter segments keep them in step at the price of
+// more histogram merges (one per segment, lag group and window bin).
+void split_streams(Layout* lay, int seg) {
+    std::vector<KStream> out;
+    for (const KStream& s : lay->streams) {
+        const int len = s.p1 - s.p0;
+        const int nseg = (len + seg - 1) / seg;
+        for (int k = 0; k < nseg; ++k) {
+            KStream t = s;
+            t.p0 = s.p0 + (int)((int64_t)k * len / nseg);
+            t.p1 = s.p0 + (int)((int64_t)(k + 1) * len / nseg);
+            out.push_back(t);
+        }
+    }
+    lay->streams.swap(out);
+}
+
+// A task's cost is its tile pairs plus about one more for clearing and
+// merging its histogram, so with Q tile pairs for every workgroup slot the
+// length near sqrt(Q) balances the merges against the half-empty last round
+// of tasks (and keeps the lag groups of a segment in step, see above).  For
+// few pairs per slot (Q < 32) the rounds are counted: the longest segments
+// of the least ceil(tasks / slots) (length + 1).  Fused launch, whole streams
+// or 96-pair segments against the length chosen: sc 8^3 x 64 lags 69 -> 30 us
+// (1 pair), sc 12^3 x 70 lags 283 -> 190 us (14), bcc 13x14x15 x 130 lags 7.63
+// -> 7.15 ms (18), 3001 points x 100 lags 1.27 -> 0.89 ms (7), 20 011 points x
+// 128 lags 58.0 -> 56.1 ms (55).  Never above 32 pairs (radial 64): over
+// longer ones the lag groups lose step and their operand re-reads miss L2
+// (periodic samples of 25 000 to 100 000 sites with 32 pairs are up to 4%
+// faster than with 96 and at most 3% slower than with their best of 16, 32
+// and 48; 65 536 points in 1024 shells take 588 ms with 64 and 600 ms with
+// 181 or whole streams).
+int fitted_segment(const Layout& lay, int n_groups, int64_t slots, int cap) {
+    cap = std::min(cap, lay.kind == SDC_BINS_RADIAL ? 64 : 32);
+    const double q = (double)lay.pairs.size() * n_groups / (double)slots;
+    if (q >= 32.0) return std::max(1, (int)std::min((double)cap, std::sqrt(q) + 0.5));
+    int longest = 1;
+    for (const KStream& s : lay.streams) longest = std::max(longest, s.p1 - s.p0);
+    longest = std::min(longest, cap);
+    int best = longest;
+    double best_cost = -1.0;
+    for (int seg = longest; seg >= 1; --seg) {
+        int64_t tasks = 0;
+        int len = 1;
+        for (const KStream& s : lay.streams) {
+            const int n = s.p1 - s.p0, k = (n + seg - 1) / seg;
+            tasks += k;
+            len = std::max(len, (n + k - 1) / k);
+        }
+        const double cost = std::ceil((double)tasks * n_groups / (double)slots) * (len + 1);
+        if (best_cost < 0.0 || cost < best_cost) {
+            best_cost = cost;
+            best = seg;
+        }
+    }
+    return best;
+}
 
 sdc_status build_layout(const float* pos, int64_t n, const sdc_bin_spec* spec, int segment_pairs, Layout* lay,
                         std::string* err) {

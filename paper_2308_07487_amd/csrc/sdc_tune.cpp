@@ -202,9 +202,10 @@ bool split_precision(int p) { return p == SDC_PREC_SPLIT_BF16 || p == SDC_PREC_S
 namespace sdc {
 
 sdc_status resolve_tuning(const sdc_tuning* given, int64_t n_sites, const sdc_bin_spec* bins,
-                          const sdc_corr_spec* corr, int device, sdc_tuning* out) {
+                          const sdc_corr_spec* corr, int device, sdc_tuning* out, bool* default_segment) {
     sdc_tuning t{};
     if (given) t = *given;
+    if (default_segment) *default_segment = false;
     if (t.schedule < SDC_SCHED_DEFAULT || t.schedule > SDC_SCHED_FOLD)
         return set_error(SDC_ERR_INVALID_ARG, "unknown schedule");
     if (t.segment_pairs < 0 || t.segment_pairs > kMaxSegmentPairs)
@@ -227,7 +228,10 @@ sdc_status resolve_tuning(const sdc_tuning* given, int64_t n_sites, const sdc_bi
         return set_error(SDC_ERR_INVALID_ARG, "unknown schedule in the tuning file");
     if (!sched_valid(corr->precision, sched_index(t.schedule)))
         return set_error(SDC_ERR_UNSUPPORTED, "schedule not available for this precision");
-    if (t.segment_pairs <= 0 || t.segment_pairs > kMaxSegmentPairs) t.segment_pairs = default_segment_pairs(bins->kind);
+    if (t.segment_pairs <= 0 || t.segment_pairs > kMaxSegmentPairs) {
+        t.segment_pairs = default_segment_pairs(bins->kind);
+        if (default_segment) *default_segment = true;
+    }
     *out = t;
     return SDC_OK;
 }
