@@ -279,6 +279,8 @@ sdc_status queue_pack_self(sdc_plan* p, const LagSel& sel, const float* spins_de
     pa.A = p->d_A;
     pa.B = p->d_B;
     pa.mean = p->d_mean;
+    pa.mframe = p->d_mframe;
+    pa.n_sums = (int64_t)(p->corr.n_origins - 1) * p->corr.origin_stride + sel.max_lag + 1;
     if (timing) SDC_HIP(hipEventRecord(p->ev[0], hs), "hipEventRecord");
     int e = 0;
     if (p->d_mean)
@@ -296,7 +298,7 @@ sdc_status queue_pack_self(sdc_plan* p, const LagSel& sel, const float* spins_de
     sa.stride = p->corr.origin_stride;
     sa.lags = sel.d_lags;
     sa.n_sel = sel.n_sel;
-    sa.t_need = (int64_t)(p->corr.n_origins - 1) * p->corr.origin_stride + sel.max_lag + 1;
+    sa.t_need = pa.n_sums;
     sa.self = p->d_self;
     sa.precision = p->corr.precision;
     sa.H = p->d_H;
@@ -911,12 +913,15 @@ sdc_status sdc_plan_reset(sdc_plan* p, void* stream) {
     sdc_status s = plan_usable(p);
     if (s != SDC_OK) return s;
     SDC_HIP(select_device(p->device), "hipSetDevice");
-    int e = sdc::launch_zero(p->d_H, (int64_t)p->corr.n_lags * p->lay.n_bins * 8, stream);
-    if (e == 0) e = sdc::launch_zero(p->d_self, (int64_t)p->corr.n_lags * 8, stream);
-    if (e == 0) e = sdc::launch_zero(p->d_norg, (int64_t)p->corr.n_lags * 8, stream);
-    if (e == 0) e = sdc::launch_zero(p->d_msum, (int64_t)p->corr.n_lags * 8, stream);
-    if (e == 0 && p->d_Hq) e = sdc::launch_zero(p->d_Hq, (int64_t)p->corr.n_lags * p->lay.n_bins * 8, stream);
-    if (e == 0 && p->d_selfq) e = sdc::launch_zero(p->d_selfq, (int64_t)p->corr.n_lags * 8, stream);
+    const int64_t nl = p->corr.n_lags, nb = p->lay.n_bins;
+    sdc::ZeroRanges z{};
+    z.add(p->d_H, nl * nb * 8);
+    z.add(p->d_self, nl * 8);
+    z.add(p->d_norg, nl * 8);
+    z.add(p->d_msum, nl * 8);
+    if (p->d_Hq) z.add(p->d_Hq, nl * nb * 8);
+    if (p->d_selfq) z.add(p->d_selfq, nl * 8);
+    const int e = sdc::launch_zero_ranges(z, stream);
     if (e != 0) {
         p->failed = true;
         return hip_err(e, "reset");
@@ -1426,8 +1431,10 @@ sdc_status sdc_sq_reset(sdc_sq* q, void* stream) {
     sdc_status s = sq_usable(q);
     if (s != SDC_OK) return s;
     SDC_HIP(select_device(q->device), "hipSetDevice");
-    int e = sdc::launch_zero(q->d_raw, (int64_t)q->n_q * q->spec.n_lags * 16, stream);
-    if (e == 0) e = sdc::launch_zero(q->d_norg, 8, stream);
+    sdc::ZeroRanges z{};
+    z.add(q->d_raw, (int64_t)q->n_q * q->spec.n_lags * 16);
+    z.add(q->d_norg, 8);
+    const int e = sdc::launch_zero_ranges(z, stream);
     if (e != 0) {
         q->failed = true;
         return hip_err(e, "reset");

@@ -223,6 +223,8 @@ struct PackArgs {
     const float* mean;    // [n][4] per-site origin averages subtracted from A, or null
     void* A;              // [3][O8][n_pad] x 32 B
     void* B;              // [n_phase][3][F8][n_pad] x 32 B
+    double* mframe;       // [n_sums][3]: site-summed spin of the first n_sums frames
+    int64_t n_sums;
 };
 int launch_pack(const PackArgs& a, void* stream);
 
@@ -303,7 +305,7 @@ struct SelfArgs {
     double* H;            // [n_lags][n_bins]; the i = j pairs all fall in bin 0
     int64_t n_bins;
     double* norg;         // [n_lags] origin totals, += n_origins per selected lag
-    double* mframe;       // [t_need][3] scratch: site-summed spin of each frame
+    const double* mframe; // [t_need][3] site-summed spin of each frame (from the pack launch)
     double* msum;         // [n_lags] += sum_o M(o s) . M(o s + t)
     const float* mean;    // [n][4] origin averages (connected form), or null
     int det;              // deterministic mode: fixed-point self sums and bins
@@ -389,6 +391,17 @@ int launch_sq_finalize(const double* raw, const double* n_org, int64_t n_sites, 
                        double* sqw, void* stream);
 
 int launch_zero(void* ptr, int64_t bytes, void* stream);
+// Several ranges (whole 32-bit words) cleared in one launch.
+struct ZeroRanges {
+    void* ptr[6];
+    int64_t bytes[6];
+    int n;
+    void add(void* p, int64_t b) {
+        ptr[n] = p;
+        bytes[n++] = b;
+    }
+};
+int launch_zero_ranges(const ZeroRanges& z, void* stream);
 
 // Fixed device scratch of the entry points that allocate nothing
 // (sdc_static.hip): kStaticScratchBytes per device, shared by every call on
@@ -462,7 +475,8 @@ int launch_mc_finish(const McArgs& a, double* partial, double T_last, float* out
 
 int fused_lds_bytes(int win, int precision);
 // Largest dynamic LDS of a fused launch (the CU's 160 KB less room for the
-// batch kernel's few static words) and the self kernel's staging budget.
+// batch kernel's few static words) and the self kernel's budget for the
+// samples of one site (beside at most 16 KB of lag sums).
 constexpr int kMaxFusedLds = 160 * 1024 - 256;
 constexpr int64_t kSelfLdsBudget = 96 * 1024;
 // Set the kernels' dynamic-LDS limits on the current device.

@@ -98,14 +98,50 @@ __device__ inline PackElem<PREC> make_chunk(const float v[8]) {
     return c;
 }
 
+// Site-summed spin M(f) = sum_i S_i(f) of one frame in FP64, by one workgroup.
+__device__ inline void frame_sum(const float* __restrict__ frames, int64_t n, int64_t f, double* __restrict__ M) {
+    __shared__ double red[3][4];
+    const float* x = frames + f * n * 3;
+    double s[3] = {0.0, 0.0, 0.0};
+    for (int64_t i = threadIdx.x; i < n; i += 256)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) s[c] += (double)x[3 * i + c];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+#pragma unroll
+        for (int w = 32; w > 0; w >>= 1) s[c] += __shfl_down(s[c], w);
+        if ((threadIdx.x & 63) == 0) red[c][threadIdx.x >> 6] = s[c];
+    }
+    __syncthreads();
+    if (threadIdx.x < 3)
+        M[f * 3 + threadIdx.x] =
+            (red[threadIdx.x][0] + red[threadIdx.x][1]) + (red[threadIdx.x][2] + red[threadIdx.x][3]);
+    __syncthreads();  // the next frame reuses the partial sums
+}
+
+// Grid rows of a pack launch that sum frames, gx workgroups each.
+__host__ __device__ inline int sum_rows(int64_t n_sums, int64_t gx) {
+    const int64_t r = (n_sums + gx - 1) / gx;
+    return (int)(r < 4096 ? r : 4096);  // a grid has at most 65535 rows; the sums then take several frames each
+}
+
 // One thread per (block of 8 samples, packed site); writes the three
 // components.  Rows 0..3*O8 of the work index the A pack (origins o*s),
 // the rest the B packs (phase copies: sample g of phase ph is frame s*g + ph).
+// The first rows of the grid sum the frames that the site sums read, one
+// frame per workgroup (independent work that would be a launch of its own:
+// at sc 8^3 each launch costs about as much as its kernel).
 template <int PREC>
 __global__ __launch_bounds__(256) void pack_kernel(PackArgs a) {
+    const int n_sum = sum_rows(a.n_sums, gridDim.x);
+    const int row = (int)blockIdx.y - n_sum;  // 0..O8 + n_phase*F8 - 1 after the frame sums
+    if (row < 0) {
+        for (int64_t f = (int64_t)blockIdx.y * gridDim.x + blockIdx.x; f < a.n_sums; f += (int64_t)n_sum * gridDim.x)
+            frame_sum(a.frames, a.n, f, a.mframe);
+        return;
+    }
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= a.n_pad) return;
-    const int row = blockIdx.y;  // 0..O8 + n_phase*F8 - 1
     const int32_t orig = a.perm[p];
     float v[3][8];
     const bool isA = row < a.O8;
@@ -155,7 +191,8 @@ __global__ __launch_bounds__(256) void pack_kernel(PackArgs a) {
 
 int launch_pack(const PackArgs& a, void* stream) {
     dim3 block(256);
-    dim3 grid((unsigned)((a.n_pad + 255) / 256), (unsigned)(a.O8 + a.n_phase * a.F8));
+    const int64_t gx = (a.n_pad + 255) / 256;
+    dim3 grid((unsigned)gx, (unsigned)(a.O8 + a.n_phase * a.F8 + sum_rows(a.n_sums, gx)));
     hipStream_t s = (hipStream_t)stream;
     switch (a.precision) {
         case SDC_PREC_FP32: hipLaunchKernelGGL(pack_kernel<SDC_PREC_FP32>, grid, block, 0, s, a); break;
@@ -1015,93 +1052,223 @@ int launch_count(const CountArgs& a, void* stream) {
 // self term: sum_o sum_i S_i(o s) . S_i(o s + t) in FP64
 // ---------------------------------------------------------------------------
 
-// Low part of the hi/lo split exactly as the pack kernel forms it.
+// Small pieces of v exactly as the pack kernel forms them: lo of the hi/lo
+// splits; mid and lo of the three-piece form.
 template <int PREC>
-__device__ inline double split_lo(float v) {
-    if constexpr (PREC == SDC_PREC_SPLIT_BF16) return (double)bf16_val(bf16_bits(v - bf16_val(bf16_bits(v))));
-    else if constexpr (PREC == SDC_PREC_SPLIT_FP16) return (double)f16_val(f16_bits(v - f16_val(f16_bits(v))));
-    else return 0.0;
-}
-
-// The part of x*y that the reduced-precision contraction leaves out, from
-// the pieces the pack kernel forms (FP64, exact): lo*lo for the hi/lo splits;
-// mid*lo + lo*mid + lo*lo for the three-piece form.
-template <int PREC>
-__device__ inline double dropped_product(float x, float y) {
-    if constexpr (PREC == SDC_PREC_BF16X3) {
-        const float rx = x - bf16_val(bf16_bits(x)), ry = y - bf16_val(bf16_bits(y));
-        const double mx = (double)bf16_val(bf16_bits(rx)), my = (double)bf16_val(bf16_bits(ry));
-        const double lx = (double)bf16_val(bf16_bits(rx - (float)mx));
-        const double ly = (double)bf16_val(bf16_bits(ry - (float)my));
-        return mx * ly + lx * my + lx * ly;
-    } else {
-        return split_lo<PREC>(x) * split_lo<PREC>(y);
+__device__ inline void small_pieces(float v, float (&p)[2]) {
+    if constexpr (PREC == SDC_PREC_SPLIT_BF16) {
+        p[0] = bf16_val(bf16_bits(v - bf16_val(bf16_bits(v))));
+    } else if constexpr (PREC == SDC_PREC_SPLIT_FP16) {
+        p[0] = f16_val(f16_bits(v - f16_val(f16_bits(v))));
+    } else if constexpr (PREC == SDC_PREC_BF16X3) {
+        const float r = v - bf16_val(bf16_bits(v));
+        p[0] = bf16_val(bf16_bits(r));
+        p[1] = bf16_val(bf16_bits(r - p[0]));
     }
 }
+// Pieces kept per value: the number of small ones.
+template <int PREC>
+constexpr int n_small() {
+    return PREC == SDC_PREC_FP32 ? 0 : PREC == SDC_PREC_BF16X3 ? 2 : 1;
+}
+// The part of x*y that the reduced-precision contraction leaves out, from
+// the small pieces (FP64, exact): lo*lo for the hi/lo splits; mid*lo +
+// lo*mid + lo*lo for the three-piece form.
+template <int PREC>
+__device__ inline double dropped_product(const float (&x)[2], const float (&y)[2]) {
+    if constexpr (PREC == SDC_PREC_BF16X3)
+        return (double)x[0] * (double)y[1] + (double)x[1] * (double)y[0] + (double)x[1] * (double)y[1];
+    else
+        return (double)x[0] * (double)y[0];
+}
 
-// Block: up to 16 consecutive sites.  With USE_LDS their whole time series
-// sits in LDS; otherwise the samples are read from global memory.
-// Thread (site q = tid / 16, lane r = tid % 16) takes lags r, r + 16, ...
+// Site-summed correlation of selected lag l: the sum over all ordered pairs
+// of S_i(o s) . S_j(o s + t) equals M(o s) . M(o s + t), summed over the
+// origins in FP64 (one thread per lag).  For the connected form the origin
+// side is centred: the sum over all pairs of (S_i(o s) - <S_i>) . S_j(o s + t)
+// is (M(o s) - <M>) . M(o s + t).
+__device__ inline void site_sum(const SelfArgs& a, int l) {
+    const int t = a.lags[l];
+    double mb[3] = {0.0, 0.0, 0.0};
+    if (a.mean) {
+        for (int o = 0; o < a.n_origins; ++o)
+            for (int c = 0; c < 3; ++c) mb[c] += a.mframe[(int64_t)o * a.stride * 3 + c];
+        for (int c = 0; c < 3; ++c) mb[c] /= (double)a.n_origins;
+    }
+    double s = 0.0;
+#pragma unroll 4
+    for (int o = 0; o < a.n_origins; ++o) {
+        const double* m0 = a.mframe + (int64_t)o * a.stride * 3;
+        const double* m1 = m0 + (int64_t)t * 3;
+        s += (m0[0] - mb[0]) * m1[0] + (m0[1] - mb[1]) * m1[1] + (m0[2] - mb[2]) * m1[2];
+    }
+    a.msum[t] += s;
+}
+
+// Where the self kernel finds the samples of its sites: in global memory, as
+// whole series in LDS, or in LDS with their small pieces and the centred
+// origin side beside them (kSelfPieces; when all of it fits the budget).
+constexpr int kSelfGlobal = 0, kSelfSeries = 1, kSelfPieces = 2;
+
+// LDS floats per site.
+static int64_t self_floats(int mode, int pieces, int64_t t_need, int n_origins) {
+    if (mode == kSelfSeries) return 3 * t_need;
+    if (mode == kSelfPieces) return 3 * (1 + pieces) * (t_need + n_origins);
+    return 0;
+}
+
+// Self sums.  A workgroup takes groups of `spb` consecutive sites (a power of
+// two, 256 / spb threads each, every thread the lags r, r + 256 / spb, ...) and
+// adds its lag sums to the global ones once at the end.  Bound: FP64 vector
+// arithmetic, 3 n_o multiply-adds per site and lag, twice that with the
+// dropped products.  The pieces are split once per sample and origin (split
+// again in every product the kernel took 3.8 ms at sc 36^3 x 256 lags and 25 us
+// at sc 8^3 x 64), and spb shrinks until the chip is filled (16 sites per
+// workgroup left sc 8^3 with 32 workgroups, and larger samples with one
+// workgroup per compute unit).
 // Besides the exact self sum it forms, for split precisions, the lo*lo
 // product that the three-product contraction leaves out, restricted to the
 // i = j pairs, and adds it to bin 0 (the bin of zero displacement for every
 // bin kind).  On the diagonal that term has a fixed sign, so dropping it
 // would bias C(0, 0); off the diagonal it is unbiased rounding noise.
-template <bool USE_LDS, int PREC>
-__global__ __launch_bounds__(256) void self_kernel(SelfArgs a, int sites_per_block) {
-    extern __shared__ float ser[];  // [t_need][sites_per_block][3]
-    __shared__ double part[1024];
-    __shared__ double part_lo[1024];
+// The blocks from n_blocks on form the site sums (the frame sums were queued
+// before).
+template <int MODE, int PREC>
+__global__ __launch_bounds__(256) void self_kernel(SelfArgs a, int spb, int n_blocks) {
+    // sums per lag, then (except kSelfGlobal) the series [t_need][spb][3], per
+    // small piece the same, and the origin side
+    extern __shared__ double part[];
+    double* const part_lo = part + a.n_sel;
+    float* const ser = (float*)(part + 2 * a.n_sel);
+    constexpr int P = n_small<PREC>();
     const int tid = threadIdx.x;
-    const int64_t i0 = (int64_t)blockIdx.x * sites_per_block;
-    const int nsb = (int)((a.n - i0) < sites_per_block ? (a.n - i0) : sites_per_block);
-    if constexpr (USE_LDS) {
-        for (int64_t x = tid; x < a.t_need * nsb * 3; x += 256) {
-            const int64_t f = x / (nsb * 3);
-            const int64_t rem = x - f * nsb * 3;
-            ser[f * sites_per_block * 3 + rem] = a.frames[(f * a.n + i0) * 3 + rem];
-        }
+    if ((int)blockIdx.x >= n_blocks) {
+        const int l = ((int)blockIdx.x - n_blocks) * 256 + tid;
+        if (l < a.n_sel) site_sum(a, l);
+        return;
     }
+    const int w = spb * 3;  // values per frame
+    float* const lo = ser + a.t_need * w;                    // [P][t_need][spb][3]
+    float* const org = lo + P * a.t_need * w;                // [n_origins][spb][3] (kSelfPieces)
+    float* const org_lo = org + (int64_t)a.n_origins * w;    // [P][n_origins][spb][3]
+    const int tps = 256 / spb, q = tid / tps, r = tid % tps;
     for (int x = tid; x < a.n_sel; x += 256) {
         part[x] = 0.0;
         part_lo[x] = 0.0;
     }
-    __syncthreads();
-    const int q = tid / 16, r = tid % 16;
-    float mu[3] = {0.0f, 0.0f, 0.0f};  // origin-side average (connected form)
-    if (a.mean && q < nsb)
-        for (int c = 0; c < 3; ++c) mu[c] = a.mean[4 * (i0 + q) + c];
-    if (q < nsb) {
-        for (int l = r; l < a.n_sel; l += 16) {
-            const int t = a.lags[l];
-            double s = 0.0, sl = 0.0;
-            for (int o = 0; o < a.n_origins; ++o) {
-                const int64_t f0 = (int64_t)o * a.stride, f1 = f0 + t;
-                const float* x0;
-                const float* x1;
-                if constexpr (USE_LDS) {
-                    x0 = ser + (f0 * sites_per_block + q) * 3;
-                    x1 = ser + (f1 * sites_per_block + q) * 3;
-                } else {
-                    x0 = a.frames + (f0 * a.n + i0 + q) * 3;
-                    x1 = a.frames + (f1 * a.n + i0 + q) * 3;
-                }
+    for (int64_t i0 = (int64_t)blockIdx.x * spb; i0 < a.n; i0 += (int64_t)n_blocks * spb) {
+        const int nsb = (int)((a.n - i0) < spb ? (a.n - i0) : spb);
+        __syncthreads();
+        if constexpr (MODE != kSelfGlobal) {
+#pragma unroll 4
+            for (int x = tid; x < (int)a.t_need * w; x += 256) {
+                const int f = x / w, rem = x - f * w;
+                const float v = rem < nsb * 3 ? a.frames[((int64_t)f * a.n + i0) * 3 + rem] : 0.0f;
+                ser[x] = v;
+                if constexpr (MODE == kSelfPieces && P > 0) {
+                    float p[2];
+                    small_pieces<PREC>(v, p);
 #pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    const float u = x0[c] - mu[c];  // as the pack kernel forms it
-                    s += (double)u * (double)x1[c];
-                    if constexpr (PREC != SDC_PREC_FP32) sl += dropped_product<PREC>(u, x1[c]);
+                    for (int k = 0; k < P; ++k) lo[k * a.t_need * w + x] = p[k];
                 }
             }
-            if (a.det) {
-                atomicAdd(reinterpret_cast<unsigned long long*>(part) + l, to_fixed(s));
-                if constexpr (PREC != SDC_PREC_FP32)
-                    atomicAdd(reinterpret_cast<unsigned long long*>(part_lo) + l, to_fixed(sl));
-            } else {
-                atomicAdd(&part[l], s);
-                if constexpr (PREC != SDC_PREC_FP32) atomicAdd(&part_lo[l], sl);
-            }
+            __syncthreads();
         }
+        if constexpr (MODE == kSelfPieces) {
+            for (int x = tid; x < a.n_origins * w; x += 256) {
+                const int o = x / w, rem = x - o * w;
+                if (rem >= nsb * 3) continue;
+                const int64_t y = (int64_t)o * a.stride * w + rem;
+                if (a.mean) {  // as the pack kernel forms it
+                    const float u = ser[y] - a.mean[4 * (i0 + rem / 3) + rem % 3];
+                    org[x] = u;
+                    float p[2];
+                    small_pieces<PREC>(u, p);
+#pragma unroll
+                    for (int k = 0; k < P; ++k) org_lo[k * a.n_origins * w + x] = p[k];
+                } else {
+                    org[x] = ser[y];
+#pragma unroll
+                    for (int k = 0; k < P; ++k) org_lo[k * a.n_origins * w + x] = lo[k * a.t_need * w + y];
+                }
+            }
+            __syncthreads();
+        }
+        if (q >= nsb) continue;
+        float mu[3] = {0.0f, 0.0f, 0.0f};  // origin-side average (connected form)
+        if (MODE != kSelfPieces && a.mean)
+            for (int c = 0; c < 3; ++c) mu[c] = a.mean[4 * (i0 + q) + c];
+        // lags l, l + tps, ... of the site, L at a time: L lags share the
+        // reads and conversions of the origin side
+        auto lags = [&](auto count, int l) {
+            constexpr int L = decltype(count)::value;
+            double s[L] = {}, sl[L] = {};
+            if constexpr (MODE == kSelfPieces) {
+                const float* x0 = org + 3 * q;
+                const float* l0 = org_lo + 3 * q;
+                const int step = a.stride * w, pa = a.n_origins * w, pb = (int)a.t_need * w;
+                int at[L];
+#pragma unroll
+                for (int j = 0; j < L; ++j) at[j] = a.lags[l + j * tps] * w + 3 * q;
+#pragma unroll 2
+                for (int o = 0; o < a.n_origins; ++o) {
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) {
+                        const double x = (double)x0[o * w + c];
+                        float u[2];
+#pragma unroll
+                        for (int k = 0; k < P; ++k) u[k] = l0[k * pa + o * w + c];
+#pragma unroll
+                        for (int j = 0; j < L; ++j) {
+                            const int y = at[j] + o * step + c;
+                            s[j] += x * (double)ser[y];
+                            if constexpr (P > 0) {
+                                float v[2];
+#pragma unroll
+                                for (int k = 0; k < P; ++k) v[k] = lo[k * pb + y];
+                                sl[j] += dropped_product<PREC>(u, v);
+                            }
+                        }
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int j = 0; j < L; ++j) {
+                    const int t = a.lags[l + j * tps];
+                    for (int o = 0; o < a.n_origins; ++o) {
+                        const int64_t f0 = (int64_t)o * a.stride, f1 = f0 + t;
+                        const float* x0 = MODE == kSelfSeries ? ser + f0 * w + 3 * q : a.frames + (f0 * a.n + i0 + q) * 3;
+                        const float* x1 = MODE == kSelfSeries ? ser + f1 * w + 3 * q : a.frames + (f1 * a.n + i0 + q) * 3;
+#pragma unroll
+                        for (int c = 0; c < 3; ++c) {
+                            const float u = x0[c] - mu[c];  // as the pack kernel forms it
+                            s[j] += (double)u * (double)x1[c];
+                            if constexpr (P > 0) {
+                                float pu[2], pv[2];
+                                small_pieces<PREC>(u, pu);
+                                small_pieces<PREC>(x1[c], pv);
+                                sl[j] += dropped_product<PREC>(pu, pv);
+                            }
+                        }
+                    }
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < L; ++j) {
+                const int k = l + j * tps;
+                if (a.det) {
+                    atomicAdd(reinterpret_cast<unsigned long long*>(part) + k, to_fixed(s[j]));
+                    if constexpr (P > 0) atomicAdd(reinterpret_cast<unsigned long long*>(part_lo) + k, to_fixed(sl[j]));
+                } else {
+                    atomicAdd(&part[k], s[j]);
+                    if constexpr (P > 0) atomicAdd(&part_lo[k], sl[j]);
+                }
+            }
+        };
+        int l = r;
+        if constexpr (MODE == kSelfPieces)
+            for (; l + 3 * tps < a.n_sel; l += 4 * tps) lags(std::integral_constant<int, 4>{}, l);
+        for (; l < a.n_sel; l += tps) lags(std::integral_constant<int, 1>{}, l);
     }
     __syncthreads();
     // origin totals live on the device so that replays of a captured
@@ -1111,81 +1278,28 @@ __global__ __launch_bounds__(256) void self_kernel(SelfArgs a, int sites_per_blo
     for (int l = tid; l < a.n_sel; l += 256) {
         if (a.det) {
             atomicAdd(&a.selfq[a.lags[l]], reinterpret_cast<const unsigned long long*>(part)[l]);
-            if constexpr (PREC != SDC_PREC_FP32)
+            if constexpr (P > 0)
                 atomicAdd(&a.Hq[(int64_t)a.lags[l] * a.n_bins], reinterpret_cast<const unsigned long long*>(part_lo)[l]);
         } else {
             unsafeAtomicAdd(&a.self[a.lags[l]], part[l]);
-            if constexpr (PREC != SDC_PREC_FP32)
-                unsafeAtomicAdd(&a.H[(int64_t)a.lags[l] * a.n_bins], part_lo[l]);
+            if constexpr (P > 0) unsafeAtomicAdd(&a.H[(int64_t)a.lags[l] * a.n_bins], part_lo[l]);
         }
     }
 }
 
-template <bool USE_LDS>
-static void launch_self_kind(const SelfArgs& a, dim3 grid, int lds, hipStream_t s, int spb) {
-    switch (a.precision) {
-        case SDC_PREC_SPLIT_BF16:
-            hipLaunchKernelGGL((self_kernel<USE_LDS, SDC_PREC_SPLIT_BF16>), grid, dim3(256), lds, s, a, spb);
-            break;
-        case SDC_PREC_SPLIT_FP16:
-            hipLaunchKernelGGL((self_kernel<USE_LDS, SDC_PREC_SPLIT_FP16>), grid, dim3(256), lds, s, a, spb);
-            break;
-        case SDC_PREC_BF16X3:
-            hipLaunchKernelGGL((self_kernel<USE_LDS, SDC_PREC_BF16X3>), grid, dim3(256), lds, s, a, spb);
-            break;
-        default:
-            hipLaunchKernelGGL((self_kernel<USE_LDS, SDC_PREC_FP32>), grid, dim3(256), lds, s, a, spb);
-            break;
+template <int MODE>
+static const void* self_fn(int precision) {
+    switch (precision) {
+        case SDC_PREC_SPLIT_BF16: return (const void*)self_kernel<MODE, SDC_PREC_SPLIT_BF16>;
+        case SDC_PREC_SPLIT_FP16: return (const void*)self_kernel<MODE, SDC_PREC_SPLIT_FP16>;
+        case SDC_PREC_BF16X3: return (const void*)self_kernel<MODE, SDC_PREC_BF16X3>;
+        default: return (const void*)self_kernel<MODE, SDC_PREC_FP32>;
     }
 }
-
-// Site-summed spin M(f) = sum_i S_i(f) of every frame the accumulate reads,
-// in FP64: one workgroup per frame.
-__global__ __launch_bounds__(256) void magnet_kernel(const float* __restrict__ frames, int64_t n,
-                                                     double* __restrict__ M) {
-    __shared__ double red[3][256];
-    const int64_t f = blockIdx.x;
-    const float* x = frames + f * n * 3;
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-    for (int64_t i = threadIdx.x; i < n; i += 256) {
-        s0 += (double)x[3 * i];
-        s1 += (double)x[3 * i + 1];
-        s2 += (double)x[3 * i + 2];
-    }
-    red[0][threadIdx.x] = s0;
-    red[1][threadIdx.x] = s1;
-    red[2][threadIdx.x] = s2;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w)
-            for (int c = 0; c < 3; ++c) red[c][threadIdx.x] += red[c][threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x < 3) M[f * 3 + threadIdx.x] = red[threadIdx.x][0];
-}
-
-// Site-summed correlation of each selected lag: the sum over all ordered
-// pairs of S_i(o s) . S_j(o s + t) equals M(o s) . M(o s + t), summed over
-// the origins in FP64 (one thread per lag).
-// For the connected form the origin side is centred: the sum over all pairs
-// of (S_i(o s) - <S_i>) . S_j(o s + t) is (M(o s) - <M>) . M(o s + t).
-__global__ __launch_bounds__(256) void msum_kernel(SelfArgs a) {
-    const int l = blockIdx.x * blockDim.x + threadIdx.x;
-    if (l >= a.n_sel) return;
-    const int t = a.lags[l];
-    double mb[3] = {0.0, 0.0, 0.0};
-    if (a.mean) {
-        for (int o = 0; o < a.n_origins; ++o)
-            for (int c = 0; c < 3; ++c) mb[c] += a.mframe[(int64_t)o * a.stride * 3 + c];
-        for (int c = 0; c < 3; ++c) mb[c] /= (double)a.n_origins;
-    }
-    double s = 0.0;
-    for (int o = 0; o < a.n_origins; ++o) {
-        const double* m0 = a.mframe + (int64_t)o * a.stride * 3;
-        const double* m1 = m0 + (int64_t)t * 3;
-        s += (m0[0] - mb[0]) * m1[0] + (m0[1] - mb[1]) * m1[1] + (m0[2] - mb[2]) * m1[2];
-    }
-    a.msum[t] += s;
+static const void* self_kernel_of(int mode, int precision) {
+    return mode == kSelfPieces   ? self_fn<kSelfPieces>(precision)
+           : mode == kSelfSeries ? self_fn<kSelfSeries>(precision)
+                                 : self_fn<kSelfGlobal>(precision);
 }
 
 __global__ __launch_bounds__(256) void mean_kernel(const float* __restrict__ frames, int64_t n, int n_origins,
@@ -1215,20 +1329,25 @@ int launch_mean(const float* frames, int64_t n, int n_origins, int stride, float
 int launch_self(const SelfArgs& a, void* stream) {
     if (a.n_sel == 0) return 0;
     if (a.n_sel > 1024) return (int)hipErrorInvalidValue;
-    const int64_t budget = kSelfLdsBudget;
-    const int64_t per_site = a.t_need * 3 * (int64_t)sizeof(float);
-    hipStream_t s = (hipStream_t)stream;
-    if (per_site <= budget) {
-        int spb = (int)(budget / per_site);
-        if (spb > 16) spb = 16;
-        const int lds = (int)(a.t_need * spb * 3 * sizeof(float));
-        launch_self_kind<true>(a, dim3((unsigned)((a.n + spb - 1) / spb)), lds, s, spb);
-    } else {
-        launch_self_kind<false>(a, dim3((unsigned)((a.n + 15) / 16)), 0, s, 16);
-    }
-    hipLaunchKernelGGL(magnet_kernel, dim3((unsigned)a.t_need), dim3(256), 0, s, a.frames, a.n, a.mframe);
-    hipLaunchKernelGGL(msum_kernel, dim3((unsigned)((a.n_sel + 255) / 256)), dim3(256), 0, s, a);
-    return (int)hipGetLastError();
+    const int pieces = a.precision == SDC_PREC_FP32 ? 0 : a.precision == SDC_PREC_BF16X3 ? 2 : 1;
+    int mode = kSelfPieces;
+    while (mode != kSelfGlobal && self_floats(mode, pieces, a.t_need, a.n_origins) * 4 > kSelfLdsBudget) --mode;
+    // sites per workgroup: at most 16, few enough for four workgroups per
+    // compute unit (256 of them) both by their number and by their LDS, but
+    // enough to give every thread a lag (more workgroups than that only queue
+    // their atomics on the sums: sc 8^3 x 64 lags took 16 us with one site per
+    // workgroup)
+    const int64_t per_site = self_floats(mode, pieces, a.t_need, a.n_origins) * 4, sums = (int64_t)16 * a.n_sel;
+    int spb = 16;
+    while (spb > 1 && (spb * per_site + sums > 40 * 1024 || (a.n < (int64_t)1024 * spb && a.n_sel * spb > 256)))
+        spb /= 2;
+    // 1024 workgroups share the sites: each adds 2 n_sel sums to global memory
+    const int64_t groups = (a.n + spb - 1) / spb;
+    int n_blocks = (int)(groups < 1024 ? groups : 1024);
+    SelfArgs args = a;
+    void* params[] = {(void*)&args, (void*)&spb, (void*)&n_blocks};
+    return (int)hipLaunchKernel(self_kernel_of(mode, a.precision), dim3((unsigned)(n_blocks + (a.n_sel + 255) / 256)),
+                                dim3(256), params, (size_t)(spb * per_site + sums), (hipStream_t)stream);
 }
 
 // Dynamic-LDS limits of every kernel that takes more than the default, set
@@ -1245,14 +1364,13 @@ int prepare_kernels() {
                 hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxFusedLds);
                 if (e != hipSuccess) return (int)e;
             }
-    const void* self[] = {(const void*)self_kernel<true, SDC_PREC_FP32>,
-                          (const void*)self_kernel<true, SDC_PREC_SPLIT_BF16>,
-                          (const void*)self_kernel<true, SDC_PREC_SPLIT_FP16>,
-                          (const void*)self_kernel<true, SDC_PREC_BF16X3>};
-    for (const void* f : self) {
-        hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSelfLdsBudget);
-        if (e != hipSuccess) return (int)e;
-    }
+    for (int prec = SDC_PREC_FP32; prec <= SDC_PREC_BF16X3; ++prec)
+        for (int mode = kSelfSeries; mode <= kSelfPieces; ++mode) {
+            const hipError_t e = hipFuncSetAttribute(self_kernel_of(mode, prec),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                     (int)kSelfLdsBudget + 16 * 1024);
+            if (e != hipSuccess) return (int)e;
+        }
     return 0;
 }
 
@@ -1260,48 +1378,106 @@ int prepare_kernels() {
 // finalize: normalisation, site sums, windowed DFT (all FP64)
 // ---------------------------------------------------------------------------
 
-__global__ void normalize_kernel(FinalArgs a) {
-    const int64_t total = (int64_t)a.n_lags * a.n_bins;
-    for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < total;
-         x += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t t = x / a.n_bins;
-        const int64_t b = x - t * a.n_bins;
-        const double den = a.n_org[t] * (double)a.counts[b];
-        a.C[x] = den > 0.0 ? a.H[x] / den : 0.0;
-    }
-}
-
-// Site-summed and self correlations per lag.  The site sum comes from the
-// magnetisation products (an exact identity for the sum of H over all
-// bins), which keeps the per-bin rounding of the reduced-precision products
-// from adding up over N^2 pairs.
-__global__ __launch_bounds__(256) void sums_kernel(FinalArgs a) {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= a.n_lags) return;
-    const double d = (double)a.n_sites * a.n_org[t];
-    a.csum[t] = d > 0.0 ? a.msum[t] / d : 0.0;
-    a.cself[t] = d > 0.0 ? a.self[t] / d : 0.0;
-}
-
-__global__ void dft_kernel(FinalArgs a) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    const int m = a.n_lags;
-    if (k >= m) return;
-    double re0 = 0, im0 = 0, re1 = 0, im1 = 0;
-    for (int t = 0; t < m; ++t) {
+// Windowed DFT over the lags of NS complex series x of length m:
+// out[k] = sum_t w_t x_t exp(-2 pi i k t / m), w_t = (1 + cos(pi t / m)) / 2, for 64 k per
+// workgroup (k0 + tid % 64), a quarter of the t per thread group.  lds holds
+// the m phases and then the windowed series (2 + 2 NS doubles per t), filled
+// here; value(s, t, re, im) gives x.  The phases come from one table of m
+// sines and cosines instead of one pair per (k, t): with those the kernel of
+// 256 lags took 56 us.
+template <int NS, class Value, class Store>
+__device__ inline void lag_dft(int m, int k0, double* lds, const Value& value, const Store& store) {
+    double* const cs = lds;
+    double* const sn = lds + m;
+    double* const x = lds + 2 * m;  // [NS][2][m]
+    for (int t = threadIdx.x; t < m; t += 256) {
+        sincospi(-2.0 * (double)t / (double)m, &sn[t], &cs[t]);
         const double w = 0.5 * (1.0 + cospi((double)t / (double)m));
-        const int64_t kt = ((int64_t)k * t) % m;
-        double sn, cs;
-        sincospi(-2.0 * (double)kt / (double)m, &sn, &cs);
-        re0 += w * a.csum[t] * cs;
-        im0 += w * a.csum[t] * sn;
-        re1 += w * a.cself[t] * cs;
-        im1 += w * a.cself[t] * sn;
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            double re, im;
+            value(s, t, re, im);
+            x[2 * s * m + t] = w * re;
+            x[(2 * s + 1) * m + t] = w * im;
+        }
     }
-    a.ssum[2 * k] = re0;
-    a.ssum[2 * k + 1] = im0;
-    a.sself[2 * k] = re1;
-    a.sself[2 * k + 1] = im1;
+    __syncthreads();
+    const int k = k0 + (int)(threadIdx.x & 63), g = threadIdx.x >> 6;
+    const int t0 = g * m / 4, t1 = (g + 1) * m / 4;
+    double re[NS] = {}, im[NS] = {};
+    if (k < m) {
+        int kt = (int)(((int64_t)k * t0) % m);
+        for (int t = t0; t < t1; ++t) {
+            const double c = cs[kt], d = sn[kt];
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+                const double xr = x[2 * s * m + t], xi = x[(2 * s + 1) * m + t];
+                re[s] += xr * c - xi * d;
+                im[s] += xr * d + xi * c;
+            }
+            kt += k;
+            if (kt >= m) kt -= m;
+        }
+    }
+    __syncthreads();
+    double* const red = lds;  // [4][64][2 NS] in the space of the tables
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        red[(threadIdx.x * NS + s) * 2] = re[s];
+        red[(threadIdx.x * NS + s) * 2 + 1] = im[s];
+    }
+    __syncthreads();
+    if (g == 0 && k < m) {
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            double r = 0.0, i = 0.0;
+            for (int h = 0; h < 4; ++h) {
+                r += red[((threadIdx.x + 64 * h) * NS + s) * 2];
+                i += red[((threadIdx.x + 64 * h) * NS + s) * 2 + 1];
+            }
+            store(s, k, r, i);
+        }
+    }
+}
+template <int NS>
+static int lag_dft_lds(int m) {
+    const int tables = (2 + 2 * NS) * m, red = 256 * 2 * NS;
+    return (tables > red ? tables : red) * (int)sizeof(double);
+}
+
+// Rows 0 .. n_lags - 1 of the grid normalise H (when C is asked for); the
+// blocks of the rows after them form the site-summed and self correlations
+// and their spectra, 64 frequencies each.  The site sum comes from the
+// magnetisation products (an exact identity for the sum of H over all bins),
+// which keeps the per-bin rounding of the reduced-precision products from
+// adding up over N^2 pairs.
+__global__ __launch_bounds__(256) void finalize_kernel(FinalArgs a) {
+    extern __shared__ double lds[];
+    const int rows = a.C ? a.n_lags : 0;
+    if ((int)blockIdx.y < rows) {
+        const int t = blockIdx.y;
+        const double no = a.n_org[t];
+        for (int64_t b = (int64_t)blockIdx.x * 256 + threadIdx.x; b < a.n_bins; b += (int64_t)gridDim.x * 256) {
+            const double den = no * (double)a.counts[b];
+            a.C[t * a.n_bins + b] = den > 0.0 ? a.H[t * a.n_bins + b] / den : 0.0;
+        }
+        return;
+    }
+    const int k0 = (((int)blockIdx.y - rows) * (int)gridDim.x + (int)blockIdx.x) * 64;
+    if (k0 >= a.n_lags) return;
+    lag_dft<2>(
+        a.n_lags, k0, lds,
+        [&](int s, int t, double& re, double& im) {
+            const double d = (double)a.n_sites * a.n_org[t];
+            re = d > 0.0 ? (s == 0 ? a.msum[t] : a.self[t]) / d : 0.0;
+            im = 0.0;
+            if (k0 == 0) (s == 0 ? a.csum : a.cself)[t] = re;
+        },
+        [&](int s, int k, double re, double im) {
+            double* out = (s == 0 ? a.ssum : a.sself) + 2 * k;
+            out[0] = re;
+            out[1] = im;
+        });
 }
 
 // One workgroup per (q, lag): S(q, t) = sum_b exp(-i q.d_b) H(b, t) / (N n_org),
@@ -1348,29 +1524,31 @@ __global__ __launch_bounds__(256) void sqt_kernel(SqtArgs a) {
 }
 
 // Windowed DFT over the lags of each q (same window as the site sums).
-__global__ void sqw_kernel(const double* __restrict__ sqt, double* __restrict__ sqw, int m) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    const int qi = blockIdx.y;
-    if (k >= m) return;
-    const double* x = sqt + (int64_t)qi * m * 2;
-    double re = 0.0, im = 0.0;
-    for (int t = 0; t < m; ++t) {
-        const double w = 0.5 * (1.0 + cospi((double)t / (double)m));
-        const int64_t kt = ((int64_t)k * t) % m;
-        double sn, cs;
-        sincospi(-2.0 * (double)kt / (double)m, &sn, &cs);
-        // (x_re + i x_im)(cs + i sn)
-        re += w * (x[2 * t] * cs - x[2 * t + 1] * sn);
-        im += w * (x[2 * t] * sn + x[2 * t + 1] * cs);
-    }
-    sqw[((int64_t)qi * m + k) * 2] = re;
-    sqw[((int64_t)qi * m + k) * 2 + 1] = im;
+__global__ __launch_bounds__(256) void sqw_kernel(const double* __restrict__ sqt, double* __restrict__ sqw, int m) {
+    extern __shared__ double lds[];
+    const double* x = sqt + (int64_t)blockIdx.y * m * 2;
+    double* out = sqw + (int64_t)blockIdx.y * m * 2;
+    lag_dft<1>(
+        m, (int)blockIdx.x * 64, lds,
+        [&](int, int t, double& re, double& im) {
+            re = x[2 * t];
+            im = x[2 * t + 1];
+        },
+        [&](int, int k, double re, double im) {
+            out[2 * k] = re;
+            out[2 * k + 1] = im;
+        });
 }
 
 int launch_sqw(const double* sqt, double* sqw, int n_q, int n_lags, void* stream) {
     if (n_q == 0) return 0;
-    hipLaunchKernelGGL(sqw_kernel, dim3((unsigned)((n_lags + 63) / 64), (unsigned)n_q), dim3(64), 0,
-                       (hipStream_t)stream, sqt, sqw, n_lags);
+    // gridDim.y is at most 65535
+    for (int q = 0; q < n_q; q += 65535) {
+        const int nq = n_q - q < 65535 ? n_q - q : 65535;
+        hipLaunchKernelGGL(sqw_kernel, dim3((unsigned)((n_lags + 63) / 64), (unsigned)nq), dim3(256),
+                           lag_dft_lds<1>(n_lags), (hipStream_t)stream, sqt + (int64_t)q * n_lags * 2,
+                           sqw + (int64_t)q * n_lags * 2, n_lags);
+    }
     return (int)hipGetLastError();
 }
 
@@ -1382,22 +1560,23 @@ int launch_sqt(const SqtArgs& a, void* stream) {
 }
 
 int launch_finalize(const FinalArgs& a, void* stream) {
-    hipStream_t s = (hipStream_t)stream;
-    if (a.C) {
-        const int64_t total = (int64_t)a.n_lags * a.n_bins;
-        int64_t blocks = (total + 255) / 256;
-        if (blocks > 8192) blocks = 8192;
-        hipLaunchKernelGGL(normalize_kernel, dim3((unsigned)blocks), dim3(256), 0, s, a);
-    }
-    hipLaunchKernelGGL(sums_kernel, dim3((a.n_lags + 255) / 256), dim3(256), 0, s, a);
-    hipLaunchKernelGGL(dft_kernel, dim3((a.n_lags + 63) / 64), dim3(64), 0, s, a);
+    int64_t gx = a.C ? (a.n_bins + 255) / 256 : 1;
+    if (gx > 256) gx = 256;
+    const int64_t n_dft = (a.n_lags + 63) / 64;
+    const int64_t gy = (a.C ? a.n_lags : 0) + (n_dft + gx - 1) / gx;
+    hipLaunchKernelGGL(finalize_kernel, dim3((unsigned)gx, (unsigned)gy), dim3(256), lag_dft_lds<2>(a.n_lags),
+                       (hipStream_t)stream, a);
     return (int)hipGetLastError();
 }
 
-__global__ void zero_kernel(uint32_t* p, int64_t words) {
-    for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < words;
-         x += (int64_t)gridDim.x * blockDim.x)
-        p[x] = 0u;
+__global__ __launch_bounds__(256) void zero_kernel(ZeroRanges z) {
+    for (int k = 0; k < z.n; ++k) {
+        uint32_t* p = (uint32_t*)z.ptr[k];
+        const int64_t words = z.bytes[k] / 4;
+        for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < words;
+             x += (int64_t)gridDim.x * blockDim.x)
+            p[x] = 0u;
+    }
 }
 
 __global__ void fixed_to_double_kernel(const unsigned long long* __restrict__ q, double* __restrict__ d, int64_t n) {
@@ -1427,14 +1606,20 @@ int launch_double_to_fixed(const double* d, unsigned long long* q, int64_t n, vo
     return (int)hipGetLastError();
 }
 
-int launch_zero(void* ptr, int64_t bytes, void* stream) {
-    if (bytes <= 0) return 0;
-    const int64_t words = bytes / 4;
+int launch_zero_ranges(const ZeroRanges& z, void* stream) {
+    int64_t words = 0;
+    for (int k = 0; k < z.n; ++k) words = z.bytes[k] / 4 > words ? z.bytes[k] / 4 : words;
+    if (words <= 0) return 0;
     int64_t blocks = (words + 255) / 256;
     if (blocks > 4096) blocks = 4096;
-    hipLaunchKernelGGL(zero_kernel, dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream,
-                       (uint32_t*)ptr, words);
+    hipLaunchKernelGGL(zero_kernel, dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream, z);
     return (int)hipGetLastError();
+}
+
+int launch_zero(void* ptr, int64_t bytes, void* stream) {
+    ZeroRanges z{};
+    z.add(ptr, bytes);
+    return launch_zero_ranges(z, stream);
 }
 
 // ---------------------------------------------------------------------------
