@@ -90,6 +90,16 @@ std::vector<KGroup> make_groups(const std::vector<int>& lags, int s, int lg) {
 
 sdc_status sdc::set_error(sdc_status s, const std::string& msg) { return set_err(s, msg); }
 
+// Results of a plan up to this size (C and the counts) are written by the
+// finalize kernel into the plan's own pinned host buffer and copied from
+// there by the host.  A copy into the caller's pageable memory is a blocking
+// staged transfer of 11 to 32 us: finalize of sc 8^3 x 64 lags took 77 us with
+// three of them, 33 us without.  Larger results amortise it (and save the
+// second host copy).
+constexpr size_t kPinnedResultBytes = (size_t)512 << 10;
+// Largest scratch of the structure factor that a plan keeps between calls.
+constexpr size_t kMaxKeptScratch = (size_t)64 << 20;
+
 // Largest radial key table kept per plan (2 bytes per ordered tile-pair slot).
 constexpr size_t kMaxKeyTableBytes = (size_t)32 << 30;
 
@@ -127,7 +137,11 @@ struct sdc_plan {
     unsigned long long* d_Hq = nullptr;     // deterministic mode: fixed-point H
     unsigned long long* d_selfq = nullptr;  // deterministic mode: fixed-point self sums
     double* d_C = nullptr;
-    double* d_fin = nullptr;  // csum, cself, ssum[2], sself[2]
+    double* h_fin = nullptr;  // pinned: csum, cself, ssum[2], sself[2], then (small plans) C and the counts
+    double* h_C = nullptr;    // [n_lags][n_bins] in h_fin's buffer, or null
+    unsigned long long* h_counts = nullptr;
+    void* d_sqt = nullptr;    // scratch of the structure factor (wave vectors, S(q, t), S(q, w))
+    size_t sqt_bytes = 0;
     void* d_A = nullptr;
     void* d_B = nullptr;
     size_t bytes_A = 0, bytes_B = 0;
@@ -142,6 +156,8 @@ struct sdc_plan {
         for (hipEvent_t e : ev)
             if (e) (void)hipEventDestroy(e);
         for (void* p : owned) (void)hipFree(p);
+        if (d_sqt) (void)hipFree(d_sqt);
+        if (h_fin) (void)hipHostFree(h_fin);
     }
 };
 
@@ -545,7 +561,20 @@ sdc_status sdc_plan_create_tuned(const float* positions_host, int64_t n_sites, c
         TRYHIP(hipMemset(p->d_Hq, 0, (size_t)corr->n_lags * L.n_bins * 8), "zero fixed-point H");
         TRYHIP(hipMemset(p->d_selfq, 0, (size_t)corr->n_lags * 8), "zero fixed-point self sums");
     }
-    TRY(dalloc(&p->d_fin, (size_t)6 * corr->n_lags, &p->owned));
+    {
+        const size_t fin = (size_t)6 * corr->n_lags, cells = (size_t)corr->n_lags * L.n_bins + (size_t)L.n_bins;
+        const bool small = cells * 8 <= kPinnedResultBytes;
+        if (hipHostMalloc((void**)&p->h_fin, (fin + (small ? cells : 0)) * 8, hipHostMallocDefault) != hipSuccess) {
+            (void)hipGetLastError();
+            p->h_fin = nullptr;
+            delete p;
+            return set_err(SDC_ERR_OOM, "hipHostMalloc failed");
+        }
+        if (small) {
+            p->h_C = p->h_fin + fin;
+            p->h_counts = (unsigned long long*)(p->h_C + (size_t)corr->n_lags * L.n_bins);
+        }
+    }
     TRY(dalloc((char**)&p->d_A, p->bytes_A, &p->owned));
     TRY(dalloc((char**)&p->d_B, p->bytes_B, &p->owned));
 
@@ -667,7 +696,7 @@ sdc_status sdc_finalize(sdc_plan* p, double* C_host, uint64_t* counts_host, doub
     const Layout& L = p->lay;
     const int nl = p->corr.n_lags;
     hipStream_t hs = (hipStream_t)stream;
-    if (C_host && !p->d_C) {
+    if (C_host && !p->h_C && !p->d_C) {
         s = dalloc(&p->d_C, (size_t)nl * L.n_bins, &p->owned);
         if (s != SDC_OK) return s;
     }
@@ -687,32 +716,33 @@ sdc_status sdc_finalize(sdc_plan* p, double* C_host, uint64_t* counts_host, doub
     fa.n_bins = L.n_bins;
     fa.n_sites = L.n;
     fa.n_lags = nl;
-    fa.C = C_host ? p->d_C : nullptr;
-    fa.csum = p->d_fin;
-    fa.cself = p->d_fin + nl;
-    fa.ssum = p->d_fin + 2 * nl;
-    fa.sself = p->d_fin + 4 * nl;
+    fa.C = !C_host ? nullptr : p->h_C ? p->h_C : p->d_C;
+    fa.counts_out = C_host && counts_host ? p->h_counts : nullptr;  // null when there is no room for them
+    fa.csum = p->h_fin;
+    fa.cself = p->h_fin + nl;
+    fa.ssum = p->h_fin + 2 * nl;
+    fa.sself = p->h_fin + 4 * nl;
     int e = sdc::launch_finalize(fa, stream);
     if (e != 0) {
         p->failed = true;
         return hip_err(e, "finalize kernels");
     }
-    std::vector<double> fin(6 * (size_t)nl);
-    SDC_HIP(hipMemcpyAsync(fin.data(), p->d_fin, fin.size() * sizeof(double), hipMemcpyDeviceToHost, hs), "copy out");
-    if (C_host)
-        SDC_HIP(hipMemcpyAsync(C_host, p->d_C, (size_t)nl * L.n_bins * sizeof(double), hipMemcpyDeviceToHost, hs),
-                "copy C");
-    if (counts_host)
+    const size_t cells = (size_t)nl * L.n_bins;
+    if (C_host && !p->h_C)
+        SDC_HIP(hipMemcpyAsync(C_host, p->d_C, cells * sizeof(double), hipMemcpyDeviceToHost, hs), "copy C");
+    if (counts_host && !fa.counts_out)
         SDC_HIP(hipMemcpyAsync(counts_host, p->d_counts, (size_t)L.n_bins * 8, hipMemcpyDeviceToHost, hs), "copy counts");
     hipError_t se = hipStreamSynchronize(hs);
     if (se != hipSuccess) {
         p->failed = true;
         return hip_err((int)se, "finalize (or earlier queued work)");
     }
-    if (Csum_host) std::memcpy(Csum_host, fin.data(), nl * sizeof(double));
-    if (Cself_host) std::memcpy(Cself_host, fin.data() + nl, nl * sizeof(double));
-    if (Ssum_host) std::memcpy(Ssum_host, fin.data() + 2 * nl, 2 * nl * sizeof(double));
-    if (Sself_host) std::memcpy(Sself_host, fin.data() + 4 * nl, 2 * nl * sizeof(double));
+    if (C_host && p->h_C) std::memcpy(C_host, p->h_C, cells * sizeof(double));
+    if (fa.counts_out) std::memcpy(counts_host, p->h_counts, (size_t)L.n_bins * 8);
+    if (Csum_host) std::memcpy(Csum_host, p->h_fin, nl * sizeof(double));
+    if (Cself_host) std::memcpy(Cself_host, p->h_fin + nl, nl * sizeof(double));
+    if (Ssum_host) std::memcpy(Ssum_host, p->h_fin + 2 * nl, 2 * nl * sizeof(double));
+    if (Sself_host) std::memcpy(Sself_host, p->h_fin + 4 * nl, 2 * nl * sizeof(double));
     return SDC_OK;
 }
 
@@ -731,18 +761,29 @@ sdc_status sdc_plan_structure_factor(sdc_plan* p, const int32_t* m_host, int32_t
     SDC_HIP(select_device(p->device), "hipSetDevice");
     const int nl = p->corr.n_lags;
     const size_t out_n = (size_t)n_q * nl * 2;
-    std::vector<void*> tmp;
-    int32_t* d_m = nullptr;
-    double* d_out = nullptr;
-    s = dalloc(&d_m, (size_t)3 * n_q, &tmp);
-    if (s == SDC_OK) s = dalloc(&d_out, 2 * out_n, &tmp);
-    auto release = [&]() {
-        for (void* q : tmp) (void)hipFree(q);
-    };
-    if (s != SDC_OK) {
-        release();
-        return s;
+    // wave vectors (padded to 256 bytes), S(q, t), S(q, w); kept by the plan for
+    // the next call unless large
+    const size_t m_bytes = ((size_t)3 * n_q * sizeof(int32_t) + 255) / 256 * 256;
+    const size_t need = m_bytes + 2 * out_n * sizeof(double);
+    if (need > p->sqt_bytes) {
+        if (p->d_sqt) (void)hipFree(p->d_sqt);
+        p->d_sqt = nullptr;
+        p->sqt_bytes = 0;
+        if (hipMalloc(&p->d_sqt, need) != hipSuccess) {
+            (void)hipGetLastError();
+            p->d_sqt = nullptr;
+            return set_err(SDC_ERR_OOM, "hipMalloc failed");
+        }
+        p->sqt_bytes = need;
     }
+    int32_t* d_m = (int32_t*)p->d_sqt;
+    double* d_out = (double*)((char*)p->d_sqt + m_bytes);
+    auto release = [&]() {
+        if (p->sqt_bytes <= kMaxKeptScratch) return;
+        (void)hipFree(p->d_sqt);
+        p->d_sqt = nullptr;
+        p->sqt_bytes = 0;
+    };
     hipStream_t hs = (hipStream_t)stream;
     hipError_t he = hipMemcpyAsync(d_m, m_host, (size_t)3 * n_q * sizeof(int32_t), hipMemcpyHostToDevice, hs);
     if (he == hipSuccess) he = (hipError_t)refresh_fixed(p, stream);
@@ -1211,7 +1252,8 @@ struct sdc_sq {
     double* d_F = nullptr;     // [n_q][t_used][3][2]
     double* d_raw = nullptr;   // [n_q][n_lags][2]
     double* d_norg = nullptr;  // [1]
-    double* d_out = nullptr;   // [2][n_q][n_lags][2]: S(q, t), S(q, w)
+    double* d_out = nullptr;   // [2][n_q][n_lags][2]: S(q, t), S(q, w); small results: h_out
+    double* h_out = nullptr;   // the same in pinned host memory, or null (see kPinnedResultBytes)
     bool failed = false;
     hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
     bool timed = false;
@@ -1220,6 +1262,7 @@ struct sdc_sq {
         for (hipEvent_t e : ev)
             if (e) (void)hipEventDestroy(e);
         for (void* p : owned) (void)hipFree(p);
+        if (h_out) (void)hipHostFree(h_out);
     }
 };
 
@@ -1323,7 +1366,17 @@ sdc_status sdc_sq_create(const float* positions_host, int64_t n_sites, const dou
     SQ_TRY(dalloc(&q->d_F, (size_t)n_q * 2 * n_cols, &q->owned));
     SQ_TRY(dalloc(&q->d_raw, out_n, &q->owned));
     SQ_TRY(dalloc(&q->d_norg, 1, &q->owned));
-    SQ_TRY(dalloc(&q->d_out, 2 * out_n, &q->owned));
+    if (2 * out_n * sizeof(double) <= kPinnedResultBytes) {
+        if (hipHostMalloc((void**)&q->h_out, 2 * out_n * sizeof(double), hipHostMallocDefault) != hipSuccess) {
+            (void)hipGetLastError();
+            q->h_out = nullptr;
+            delete q;
+            return set_err(SDC_ERR_OOM, "hipHostMalloc failed");
+        }
+        q->d_out = q->h_out;
+    } else {
+        SQ_TRY(dalloc(&q->d_out, 2 * out_n, &q->owned));
+    }
 #undef SQ_TRY
     hipError_t e = hipMemcpy(q->d_pos, positions_host, (size_t)3 * n_sites * sizeof(float), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(q->d_q, q_host, (size_t)3 * n_q * sizeof(double), hipMemcpyHostToDevice);
@@ -1398,11 +1451,13 @@ sdc_status sdc_sq_finalize(sdc_sq* q, double* Sqt_host, double* Sqw_host, void* 
     const size_t out_n = (size_t)q->n_q * q->spec.n_lags * 2;
     int e = sdc::launch_sq_finalize(q->d_raw, q->d_norg, q->n, q->n_q, q->spec.n_lags, q->d_out, q->d_out + out_n,
                                     stream);
-    if (e == 0 && Sqt_host)
+    if (e == 0 && Sqt_host && !q->h_out)
         e = (int)hipMemcpyAsync(Sqt_host, q->d_out, out_n * sizeof(double), hipMemcpyDeviceToHost, hs);
-    if (e == 0 && Sqw_host)
+    if (e == 0 && Sqw_host && !q->h_out)
         e = (int)hipMemcpyAsync(Sqw_host, q->d_out + out_n, out_n * sizeof(double), hipMemcpyDeviceToHost, hs);
     if (e == 0) e = (int)hipStreamSynchronize(hs);
+    if (e == 0 && Sqt_host && q->h_out) std::memcpy(Sqt_host, q->h_out, out_n * sizeof(double));
+    if (e == 0 && Sqw_host && q->h_out) std::memcpy(Sqw_host, q->h_out + out_n, out_n * sizeof(double));
     if (e != 0) {
         q->failed = true;
         return hip_err(e, "structure factor finalize (or earlier queued work)");

@@ -326,6 +326,7 @@ struct FinalArgs {
     int64_t n_bins, n_sites;
     int n_lags;
     double* C;             // [n_lags][n_bins] or null
+    unsigned long long* counts_out;  // [n_bins] or null: a copy of the counts beside C
     double* csum;          // [n_lags]
     double* cself;         // [n_lags]
     double* ssum;          // [n_lags][2]
@@ -347,9 +348,11 @@ struct SqtArgs {
     double* sqw;           // [n_q][n_lags][2]
 };
 int launch_sqt(const SqtArgs& a, void* stream);
-// Windowed time transform of S(q, t) for every q (the window of the site sums):
-// sqw[q][k] = sum_t w_t sqt[q][t] exp(-2 pi i k t / n_lags), (re, im) pairs.
-int launch_sqw(const double* sqt, double* sqw, int n_q, int n_lags, void* stream);
+// Windowed time transform over the lags of every q (the window of the site
+// sums), (re, im) pairs: sqw[q][k] = sum_t w_t x[q][t] exp(-2 pi i k t / n_lags),
+// x = in, or with n_org (device [1]) x = in / (n_sites n_org), stored in sqt.
+int launch_sqw(const double* in, const double* n_org, int64_t n_sites, double* sqt, double* sqw, int n_q, int n_lags,
+               void* stream);
 
 // q-resolved S(q, t) of Eq. (3) at arbitrary wave vectors (sdc_sq.hip).
 struct SqTransformArgs {

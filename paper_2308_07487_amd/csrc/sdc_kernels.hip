@@ -1460,6 +1460,7 @@ __global__ __launch_bounds__(256) void finalize_kernel(FinalArgs a) {
         for (int64_t b = (int64_t)blockIdx.x * 256 + threadIdx.x; b < a.n_bins; b += (int64_t)gridDim.x * 256) {
             const double den = no * (double)a.counts[b];
             a.C[t * a.n_bins + b] = den > 0.0 ? a.H[t * a.n_bins + b] / den : 0.0;
+            if (t == 0 && a.counts_out) a.counts_out[b] = a.counts[b];
         }
         return;
     }
@@ -1541,31 +1542,44 @@ __global__ __launch_bounds__(256) void sqt_kernel(SqtArgs a) {
     }
 }
 
-// Windowed DFT over the lags of each q (same window as the site sums).
-__global__ __launch_bounds__(256) void sqw_kernel(const double* __restrict__ sqt, double* __restrict__ sqw, int m) {
+// Windowed DFT over the lags of each q (same window as the site sums).  With
+// n_org, x holds raw sums: they are divided by n_sites n_org[0] first, and the
+// quotients stored in sqt.
+__global__ __launch_bounds__(256) void sqw_kernel(const double* __restrict__ in, const double* __restrict__ n_org,
+                                                  int64_t n_sites, double* __restrict__ sqt,
+                                                  double* __restrict__ sqw, int m) {
     extern __shared__ double lds[];
-    const double* x = sqt + (int64_t)blockIdx.y * m * 2;
-    double* out = sqw + (int64_t)blockIdx.y * m * 2;
+    const int64_t at = (int64_t)blockIdx.y * m * 2;
+    const double* x = in + at;
+    const double d = n_org ? (double)n_sites * n_org[0] : 1.0;
     lag_dft<1>(
         m, (int)blockIdx.x * 64, lds,
         [&](int, int t, double& re, double& im) {
             re = x[2 * t];
             im = x[2 * t + 1];
+            if (n_org) {
+                re = d > 0.0 ? re / d : 0.0;
+                im = d > 0.0 ? im / d : 0.0;
+                if (blockIdx.x == 0) {
+                    sqt[at + 2 * t] = re;
+                    sqt[at + 2 * t + 1] = im;
+                }
+            }
         },
         [&](int, int k, double re, double im) {
-            out[2 * k] = re;
-            out[2 * k + 1] = im;
+            sqw[at + 2 * k] = re;
+            sqw[at + 2 * k + 1] = im;
         });
 }
 
-int launch_sqw(const double* sqt, double* sqw, int n_q, int n_lags, void* stream) {
-    if (n_q == 0) return 0;
-    // gridDim.y is at most 65535
-    for (int q = 0; q < n_q; q += 65535) {
+int launch_sqw(const double* in, const double* n_org, int64_t n_sites, double* sqt, double* sqw, int n_q, int n_lags,
+               void* stream) {
+    for (int q = 0; q < n_q; q += 65535) {  // rows of one grid
         const int nq = n_q - q < 65535 ? n_q - q : 65535;
+        const int64_t at = (int64_t)q * n_lags * 2;
         hipLaunchKernelGGL(sqw_kernel, dim3((unsigned)((n_lags + 63) / 64), (unsigned)nq), dim3(256),
-                           lag_dft_lds<1>(n_lags), (hipStream_t)stream, sqt + (int64_t)q * n_lags * 2,
-                           sqw + (int64_t)q * n_lags * 2, n_lags);
+                           lag_dft_lds<1>(n_lags), (hipStream_t)stream, in + at, n_org, n_sites,
+                           sqt ? sqt + at : nullptr, sqw + at, n_lags);
     }
     return (int)hipGetLastError();
 }
@@ -1575,7 +1589,7 @@ int launch_sqt(const SqtArgs& a, void* stream) {
     hipLaunchKernelGGL(sqt_kernel, dim3((unsigned)a.n_q, (unsigned)((a.n_lags + kSqtLags - 1) / kSqtLags)), dim3(256),
                        0, (hipStream_t)stream, a);
     const int e = (int)hipGetLastError();
-    return e != 0 ? e : launch_sqw(a.sqt, a.sqw, a.n_q, a.n_lags, stream);
+    return e != 0 ? e : launch_sqw(a.sqt, nullptr, 0, nullptr, a.sqw, a.n_q, a.n_lags, stream);
 }
 
 int launch_finalize(const FinalArgs& a, void* stream) {

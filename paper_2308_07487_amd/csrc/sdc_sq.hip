@@ -309,13 +309,6 @@ __global__ __launch_bounds__(256) void sq_corr_kernel(SqCorrArgs a) {
     if (qq == 0 && threadIdx.x == 0) a.n_org[0] += (double)a.n_origins;
 }
 
-__global__ __launch_bounds__(256) void sq_norm_kernel(const double* __restrict__ raw, const double* __restrict__ n_org,
-                                                      int64_t n_sites, int64_t count, double* __restrict__ sqt) {
-    const double d = (double)n_sites * n_org[0];
-    for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < count; x += (int64_t)gridDim.x * blockDim.x)
-        sqt[x] = d > 0.0 ? raw[x] / d : 0.0;
-}
-
 dim3 sq_transform_grid(int n_q, int n_frames_used, int n_split) {
     return dim3((unsigned)((n_q + kSqQ - 1) / kSqQ), (unsigned)((n_frames_used + kSqFrames - 1) / kSqFrames),
                 (unsigned)n_split);
@@ -364,11 +357,7 @@ int launch_sq_corr(const SqTransformArgs& t, const SqCorrArgs& a, void* stream) 
 
 int launch_sq_finalize(const double* raw, const double* n_org, int64_t n_sites, int n_q, int n_lags, double* sqt,
                        double* sqw, void* stream) {
-    const int64_t count = (int64_t)n_q * n_lags * 2;
-    hipLaunchKernelGGL(sq_norm_kernel, dim3((unsigned)blocks_for(count)), dim3(256), 0, (hipStream_t)stream, raw,
-                       n_org, n_sites, count, sqt);
-    const int e = (int)hipGetLastError();
-    return e != 0 ? e : launch_sqw(sqt, sqw, n_q, n_lags, stream);
+    return launch_sqw(raw, n_org, n_sites, sqt, sqw, n_q, n_lags, stream);
 }
 
 }  // namespace sdc

@@ -358,13 +358,12 @@ class Plan:
         counts = np.zeros(nb, dtype=np.uint64)
         cs = np.zeros(nl)
         cf = np.zeros(nl)
-        ss = np.zeros((nl, 2))
-        sf = np.zeros((nl, 2))
+        ss = np.zeros(nl, dtype=np.complex128)
+        sf = np.zeros(nl, dtype=np.complex128)
         _check(lib().sdc_finalize(self._h, _np_ptr(C) if C is not None else None, _np_ptr(counts),
                                   _np_ptr(cs), _np_ptr(cf), _np_ptr(ss), _np_ptr(sf),
                                   _stream_ptr(stream)), "sdc_finalize")
-        return dict(C=C, counts=counts, Csum=cs, Cself=cf, Ssum=ss[:, 0] + 1j * ss[:, 1],
-                    Sself=sf[:, 0] + 1j * sf[:, 1])
+        return dict(C=C, counts=counts, Csum=cs, Cself=cf, Ssum=ss, Sself=sf)
 
     def raw(self, stream=None):
         """(H [n_lags][n_bins], n_org [n_lags], self [n_lags], msum [n_lags]) as
@@ -391,11 +390,11 @@ class Plan:
         m = np.ascontiguousarray(np.atleast_2d(m), dtype=np.int32)
         if m.shape[1] != 3:
             raise ValueError("m must have shape [n_q][3]")
-        sqt = np.zeros((m.shape[0], self.n_lags, 2))
-        sqw = np.zeros((m.shape[0], self.n_lags, 2))
+        sqt = np.zeros((m.shape[0], self.n_lags), dtype=np.complex128)
+        sqw = np.zeros((m.shape[0], self.n_lags), dtype=np.complex128)
         _check(lib().sdc_plan_structure_factor(self._h, _np_ptr(m), m.shape[0], _np_ptr(sqt), _np_ptr(sqw),
                                                _stream_ptr(stream)), "sdc_plan_structure_factor")
-        return sqt[..., 0] + 1j * sqt[..., 1], sqw[..., 0] + 1j * sqw[..., 1]
+        return sqt, sqw
 
     def structure_factor_static(self, m, stream=None):
         """structure_factor through sdc_plan_structure_factor_static (fixed
@@ -403,12 +402,12 @@ class Plan:
         m = np.ascontiguousarray(np.atleast_2d(m), dtype=np.int32)
         if m.shape[1] != 3:
             raise ValueError("m must have shape [n_q][3]")
-        sqt = np.zeros((m.shape[0], self.n_lags, 2))
-        sqw = np.zeros((m.shape[0], self.n_lags, 2))
+        sqt = np.zeros((m.shape[0], self.n_lags), dtype=np.complex128)
+        sqw = np.zeros((m.shape[0], self.n_lags), dtype=np.complex128)
         _check(lib().sdc_plan_structure_factor_static(self._h, _np_ptr(m), m.shape[0], _np_ptr(sqt),
                                                       _np_ptr(sqw), _stream_ptr(stream)),
                "sdc_plan_structure_factor_static")
-        return sqt[..., 0] + 1j * sqt[..., 1], sqw[..., 0] + 1j * sqw[..., 1]
+        return sqt, sqw
 
     def timings(self):
         """(pack_ms, self_ms, fused_ms) of the last accumulate (timing plans only)."""
@@ -656,10 +655,10 @@ class StructureFactor:
 
     def finalize(self, stream=None):
         """(Sqt [n_q][n_lags], Sqw [n_q][n_lags]) complex128."""
-        sqt = np.zeros((self.n_q, self.n_lags, 2))
-        sqw = np.zeros((self.n_q, self.n_lags, 2))
+        sqt = np.zeros((self.n_q, self.n_lags), dtype=np.complex128)
+        sqw = np.zeros((self.n_q, self.n_lags), dtype=np.complex128)
         _check(lib().sdc_sq_finalize(self._h, _np_ptr(sqt), _np_ptr(sqw), _stream_ptr(stream)), "sdc_sq_finalize")
-        return sqt[..., 0] + 1j * sqt[..., 1], sqw[..., 0] + 1j * sqw[..., 1]
+        return sqt, sqw
 
     def timings(self):
         """(pack_ms, contraction_ms, reduce_and_correlation_ms) of the last accumulate
