@@ -462,15 +462,34 @@ struct McArgs {
     // rotated onto each axis, st_dn for the negative directions.
     int stencil;
     int L0, L1, L2;
+    double inv_L1, inv_L2;     // 1 / L1, 1 / L2
     float st_j, st_dp, st_dn, st_dz;
 };
 int mc_energy_blocks(int64_t n);
 size_t mc_counter_bytes();
+// Samples whose sweeps one workgroup of 512 threads runs with the state in
+// LDS.  Per sweep of two classes, one workgroup against one launch per class:
+// 512 sites per class 5.0 / 9.1 us, 648: 6.5 / 9.2, 800: 8.7 / 9.1, 1024:
+// 8.5 / 9.1, 1408: 12.4 / 9.0; the line leaves room for couplings that cost
+// more per site (with DMI 800 sites take 10.1 / 9.5).
+constexpr int kMcSmallSites = 4096, kMcSmallClassSites = 768, kMcSmallClasses = 32;
+// A stretch of the annealing schedule: `count` sweeps from number `sweep` on,
+// the first at temperature T after `done` of its per_T sweeps.
+struct McSmall {
+    double T, T_end, cool;
+    int64_t per_T, done, sweep, count;
+    int n_classes;
+    int class_start[kMcSmallClasses + 1];
+};
+bool mc_is_small(int64_t n, const int64_t* class_start, int n_classes);
+int launch_mc_small(const McArgs& a, const McSmall& m, long long* history, void* stream);
+// Set the small-sample kernels' dynamic-LDS limit on the current device.
+int prepare_mc_kernels();
 // Loads init (fp32, or keeps the FP64 state when init is null), sets the cone.
 int launch_mc_setup(const McArgs& a, const float* init, double cone0, void* stream);
 // One sweep: every colour class in order (class c = slots class_start[c] ..
-// class_start[c + 1]), then the cone update (history[sweep] receives the
-// accepted moves when history is not null).
+// class_start[c + 1]), the last one ending with the cone update
+// (history[sweep] receives the accepted moves when history is not null).
 int launch_mc_sweep(const McArgs& a, const int64_t* class_start, int n_classes, double T, int64_t sweep,
                     long long* history, void* stream);
 // Energy per site, final cone and temperature into info[0..2]; state as fp32.

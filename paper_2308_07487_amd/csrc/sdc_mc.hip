@@ -8,10 +8,13 @@
 // order with neighbours given as slots, so a class's own states, bond
 // tables and its neighbours' states are read as contiguous runs.  Every random number is a Philox4x32-10 draw of the
 // (site, sweep) counter, so a sweep's result does not depend on the order in
-// which threads run; the cone and the acceptance counter live in device
-// memory and are updated by a one-thread kernel after each sweep, so a whole
-// schedule is queued without host round trips.
+// which threads run; the cone and the acceptance counters live in device
+// memory and are updated by the last workgroup of a sweep, so a whole
+// schedule is queued without host round trips.  Small samples run whole
+// stretches of the schedule in one workgroup with the state in LDS.
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
 
 #include "sdc_internal.h"
 
@@ -22,214 +25,405 @@ namespace {
 constexpr double kPi = 3.14159265358979323846;
 // The accepted moves of a sweep are counted in kMcCounters counters, one per
 // 128-byte line (workgroup b adds to counter b mod kMcCounters), so that the
-// workgroups' atomics do not all queue on one address.
+// workgroups' atomics do not all queue on one address.  The workgroups of a
+// sweep's last class also count themselves in the bits from kMcTicketBit on
+// (a sweep accepts at most 2^26 moves); the one that completes its counter
+// takes a ticket of the line after the counters.
 constexpr int kMcCounters = 64;
 constexpr int kMcCounterStride = 16;  // u64 words between counters
+constexpr int kMcTicketBit = 40;
+constexpr int kMcSmallThreads = 512;  // two waves per SIMD: the update's 180 registers fit
+constexpr int kMcTickets = kMcCounters * kMcCounterStride;  // word of the ticket
 
-// One colour class of one sweep.  Site i's move: trial spin in a cone of
-// half-angle `cone` about S_i (cos a uniform in [cos cone, 1], azimuth
-// uniform), Metropolis acceptance at temperature T.  Counter = (i low,
-// sweep low, i high, 2^31 | sweep high), key = seed: u_k = (w_k + 1/2) 2^-32.
+// a / l with r = 1 / l: the quotient's rounding error is corrected once, as a
+// division does, so that several quotients share one reciprocal.
+__device__ inline double quotient(double a, double l, double r) {
+    const double q = a * r;
+    return fma(fma(-q, l, a), r, q);
+}
+
+// Box coordinates of slot t of a class of the stencil's checkerboard: with
+// L2 even the t-th site of class c is 2t or 2t + 1.  floor((2t + 1/2) / L) by
+// one multiplication: the quotient is at least 1 / (2 L) away from the next
+// integer and its error below 2^-26 (n <= 2^26, L <= 2^24).
+struct McCell {
+    int x, y, z, row, site;
+};
+__device__ inline McCell mc_cell(const McArgs& a, int cls, uint32_t t) {
+    McCell c;
+    c.row = (int)(((double)(2 * t) + 0.5) * a.inv_L2);
+    c.x = (int)(((double)c.row + 0.5) * a.inv_L1);
+    c.y = c.row - c.x * a.L1;
+    const int dl = cls ^ ((c.x + c.y) & 1);
+    c.z = (int)(2 * t) - c.row * a.L2 + dl;
+    c.site = (int)(2 * t) + dl;
+    return c;
+}
+
+// Bonds of one site: neighbour slots (-1 = none), couplings, DMI vectors.
+template <int Z>
+struct McBonds {
+    int32_t j[Z];
+    float J[Z], d[Z][3];
+};
+
+// STENCIL: the neighbours' slots follow from the slot by lattice arithmetic
+// (McArgs::stencil), so the bond tables are not read; the bonds are the
+// table's, in the table's order, so both forms give the same bits.
+template <int STENCIL, int Z>
+__device__ inline void mc_bonds(const McArgs& a, int cls, const McCell& c, int64_t k, McBonds<Z>& b) {
+    if constexpr (STENCIL) {
+        const int other = cls ? 0 : (int)(a.n / 2);  // first slot of the neighbours' class
+        const int xp = c.x + 1 < a.L0 ? c.x + 1 : 0, xm = c.x > 0 ? c.x - 1 : a.L0 - 1;
+        const int yp = c.y + 1 < a.L1 ? c.y + 1 : 0, ym = c.y > 0 ? c.y - 1 : a.L1 - 1;
+        const int zp = c.z + 1 < a.L2 ? c.z + 1 : 0, zm = c.z > 0 ? c.z - 1 : a.L2 - 1;
+        const int rxy = c.row * a.L2;  // (x L1 + y) L2
+        const int sj[6] = {(xp * a.L1 + c.y) * a.L2 + c.z, (xm * a.L1 + c.y) * a.L2 + c.z,
+                           (c.x * a.L1 + yp) * a.L2 + c.z, (c.x * a.L1 + ym) * a.L2 + c.z, rxy + zp, rxy + zm};
+#pragma unroll
+        for (int e = 0; e < 6; ++e) {
+            b.j[e] = other + (sj[e] >> 1);
+            b.J[e] = a.st_j;
+#pragma unroll
+            for (int m = 0; m < 3; ++m) b.d[e][m] = m != e / 2 ? a.st_dz : (e & 1) ? a.st_dn : a.st_dp;
+        }
+    } else {
+#pragma unroll
+        for (int e = 0; e < Z; ++e) {
+            b.j[e] = a.nbr[k * Z + e];
+            b.J[e] = a.jval[k * Z + e];
+        }
+        if (a.dvec) {
+#pragma unroll
+            for (int e = 0; e < Z; ++e)
+#pragma unroll
+                for (int m = 0; m < 3; ++m) b.d[e][m] = a.dvec[3 * (k * Z + e) + m];
+        }
+    }
+}
+
+// Field of a site's neighbours, sum_j (J_ij S_j + D_ij x S_j), the bonds in
+// table order.  All neighbours are loaded before the first is used (read
+// bond by bond, the loads of sc 128^3 waited for one another six times: see
+// mc_colour_kernel).
+template <int Z, class State>
+__device__ inline void mc_field(const McArgs& a, const State& S, const McBonds<Z>& b, double (&w)[3]) {
+    double y[Z][3];
+#pragma unroll
+    for (int e = 0; e < Z; ++e) {
+        const int64_t j = 3 * (int64_t)(b.j[e] < 0 ? 0 : b.j[e]);
+#pragma unroll
+        for (int m = 0; m < 3; ++m) y[e][m] = S[j + m];
+    }
+    w[0] = w[1] = w[2] = 0.0;
+    if (a.dvec) {
+#pragma unroll
+        for (int e = 0; e < Z; ++e) {
+            if (b.j[e] < 0) continue;
+            const double J = b.J[e], d0 = b.d[e][0], d1 = b.d[e][1], d2 = b.d[e][2];
+            w[0] += J * y[e][0];
+            w[1] += J * y[e][1];
+            w[2] += J * y[e][2];
+            w[0] += d1 * y[e][2] - d2 * y[e][1];
+            w[1] += d2 * y[e][0] - d0 * y[e][2];
+            w[2] += d0 * y[e][1] - d1 * y[e][0];
+        }
+    } else {
+#pragma unroll
+        for (int e = 0; e < Z; ++e) {
+            if (b.j[e] < 0) continue;
+            const double J = b.J[e];
+            w[0] += J * y[e][0];
+            w[1] += J * y[e][1];
+            w[2] += J * y[e][2];
+        }
+    }
+}
+
+// The same for any number of bonds, one after another.
+template <class State>
+__device__ inline void mc_field_any(const McArgs& a, const State& S, int64_t k, double (&w)[3]) {
+    w[0] = w[1] = w[2] = 0.0;
+    for (int e = 0; e < a.z_max; ++e) {
+        const int32_t j = a.nbr[k * a.z_max + e];
+        if (j < 0) continue;
+        const double J = a.jval[k * a.z_max + e];
+        const double y0 = S[3 * (int64_t)j], y1 = S[3 * (int64_t)j + 1], y2 = S[3 * (int64_t)j + 2];
+        w[0] += J * y0;
+        w[1] += J * y1;
+        w[2] += J * y2;
+        if (a.dvec) {
+            const float* d = a.dvec + 3 * (k * a.z_max + e);
+            w[0] += (double)d[1] * y2 - (double)d[2] * y1;
+            w[1] += (double)d[2] * y0 - (double)d[0] * y2;
+            w[2] += (double)d[0] * y1 - (double)d[1] * y0;
+        }
+    }
+}
+
+template <int STENCIL, int Z, class State>
+__device__ inline void mc_field_of(const McArgs& a, const State& S, int cls, const McCell& c, int64_t k,
+                                   double (&w)[3]) {
+    if constexpr (Z > 0) {
+        McBonds<Z> b;
+        mc_bonds<STENCIL, Z>(a, cls, c, k, b);
+        mc_field<Z>(a, S, b, w);
+    } else {
+        mc_field_any(a, S, k, w);
+    }
+}
+
+// One Metropolis move of site i in the field w: trial spin in a cone about s
+// (cos a uniform in [cos cone, 1], azimuth uniform), acceptance at temperature
+// T.  Counter = (i low, sweep low, i high, 2^31 | sweep high), key = seed:
+// u_k = (w_k + 1/2) 2^-32.  Returns whether the trial spin replaced s.
+__device__ inline bool mc_move(const McArgs& a, int64_t i, int64_t sweep, double T, double cos_cone,
+                               const double (&w)[3], double (&s)[3]) {
+    uint32_t c[4] = {(uint32_t)i, (uint32_t)sweep, (uint32_t)((uint64_t)i >> 32),
+                     0x80000000u | (uint32_t)((uint64_t)sweep >> 32)};
+    philox4x32_10(c, (uint32_t)a.seed, (uint32_t)(a.seed >> 32));
+    const double u0 = ((double)c[0] + 0.5) * (1.0 / 4294967296.0);
+    const double u1 = ((double)c[1] + 0.5) * (1.0 / 4294967296.0);
+    const double u2 = ((double)c[2] + 0.5) * (1.0 / 4294967296.0);
+    const double cosa = 1.0 - u0 * (1.0 - cos_cone);
+    const double sina = sqrt(fmax(0.0, 1.0 - cosa * cosa));
+    double sb, cb;
+    sincospi(2.0 * u1, &sb, &cb);
+    // frame about s: e1 from z (x when s is near z), e2 = s x e1
+    const bool near_z = fabs(s[2]) >= 0.9;
+    const double ax = near_z ? 1.0 : 0.0, az = near_z ? 0.0 : 1.0;
+    const double as = ax * s[0] + az * s[2];
+    double e10 = ax - as * s[0], e11 = -as * s[1], e12 = az - as * s[2];
+    const double l1 = sqrt(e10 * e10 + e11 * e11 + e12 * e12), r1 = 1.0 / l1;
+    e10 = quotient(e10, l1, r1);
+    e11 = quotient(e11, l1, r1);
+    e12 = quotient(e12, l1, r1);
+    const double e20 = s[1] * e12 - s[2] * e11, e21 = s[2] * e10 - s[0] * e12, e22 = s[0] * e11 - s[1] * e10;
+    double t0 = cosa * s[0] + sina * (cb * e10 + sb * e20);
+    double t1 = cosa * s[1] + sina * (cb * e11 + sb * e21);
+    double t2 = cosa * s[2] + sina * (cb * e12 + sb * e22);
+    const double lt = sqrt(t0 * t0 + t1 * t1 + t2 * t2), rt = 1.0 / lt;
+    t0 = quotient(t0, lt, rt);
+    t1 = quotient(t1, lt, rt);
+    t2 = quotient(t2, lt, rt);
+    const double dE = ((t0 - s[0]) * w[0] + (t1 - s[1]) * w[1] + (t2 - s[2]) * w[2]) -
+                      a.A * (t2 * t2 - s[2] * s[2]) - a.Hz * (t2 - s[2]);
+    if (!(dE <= 0.0 || u2 < exp(-dE / T))) return false;
+    s[0] = t0;
+    s[1] = t1;
+    s[2] = t2;
+    return true;
+}
+
+// The cone after a sweep with the given number of accepted moves.
+__device__ inline double next_cone(const McArgs& a, double c, unsigned long long acc) {
+    const double rate = (double)acc / (double)a.n;
+    if (rate < a.acc_target) return fmax(1e-3, 0.9 * c);
+    if (rate > 2.0 * a.acc_target) return fmin(kPi, 1.1 * c);
+    return c;
+}
+
+// Last workgroup of a sweep (one wave): gather the counters, clear them,
+// record the accepted moves, adapt the cone.
+__device__ inline void mc_end_sweep(const McArgs& a, long long* history, int64_t sweep) {
+    const int t = threadIdx.x;  // < 64 = kMcCounters
+    unsigned long long acc = __hip_atomic_load(a.accepted + t * kMcCounterStride, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT) &
+                             ((1ull << kMcTicketBit) - 1);
+    a.accepted[t * kMcCounterStride] = 0ull;
+    if (t == 0) a.accepted[kMcTickets] = 0ull;
+#pragma unroll
+    for (int w = 32; w > 0; w >>= 1) acc += __shfl_down(acc, w);
+    if (t != 0) return;
+    if (history) history[sweep] = (long long)acc;
+    const double c = next_cone(a, a.cone[0], acc);
+    a.cone[0] = c;
+    a.cone[1] = cos(c);
+}
+
+// One colour class of one sweep, one thread per site.  Bound: FP64 vector
+// arithmetic (Philox, a sine and cosine, three square roots, three
+// divisions, one exponential per site: about 650 vector instructions, 18 us of
+// issue for the 1 048 576 sites of a class at sc 128^3), beside it the gathers.
+// That class takes 20.1 us; 23.0 us when the neighbours were read bond by bond,
+// with 64-bit divisions in the stencil's index arithmetic and a division per
+// component.
 // Workgroups go to the 8 XCDs in turn; workgroup b takes block
 // x q + min(x, r) + b / 8 of the class (x = b mod 8, nb = 8 q + r blocks), so
 // each XCD sweeps one contiguous stretch of slots in order and its L2 keeps
 // the neighbour planes that the following slots read again.
-// STENCIL: the site and its neighbours' slots follow from the slot by
-// lattice arithmetic (McArgs::stencil), so the slot -> site map and the bond
-// tables are not read; the sums run over the bonds in table order with the
-// table's values, so both forms give the same bits.
-template <int STENCIL>
-__global__ __launch_bounds__(256) void mc_colour_kernel(McArgs a, int64_t k0, int64_t count, double T,
-                                                        int64_t sweep) {
-    const int64_t nb = gridDim.x, q = nb / 8, r = nb % 8, x = blockIdx.x % 8;
-    const int64_t lb = x * q + (x < r ? x : r) + blockIdx.x / 8;
-    const int64_t t = lb * blockDim.x + threadIdx.x;
+// `last`: this is the sweep's last class, whose last workgroup adapts the cone
+// (a launch of its own for that took 4.8 us per sweep).
+template <int STENCIL, int Z>
+__global__ __launch_bounds__(256) void mc_colour_kernel(McArgs a, int64_t k0, int64_t count, double T, int64_t sweep,
+                                                        int last, long long* history) {
+    const uint32_t nb = gridDim.x, q = nb / 8, r = nb % 8, x = blockIdx.x % 8;
+    const uint32_t lb = x * q + (x < r ? x : r) + blockIdx.x / 8;
+    const uint32_t t = lb * 256 + threadIdx.x;
     bool accepted = false;
-    if (t < count) {
-        const int64_t k = k0 + t;           // slot
-        int64_t i;                          // site index: the Philox counter
-        // field of the neighbours: sum_j (J_ij S_j + D_ij x S_j)
-        double w0 = 0.0, w1 = 0.0, w2 = 0.0;
-        auto bond = [&](int64_t j, double J, double d0, double d1, double d2, bool dmi) {
-            const double y0 = a.S[3 * j], y1 = a.S[3 * j + 1], y2 = a.S[3 * j + 2];
-            w0 += J * y0;
-            w1 += J * y1;
-            w2 += J * y2;
-            if (dmi) {
-                w0 += d1 * y2 - d2 * y1;
-                w1 += d2 * y0 - d0 * y2;
-                w2 += d0 * y1 - d1 * y0;
-            }
-        };
-        if constexpr (STENCIL) {
-            // class c = (k0 > 0) holds the sites of parity c of x + y + z in
-            // site order; with L2 even its t-th site is 2t or 2t + 1
-            const int64_t half = a.n / 2, s0 = 2 * t;
-            const int64_t row = s0 / a.L2, z0 = s0 - row * a.L2;
-            const int64_t y = row % a.L1, xx = row / a.L1;
-            const int64_t dl = (k0 > 0 ? 1 : 0) ^ ((xx + y) & 1);
-            const int64_t z = z0 + dl;
-            i = s0 + dl;
-            const int64_t other = k0 > 0 ? 0 : half;  // first slot of the neighbours' class
-            const int64_t xp = xx + 1 < a.L0 ? xx + 1 : 0, xm = xx > 0 ? xx - 1 : a.L0 - 1;
-            const int64_t yp = y + 1 < a.L1 ? y + 1 : 0, ym = y > 0 ? y - 1 : a.L1 - 1;
-            const int64_t zp = z + 1 < a.L2 ? z + 1 : 0, zm = z > 0 ? z - 1 : a.L2 - 1;
-            const int64_t rxy = row * a.L2;  // (x L1 + y) L2
-            const int64_t sj[6] = {((xp * a.L1 + y) * a.L2 + z), ((xm * a.L1 + y) * a.L2 + z),
-                                   ((xx * a.L1 + yp) * a.L2 + z), ((xx * a.L1 + ym) * a.L2 + z),
-                                   rxy + zp, rxy + zm};
-            const bool dmi = a.dvec != nullptr;
-            const double J = a.st_j, dp = a.st_dp, dn = a.st_dn, dz = a.st_dz;
-#pragma unroll
-            for (int e = 0; e < 6; ++e) {
-                const double dd = (e & 1) ? dn : dp;
-                bond(other + (sj[e] >> 1), J, e / 2 == 0 ? dd : dz, e / 2 == 1 ? dd : dz, e / 2 == 2 ? dd : dz, dmi);
-            }
-        } else {
-            i = a.site_of[k];
-            for (int e = 0; e < a.z_max; ++e) {
-                const int32_t j = a.nbr[k * a.z_max + e];
-                if (j < 0) continue;
-                const float* d = a.dvec ? a.dvec + 3 * (k * a.z_max + e) : nullptr;
-                bond(j, a.jval[k * a.z_max + e], d ? d[0] : 0.0, d ? d[1] : 0.0, d ? d[2] : 0.0, d != nullptr);
-            }
-        }
+    if (t < (uint64_t)count) {
+        const int64_t k = k0 + t;  // slot
+        const int cls = k0 > 0;    // of the stencil
+        McCell cell{};
+        if constexpr (STENCIL) cell = mc_cell(a, cls, t);
         double* si = a.S + 3 * k;
-        const double s0 = si[0], s1 = si[1], s2 = si[2];
-        uint32_t c[4] = {(uint32_t)i, (uint32_t)sweep, (uint32_t)((uint64_t)i >> 32),
-                         0x80000000u | (uint32_t)((uint64_t)sweep >> 32)};
-        philox4x32_10(c, (uint32_t)a.seed, (uint32_t)(a.seed >> 32));
-        const double u0 = ((double)c[0] + 0.5) * (1.0 / 4294967296.0);
-        const double u1 = ((double)c[1] + 0.5) * (1.0 / 4294967296.0);
-        const double u2 = ((double)c[2] + 0.5) * (1.0 / 4294967296.0);
-        const double cosa = 1.0 - u0 * (1.0 - a.cone[1]);
-        const double sina = sqrt(fmax(0.0, 1.0 - cosa * cosa));
-        double sb, cb;
-        sincospi(2.0 * u1, &sb, &cb);
-        // frame about S_i: e1 from z (x when S_i is near z), e2 = S_i x e1
-        const bool near_z = fabs(s2) >= 0.9;
-        const double ax = near_z ? 1.0 : 0.0, az = near_z ? 0.0 : 1.0;
-        const double as = ax * s0 + az * s2;
-        double e10 = ax - as * s0, e11 = -as * s1, e12 = az - as * s2;
-        const double l1 = sqrt(e10 * e10 + e11 * e11 + e12 * e12);
-        e10 /= l1;
-        e11 /= l1;
-        e12 /= l1;
-        const double e20 = s1 * e12 - s2 * e11, e21 = s2 * e10 - s0 * e12, e22 = s0 * e11 - s1 * e10;
-        double t0 = cosa * s0 + sina * (cb * e10 + sb * e20);
-        double t1 = cosa * s1 + sina * (cb * e11 + sb * e21);
-        double t2 = cosa * s2 + sina * (cb * e12 + sb * e22);
-        const double lt = sqrt(t0 * t0 + t1 * t1 + t2 * t2);
-        t0 /= lt;
-        t1 /= lt;
-        t2 /= lt;
-        const double dE = ((t0 - s0) * w0 + (t1 - s1) * w1 + (t2 - s2) * w2) - a.A * (t2 * t2 - s2 * s2) -
-                          a.Hz * (t2 - s2);
-        if (dE <= 0.0 || u2 < exp(-dE / T)) {
-            si[0] = t0;
-            si[1] = t1;
-            si[2] = t2;
-            accepted = true;
+        double s[3] = {si[0], si[1], si[2]}, w[3];
+        mc_field_of<STENCIL, Z>(a, a.S, cls, cell, k, w);
+        accepted = mc_move(a, STENCIL ? cell.site : a.site_of[k], sweep, T, a.cone[1], w, s);
+        if (accepted) {
+            si[0] = s[0];
+            si[1] = s[1];
+            si[2] = s[2];
         }
     }
     __shared__ unsigned int wave_acc[4];
+    __shared__ int ends;
     const unsigned long long ball = __ballot(accepted);
     if ((threadIdx.x & 63) == 0) wave_acc[threadIdx.x >> 6] = (unsigned int)__popcll(ball);
     __syncthreads();
     if (threadIdx.x == 0) {
         const unsigned long long sum = (unsigned long long)wave_acc[0] + wave_acc[1] + wave_acc[2] + wave_acc[3];
-        if (sum) atomicAdd(a.accepted + (blockIdx.x % kMcCounters) * kMcCounterStride, sum);
-    }
-}
-
-// After a sweep (one wave): gather the counters, clear them, record the
-// accepted moves, adapt the cone.
-__global__ __launch_bounds__(64) void mc_cone_kernel(McArgs a, long long* history, int64_t sweep) {
-    __shared__ unsigned long long part[kMcCounters];
-    const int t = threadIdx.x;
-    part[t] = a.accepted[t * kMcCounterStride];
-    a.accepted[t * kMcCounterStride] = 0ull;
-    __syncthreads();
-    if (t != 0) return;
-    unsigned long long acc = 0ull;
-    for (int c = 0; c < kMcCounters; ++c) acc += part[c];
-    if (history) history[sweep] = (long long)acc;
-    const double rate = (double)acc / (double)a.n;
-    double c = a.cone[0];
-    if (rate < a.acc_target)
-        c = fmax(1e-3, 0.9 * c);
-    else if (rate > 2.0 * a.acc_target)
-        c = fmin(kPi, 1.1 * c);
-    a.cone[0] = c;
-    a.cone[1] = cos(c);
-}
-
-__global__ __launch_bounds__(64) void mc_setup_kernel(McArgs a, double cone0) {
-    a.accepted[threadIdx.x * kMcCounterStride] = 0ull;
-    if (threadIdx.x != 0) return;
-    a.cone[0] = cone0;
-    a.cone[1] = cos(cone0);
-}
-
-__global__ __launch_bounds__(256) void mc_load_kernel(McArgs a, const float* __restrict__ init) {
-    for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < 3 * a.n; x += (int64_t)gridDim.x * blockDim.x)
-        a.S[x] = (double)init[3 * (int64_t)a.site_of[x / 3] + x % 3];
-}
-
-// Energy of Eq. (1) per block: half of each site's bond energies (each bond
-// is seen from both ends) plus its single-site terms; partial sums per block.
-__global__ __launch_bounds__(256) void mc_energy_kernel(McArgs a, double* __restrict__ partial) {
-    __shared__ double red[256];
-    double e = 0.0;
-    for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < a.n; k += (int64_t)gridDim.x * blockDim.x) {
-        const double* si = a.S + 3 * k;
-        double eb = 0.0;
-        for (int e = 0; e < a.z_max; ++e) {
-            const int32_t j = a.nbr[k * a.z_max + e];
-            if (j < 0) continue;
-            const double* sj = a.S + 3 * (int64_t)j;
-            eb += (double)a.jval[k * a.z_max + e] * (si[0] * sj[0] + si[1] * sj[1] + si[2] * sj[2]);
-            if (a.dvec) {
-                const float* d = a.dvec + 3 * (k * a.z_max + e);
-                const double cx = si[1] * sj[2] - si[2] * sj[1];
-                const double cy = si[2] * sj[0] - si[0] * sj[2];
-                const double cz = si[0] * sj[1] - si[1] * sj[0];
-                eb -= (double)d[0] * cx + (double)d[1] * cy + (double)d[2] * cz;
+        const uint32_t line = blockIdx.x % kMcCounters;
+        int e = 0;
+        if (!last) {
+            if (sum) atomicAdd(a.accepted + line * kMcCounterStride, sum);
+        } else {
+            const unsigned long long old = atomicAdd(a.accepted + line * kMcCounterStride, sum + (1ull << kMcTicketBit));
+            if ((old >> kMcTicketBit) + 1 == (nb - line + kMcCounters - 1) / kMcCounters) {
+                const uint32_t lines = nb < kMcCounters ? nb : kMcCounters;
+                e = atomicAdd(a.accepted + kMcTickets, 1ull) + 1 == lines;
             }
         }
-        e += 0.5 * eb - a.A * si[2] * si[2] - a.Hz * si[2];
+        ends = e;
     }
-    red[threadIdx.x] = e;
+    if (!last) return;
+    __syncthreads();
+    if (ends && threadIdx.x < kMcCounters) mc_end_sweep(a, history, sweep);
+}
+
+// `count` sweeps of a small sample by one workgroup, the state in LDS.  Bound:
+// the latency of one update (about 700 dependent instructions).  A class of a
+// 32 x 32 lattice is eight waves, so a launch per class and sweep end is
+// mostly launch and memory latency: 14.4 us per sweep, 9.1 without the launch
+// of the sweep's end, 4.9 in one workgroup (a whole annealing of 310 sweeps
+// 4.5 -> 1.5 ms).
+// T and `done` (sweeps made at T) follow the schedule of the host:
+// T_k = T_start cool^k while T_k > T_end, sweeps_per_T each, then T_end.
+template <int STENCIL, int Z>
+__global__ __launch_bounds__(kMcSmallThreads) void mc_small_kernel(McArgs a, McSmall m, long long* history) {
+    extern __shared__ double S[];
+    __shared__ unsigned int acc[2];
+    const int tid = threadIdx.x;
+    for (int x = tid; x < 3 * (int)a.n; x += kMcSmallThreads) S[x] = a.S[x];
+    double T = m.T, cone = a.cone[0], cos_cone = a.cone[1];
+    int64_t done = m.done;
+    if (tid < 2) acc[tid] = 0;
+    __syncthreads();
+    for (int64_t v = 0; v < m.count; ++v) {
+        const int64_t sweep = m.sweep + v;
+        const double Ts = T > m.T_end ? T : m.T_end;
+        for (int c = 0; c < m.n_classes; ++c) {
+            const int k1 = m.class_start[c + 1];
+            for (int k = m.class_start[c] + tid; k < k1; k += kMcSmallThreads) {
+                double s[3] = {S[3 * k], S[3 * k + 1], S[3 * k + 2]}, w[3];
+                McCell cell{};
+                if constexpr (STENCIL) cell = mc_cell(a, c, (uint32_t)(k - m.class_start[c]));
+                mc_field_of<STENCIL, Z>(a, S, c, cell, k, w);
+                if (mc_move(a, STENCIL ? cell.site : a.site_of[k], sweep, Ts, cos_cone, w, s)) {
+                    S[3 * k] = s[0];
+                    S[3 * k + 1] = s[1];
+                    S[3 * k + 2] = s[2];
+                    atomicAdd(&acc[v & 1], 1u);
+                }
+            }
+            __syncthreads();
+        }
+        // every thread follows the cone; the counter of the next sweep was
+        // last read before this sweep's barriers
+        const unsigned int n_acc = acc[v & 1];
+        if (tid == 0) {
+            if (history) history[sweep] = (long long)n_acc;
+            acc[(v + 1) & 1] = 0;
+        }
+        cone = next_cone(a, cone, n_acc);
+        cos_cone = cos(cone);
+        if (T > m.T_end && ++done == m.per_T) {
+            T *= m.cool;
+            done = 0;
+        }
+        __syncthreads();
+    }
+    for (int x = tid; x < 3 * (int)a.n; x += kMcSmallThreads) a.S[x] = S[x];
+    if (tid == 0) {
+        a.cone[0] = cone;
+        a.cone[1] = cos_cone;
+    }
+}
+
+// The state from init (fp32, unless null), counters cleared, cone set.
+__global__ __launch_bounds__(256) void mc_setup_kernel(McArgs a, const float* __restrict__ init, double cone0) {
+    if (blockIdx.x == 0) {
+        if (threadIdx.x < kMcCounters) a.accepted[threadIdx.x * kMcCounterStride] = 0ull;
+        if (threadIdx.x == 0) {
+            a.accepted[kMcTickets] = 0ull;
+            a.cone[0] = cone0;
+            a.cone[1] = cos(cone0);
+        }
+    }
+    if (!init) return;
+    for (int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x; k < a.n; k += (int64_t)gridDim.x * 256) {
+        const float* x = init + 3 * (int64_t)a.site_of[k];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) a.S[3 * k + c] = (double)x[c];
+    }
+}
+
+__device__ inline double mc_block_sum(double v, double* red) {
+    red[threadIdx.x] = v;
     __syncthreads();
     for (int s = 128; s > 0; s >>= 1) {
         if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
         __syncthreads();
     }
-    if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
+    return red[0];
 }
 
-// Final state as fp32 and the info block: energy per site (partials summed
-// in block order), cone, last temperature.
-__global__ __launch_bounds__(256) void mc_out_kernel(McArgs a, float* __restrict__ out) {
-    for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < 3 * a.n; x += (int64_t)gridDim.x * blockDim.x)
-        out[3 * (int64_t)a.site_of[x / 3] + x % 3] = (float)a.S[x];
+// Final state as fp32 and the energy of Eq. (1) per block: half of each site's
+// bond energies, S . field (each bond is seen from both ends), plus its
+// single-site terms.
+template <int STENCIL, int Z>
+__global__ __launch_bounds__(256) void mc_finish_kernel(McArgs a, double* __restrict__ partial,
+                                                        float* __restrict__ out) {
+    __shared__ double red[256];
+    double e = 0.0;
+    for (int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x; k < a.n; k += (int64_t)gridDim.x * 256) {
+        const int cls = STENCIL && k >= a.n / 2;
+        McCell cell{};
+        if constexpr (STENCIL) cell = mc_cell(a, cls, (uint32_t)(k - (cls ? a.n / 2 : 0)));
+        const double* si = a.S + 3 * k;
+        const double s[3] = {si[0], si[1], si[2]};
+        double w[3];
+        mc_field_of<STENCIL, Z>(a, a.S, cls, cell, k, w);
+        e += 0.5 * (s[0] * w[0] + s[1] * w[1] + s[2] * w[2]) - a.A * s[2] * s[2] - a.Hz * s[2];
+        float* o = out + 3 * (int64_t)(STENCIL ? cell.site : a.site_of[k]);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) o[c] = (float)s[c];
+    }
+    e = mc_block_sum(e, red);
+    if (threadIdx.x == 0) partial[blockIdx.x] = e;
 }
 
-// One workgroup: thread t sums partials t, t + 256, ... in order, then a
-// fixed tree (the same result on every run).
+// The info block: energy per site (one workgroup: thread t sums partials t,
+// t + 256, ... in order, then a fixed tree, the same result on every run),
+// cone, last temperature.
 __global__ __launch_bounds__(256) void mc_info_kernel(McArgs a, const double* __restrict__ partial, int n_partial,
                                                       double T_last, double* __restrict__ info) {
     __shared__ double red[256];
     double e = 0.0;
     for (int b = threadIdx.x; b < n_partial; b += 256) e += partial[b];
-    red[threadIdx.x] = e;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-        __syncthreads();
-    }
+    e = mc_block_sum(e, red);
     if (threadIdx.x != 0) return;
-    info[0] = red[0] / (double)a.n;
+    info[0] = e / (double)a.n;
     info[1] = a.cone[0];
     info[2] = T_last;
 }
@@ -239,41 +433,75 @@ unsigned grid_of(int64_t n) {
     return (unsigned)(b > 4096 ? 4096 : (b < 1 ? 1 : b));
 }
 
+// Calls f(STENCIL, Z) with the constants of the sample.
+template <class F>
+void mc_dispatch(const McArgs& a, F f) {
+    if (a.stencil) f(std::integral_constant<int, 1>{}, std::integral_constant<int, 6>{});
+    else if (a.z_max == 6) f(std::integral_constant<int, 0>{}, std::integral_constant<int, 6>{});
+    else if (a.z_max == 8) f(std::integral_constant<int, 0>{}, std::integral_constant<int, 8>{});
+    else f(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{});
+}
+
 }  // namespace
 
 int mc_energy_blocks(int64_t n) { return (int)grid_of(n); }
 
-size_t mc_counter_bytes() { return (size_t)kMcCounters * kMcCounterStride * sizeof(unsigned long long); }
+size_t mc_counter_bytes() { return (size_t)(kMcCounters + 1) * kMcCounterStride * sizeof(unsigned long long); }
 
 int launch_mc_setup(const McArgs& a, const float* init, double cone0, void* stream) {
-    hipStream_t s = (hipStream_t)stream;
-    if (init) hipLaunchKernelGGL(mc_load_kernel, dim3(grid_of(3 * a.n)), dim3(256), 0, s, a, init);
-    hipLaunchKernelGGL(mc_setup_kernel, dim3(1), dim3(64), 0, s, a, cone0);
+    hipLaunchKernelGGL(mc_setup_kernel, dim3(init ? grid_of(a.n) : 1), dim3(256), 0, (hipStream_t)stream, a, init,
+                       cone0);
     return (int)hipGetLastError();
 }
 
 int launch_mc_sweep(const McArgs& a, const int64_t* class_start, int n_classes, double T, int64_t sweep,
                     long long* history, void* stream) {
     hipStream_t s = (hipStream_t)stream;
-    for (int c = 0; c < n_classes; ++c) {
-        const int64_t count = class_start[c + 1] - class_start[c];
-        if (count == 0) continue;
-        const unsigned grid = (unsigned)((count + 255) / 256);
-        if (a.stencil)
-            hipLaunchKernelGGL(mc_colour_kernel<1>, dim3(grid), dim3(256), 0, s, a, class_start[c], count, T, sweep);
-        else
-            hipLaunchKernelGGL(mc_colour_kernel<0>, dim3(grid), dim3(256), 0, s, a, class_start[c], count, T, sweep);
+    mc_dispatch(a, [&](auto stencil, auto z) {
+        for (int c = 0; c < n_classes; ++c) {
+            const int64_t count = class_start[c + 1] - class_start[c];  // at least one site
+            const unsigned grid = (unsigned)((count + 255) / 256);
+            hipLaunchKernelGGL((mc_colour_kernel<decltype(stencil)::value, decltype(z)::value>), dim3(grid), dim3(256),
+                               0, s, a, class_start[c], count, T, sweep, c == n_classes - 1 ? 1 : 0, history);
+        }
+    });
+    return (int)hipGetLastError();
+}
+
+bool mc_is_small(int64_t n, const int64_t* class_start, int n_classes) {
+    if (n > kMcSmallSites || n_classes > kMcSmallClasses) return false;
+    for (int c = 0; c < n_classes; ++c)
+        if (class_start[c + 1] - class_start[c] > kMcSmallClassSites) return false;
+    return true;
+}
+
+int prepare_mc_kernels() {
+    const void* f[] = {(const void*)mc_small_kernel<1, 6>, (const void*)mc_small_kernel<0, 0>,
+                       (const void*)mc_small_kernel<0, 6>, (const void*)mc_small_kernel<0, 8>};
+    for (const void* k : f) {
+        const hipError_t e =
+            hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kMcSmallSites * 3 * (int)sizeof(double));
+        if (e != hipSuccess) return (int)e;
     }
-    hipLaunchKernelGGL(mc_cone_kernel, dim3(1), dim3(64), 0, s, a, history, sweep);
+    return 0;
+}
+
+int launch_mc_small(const McArgs& a, const McSmall& m, long long* history, void* stream) {
+    const size_t lds = (size_t)a.n * 3 * sizeof(double);
+    mc_dispatch(a, [&](auto stencil, auto z) {
+        hipLaunchKernelGGL((mc_small_kernel<decltype(stencil)::value, decltype(z)::value>), dim3(1),
+                           dim3(kMcSmallThreads), lds, (hipStream_t)stream, a, m, history);
+    });
     return (int)hipGetLastError();
 }
 
 int launch_mc_finish(const McArgs& a, double* partial, double T_last, float* out, double* info, void* stream) {
-    hipStream_t s = (hipStream_t)stream;
-    const unsigned g = grid_of(a.n);
-    hipLaunchKernelGGL(mc_energy_kernel, dim3(g), dim3(256), 0, s, a, partial);
-    hipLaunchKernelGGL(mc_out_kernel, dim3(grid_of(3 * a.n)), dim3(256), 0, s, a, out);
-    hipLaunchKernelGGL(mc_info_kernel, dim3(1), dim3(256), 0, s, a, (const double*)partial, (int)g, T_last, info);
+    mc_dispatch(a, [&](auto stencil, auto z) {
+        hipLaunchKernelGGL((mc_finish_kernel<decltype(stencil)::value, decltype(z)::value>), dim3(grid_of(a.n)),
+                           dim3(256), 0, (hipStream_t)stream, a, partial, out);
+    });
+    hipLaunchKernelGGL(mc_info_kernel, dim3(1), dim3(256), 0, (hipStream_t)stream, a, (const double*)partial,
+                       (int)grid_of(a.n), T_last, info);
     return (int)hipGetLastError();
 }
 

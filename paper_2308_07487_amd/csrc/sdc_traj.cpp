@@ -347,6 +347,9 @@ struct sdc_mc {
 
 namespace {
 
+// Sweeps of one launch of the small-sample kernel (a few milliseconds).
+constexpr int64_t kSmallStretch = 1024;
+
 uint32_t float_bits(float f) {
     uint32_t u;
     std::memcpy(&u, &f, sizeof u);
@@ -391,6 +394,8 @@ void mc_stencil(const sdc_mc_spec* spec, int64_t n, int n_col, const std::vector
     ma->L0 = (int)L0;
     ma->L1 = (int)L1;
     ma->L2 = (int)L2;
+    ma->inv_L1 = 1.0 / (double)L1;
+    ma->inv_L2 = 1.0 / (double)L2;
     ma->st_j = jf;
     ma->st_dp = dp;
     ma->st_dn = dn;
@@ -434,6 +439,10 @@ extern "C" sdc_status sdc_mc_create(const float* positions_host, int64_t n_sites
         return sdc::set_error(SDC_ERR_NO_DEVICE, "no HIP device");
     if (device < 0 || device >= dev_count) return sdc::set_error(SDC_ERR_INVALID_ARG, "device out of range");
     if (hipSetDevice(device) != hipSuccess) return sdc::set_error(SDC_ERR_HIP, "hipSetDevice");
+    {
+        const int e = sdc::prepare_mc_kernels();
+        if (e != 0) return sdc::set_error(SDC_ERR_HIP, hipGetErrorString((hipError_t)e));
+    }
     sdc_mc* m = nullptr;
     try {
         m = new sdc_mc();
@@ -558,12 +567,41 @@ extern "C" sdc_status sdc_mc_run(sdc_mc* m, const sdc_mc_spec* schedule, const f
     int64_t sweep = 0;
     double T_last = schedule->T_start;
     long long* hist = accepted_host ? m->d_hist : nullptr;
-    mc_schedule(schedule, [&](double T) {
-        if (le == 0)
-            le = sdc::launch_mc_sweep(ma, m->start.data(), m->n_col, T, sweep, hist, stream);
-        ++sweep;
-        T_last = T;
-    });
+    if (sdc::mc_is_small(m->n, m->start.data(), m->n_col)) {
+        // stretches of at most kSmallStretch sweeps per launch
+        sdc::McSmall sm{};
+        sm.T = schedule->T_start;
+        sm.T_end = schedule->T_end;
+        sm.cool = schedule->cool;
+        sm.per_T = schedule->sweeps_per_T;
+        sm.n_classes = m->n_col;
+        for (int c = 0; c <= m->n_col; ++c) sm.class_start[c] = (int)m->start[(size_t)c];
+        sdc::McSmall next = sm;
+        mc_schedule(schedule, [&](double T) {
+            T_last = T;
+            ++next.count;
+            if (T > next.T_end && ++next.done == next.per_T) {
+                next.T *= next.cool;
+                next.done = 0;
+            }
+            if (next.count == kSmallStretch) {
+                sm.count = next.count;
+                if (le == 0) le = sdc::launch_mc_small(ma, sm, hist, stream);
+                sm.T = next.T;
+                sm.done = next.done;
+                sm.sweep += sm.count;
+                next.count = 0;
+            }
+        });
+        sm.count = next.count;
+        if (le == 0 && sm.count > 0) le = sdc::launch_mc_small(ma, sm, hist, stream);
+    } else {
+        mc_schedule(schedule, [&](double T) {
+            if (le == 0) le = sdc::launch_mc_sweep(ma, m->start.data(), m->n_col, T, sweep, hist, stream);
+            ++sweep;
+            T_last = T;
+        });
+    }
     if (le == 0) le = (int)hipEventRecord(m->ev[1], hs);
     if (le == 0) le = sdc::launch_mc_finish(ma, m->d_partial, T_last, state_dev, m->d_info, stream);
     if (le != 0) return sdc::set_error(SDC_ERR_HIP, hipGetErrorString((hipError_t)le));
