@@ -434,7 +434,19 @@ struct TrajArgs {
     const float* init_dev;
     float* frames;             // [n_frames][n][3]
     int64_t n_frames;
-    float* work;               // [5][n][3] fp32 scratch: S, T, acc, k
+    float* work;               // [3][n][3] fp32 scratch of the bond tables' stages: two stage states, acc
+    // Periodic sc box L0 x L1 x L2 with one uniform coupling, sites in the order
+    // (x L1 + y) L2 + z: a whole step per launch, no tables (nbr, jval, dvec and
+    // work null).  DMI vectors (st_dp, st_dz, st_dz) rotated onto each axis,
+    // st_dn for the negative directions.
+    int stencil, st_dmi;
+    int L[3];
+    float st_j, st_dp, st_dn, st_dz;
+};
+// Bricks of the one-launch step: b cells per axis (nb of them), tile t with halo.
+struct TrajBrick {
+    int L[3], b[3], t[3], nb[3], halo[3];
+    float J, dp, dn, dz;
 };
 int launch_traj(const TrajArgs& a, void* stream);
 // Seeded independent uniform unit vectors, [n_frames][n][3] fp32.

@@ -10,7 +10,6 @@
 //  count   : exact integer pair counts per bin with the same tile walk.
 //  self    : the i = j term per lag in FP64.
 //  final   : normalisation, site sum and the windowed time DFT (Sec. 2.2).
-//  traj    : Landau-Lifshitz RK4 (Eq. (2), Sec. 3.1) with Philox4x32-10 starts.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -1656,10 +1655,8 @@ int launch_zero(void* ptr, int64_t bytes, void* stream) {
 }
 
 // ---------------------------------------------------------------------------
-// trajectory: Philox starts and LL RK4
+// seeded spins (Philox)
 // ---------------------------------------------------------------------------
-
-__device__ inline float u24(uint32_t w) { return (float)(w >> 8) * (1.0f / 16777216.0f); }
 
 // Independent uniform unit vectors for every (frame, site): Philox4x32-10,
 // key = seed, counter = (site low, frame, site high, 7); z = 2u0 - 1,
@@ -1688,125 +1685,6 @@ int launch_unit_spins(float* out, int64_t n, int64_t n_frames, uint64_t seed, vo
     if (blocks > 16384) blocks = 16384;
     hipLaunchKernelGGL(unit_spins_kernel, dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream, out, n,
                        n_frames, seed);
-    return (int)hipGetLastError();
-}
-
-__global__ void traj_init_kernel(TrajArgs a, float* S) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= a.n) return;
-    double x, y, z;
-    if (a.init == SDC_INIT_GIVEN) {
-        x = a.init_dev[3 * i];
-        y = a.init_dev[3 * i + 1];
-        z = a.init_dev[3 * i + 2];
-    } else {
-        uint32_t c[4] = {(uint32_t)i, 0u, (uint32_t)((uint64_t)i >> 32), 0u};
-        philox4x32_10(c, (uint32_t)a.seed, (uint32_t)(a.seed >> 32));
-        const double u0 = (double)(c[0] >> 8) * (1.0 / 16777216.0);
-        const double u1 = (double)(c[1] >> 8) * (1.0 / 16777216.0);
-        if (a.init == SDC_INIT_UNIFORM) {
-            z = 2.0 * u0 - 1.0;
-            const double r = sqrt(fmax(0.0, 1.0 - z * z));
-            double sn, cs;
-            sincospi(2.0 * u1, &sn, &cs);
-            x = r * cs;
-            y = r * sn;
-        } else {
-            const double rr = sqrt(-2.0 * log(1.0 - u0));
-            double sn, cs;
-            sincospi(2.0 * u1, &sn, &cs);
-            const double v0 = a.sigma * rr * cs, v1 = a.sigma * rr * sn;
-            const double ang = sqrt(v0 * v0 + v1 * v1);
-            const double f = ang > 0.0 ? sin(ang) / ang : 1.0;
-            x = f * v0;
-            y = f * v1;
-            z = cos(ang);
-        }
-    }
-    S[3 * i] = (float)x;
-    S[3 * i + 1] = (float)y;
-    S[3 * i + 2] = (float)z;
-    a.frames[3 * i] = (float)x;
-    a.frames[3 * i + 1] = (float)y;
-    a.frames[3 * i + 2] = (float)z;
-}
-
-// One RK4 stage: k = h_i x X_i with the effective field of Eq. (1),
-// h_i = sum_j (J_ij X_j + D_ij x X_j) - 2 A X_i^z z - H_z z.
-//  stage 0: acc = k;      Tout = S + dt/2 k
-//  stage 1: acc += 2k;    Tout = S + dt/2 k
-//  stage 2: acc += 2k;    Tout = S + dt k
-//  stage 3: S += dt/6 (acc + k), frame written
-__global__ __launch_bounds__(256) void traj_stage_kernel(TrajArgs a, int stage, float* S,
-                                                         const float* X, float* Tout, float* acc,
-                                                         float* frame) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= a.n) return;
-    float h0 = 0.f, h1 = 0.f, h2 = 0.f;
-    for (int e = 0; e < a.z_max; ++e) {
-        const int32_t j = a.nbr[i * a.z_max + e];
-        if (j < 0) continue;
-        const float J = a.jval[i * a.z_max + e];
-        const float y0 = X[3 * (int64_t)j], y1 = X[3 * (int64_t)j + 1], y2 = X[3 * (int64_t)j + 2];
-        h0 += J * y0;
-        h1 += J * y1;
-        h2 += J * y2;
-        if (a.dvec) {
-            const float* d = a.dvec + 3 * (i * a.z_max + e);
-            h0 += d[1] * y2 - d[2] * y1;
-            h1 += d[2] * y0 - d[0] * y2;
-            h2 += d[0] * y1 - d[1] * y0;
-        }
-    }
-    const float x0 = X[3 * i], x1 = X[3 * i + 1], x2 = X[3 * i + 2];
-    h2 += -a.aniso2 * x2 - a.hz;
-    const float k0 = h1 * x2 - h2 * x1;
-    const float k1 = h2 * x0 - h0 * x2;
-    const float k2 = h0 * x1 - h1 * x0;
-    const float s0 = S[3 * i], s1 = S[3 * i + 1], s2 = S[3 * i + 2];
-    if (stage == 0) {
-        acc[3 * i] = k0;
-        acc[3 * i + 1] = k1;
-        acc[3 * i + 2] = k2;
-    } else if (stage < 3) {
-        acc[3 * i] += 2.f * k0;
-        acc[3 * i + 1] += 2.f * k1;
-        acc[3 * i + 2] += 2.f * k2;
-    }
-    if (stage < 3) {
-        const float c = stage == 2 ? a.dt : 0.5f * a.dt;
-        Tout[3 * i] = s0 + c * k0;
-        Tout[3 * i + 1] = s1 + c * k1;
-        Tout[3 * i + 2] = s2 + c * k2;
-    } else {
-        const float c = a.dt / 6.0f;
-        const float n0 = s0 + c * (acc[3 * i] + k0);
-        const float n1 = s1 + c * (acc[3 * i + 1] + k1);
-        const float n2 = s2 + c * (acc[3 * i + 2] + k2);
-        S[3 * i] = n0;
-        S[3 * i + 1] = n1;
-        S[3 * i + 2] = n2;
-        frame[3 * i] = n0;
-        frame[3 * i + 1] = n1;
-        frame[3 * i + 2] = n2;
-    }
-}
-
-int launch_traj(const TrajArgs& a, void* stream) {
-    hipStream_t s = (hipStream_t)stream;
-    const unsigned grid = (unsigned)((a.n + 255) / 256);
-    float* S = a.work;
-    float* T1 = a.work + 3 * a.n;
-    float* T2 = a.work + 6 * a.n;
-    float* acc = a.work + 9 * a.n;
-    hipLaunchKernelGGL(traj_init_kernel, dim3(grid), dim3(256), 0, s, a, S);
-    for (int64_t f = 1; f < a.n_frames; ++f) {
-        float* frame = a.frames + f * a.n * 3;
-        hipLaunchKernelGGL(traj_stage_kernel, dim3(grid), dim3(256), 0, s, a, 0, S, (const float*)S, T1, acc, frame);
-        hipLaunchKernelGGL(traj_stage_kernel, dim3(grid), dim3(256), 0, s, a, 1, S, (const float*)T1, T2, acc, frame);
-        hipLaunchKernelGGL(traj_stage_kernel, dim3(grid), dim3(256), 0, s, a, 2, S, (const float*)T2, T1, acc, frame);
-        hipLaunchKernelGGL(traj_stage_kernel, dim3(grid), dim3(256), 0, s, a, 3, S, (const float*)T1, T2, acc, frame);
-    }
     return (int)hipGetLastError();
 }
 

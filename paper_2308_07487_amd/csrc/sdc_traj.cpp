@@ -1,6 +1,6 @@
 // Trajectory generator entry point: bond tables on the host (nearest
 // neighbours of sc/bcc lattices, or J(r) pairs within a cutoff for open
-// samples, with their DMI vectors), then the RK4 kernels of sdc_kernels.hip.
+// samples, with their DMI vectors), then the RK4 kernels of sdc_rk4.hip.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -205,6 +205,33 @@ sdc_status build_bonds(const float* pos, int64_t n, const sdc_traj_spec* sp, Bon
     return SDC_ERR_UNSUPPORTED;
 }
 
+// Whether the sample is a periodic sc box with one uniform coupling whose sites
+// come in the order (x L1 + y) L2 + z: then every position is a lattice point,
+// every site is there once, and no bond table is needed.  Anything else (other
+// orders, wrong positions) goes through lattice_bonds.
+bool canonical_sc(const float* pos, int64_t n, const sdc_traj_spec* sp) {
+    if (sp->kind != SDC_BINS_PERIODIC_SC || sp->coupling != SDC_COUPLING_NN_UNIFORM) return false;
+    int64_t L[3];
+    for (int a = 0; a < 3; ++a) {
+        L[a] = sp->cells[a];
+        if (L[a] < 1 || L[a] > (1 << 16)) return false;
+    }
+    if (n != L[0] * L[1] * L[2]) return false;
+    int64_t i = 0;
+    for (int64_t x = 0; x < L[0]; ++x)
+        for (int64_t y = 0; y < L[1]; ++y)
+            for (int64_t z = 0; z < L[2]; ++z, ++i) {
+                const int64_t c[3] = {x, y, z};
+                for (int a = 0; a < 3; ++a) {
+                    const double p = 2.0 * pos[3 * i + a], r = 2.0 * (double)c[a];
+                    if (std::fabs(p - r) <= 2e-3) continue;  // the usual case: inside the box
+                    const double q = std::floor(p + 0.5);
+                    if (!(std::fabs(p - q) <= 2e-3) || pmod((int64_t)q, 2 * L[a]) != 2 * c[a]) return false;
+                }
+            }
+    return true;
+}
+
 // The annealing schedule: T_k = T_start cool^k while T_k > T_end,
 // sweeps_per_T sweeps each, then sweeps_final sweeps at T_end.  Calls
 // visit(T) once per sweep, in order; returns the number of sweeps.
@@ -257,8 +284,11 @@ extern "C" sdc_status sdc_traj_generate(const float* positions_host, int64_t n_s
         return sdc_internal_set_error(SDC_ERR_INVALID_ARG, "sigma must be >= 0");
     Bonds b;
     std::string err;
-    const sdc_status s = build_bonds(positions_host, n_sites, spec, &b, &err);
-    if (s != SDC_OK) return sdc_internal_set_error(s, err.c_str());
+    const bool stencil = canonical_sc(positions_host, n_sites, spec);
+    if (!stencil) {
+        const sdc_status s = build_bonds(positions_host, n_sites, spec, &b, &err);
+        if (s != SDC_OK) return sdc_internal_set_error(s, err.c_str());
+    }
 
     int count = 0;
     if (hipGetDeviceCount(&count) != hipSuccess || count == 0)
@@ -275,16 +305,18 @@ extern "C" sdc_status sdc_traj_generate(const float* positions_host, int64_t n_s
         if (d_dv) (void)hipFree(d_dv);
         if (d_work) (void)hipFree(d_work);
     };
-    if (hipMalloc(&d_nbr, b.nbr.size() * 4) != hipSuccess || hipMalloc(&d_j, b.jv.size() * 4) != hipSuccess ||
-        (!b.dv.empty() && hipMalloc(&d_dv, b.dv.size() * 4) != hipSuccess) ||
-        hipMalloc(&d_work, (size_t)12 * n_sites * 4) != hipSuccess) {
+    if (!stencil &&
+        (hipMalloc(&d_nbr, b.nbr.size() * 4) != hipSuccess || hipMalloc(&d_j, b.jv.size() * 4) != hipSuccess ||
+         (!b.dv.empty() && hipMalloc(&d_dv, b.dv.size() * 4) != hipSuccess) ||
+         hipMalloc(&d_work, (size_t)9 * n_sites * 4) != hipSuccess)) {
         (void)hipGetLastError();
         cleanup();
         return sdc_internal_set_error(SDC_ERR_OOM, "hipMalloc failed");
     }
     hipStream_t hs = (hipStream_t)stream;
-    hipError_t e = hipMemcpyAsync(d_nbr, b.nbr.data(), b.nbr.size() * 4, hipMemcpyHostToDevice, hs);
-    if (e == hipSuccess) e = hipMemcpyAsync(d_j, b.jv.data(), b.jv.size() * 4, hipMemcpyHostToDevice, hs);
+    hipError_t e = hipSuccess;
+    if (d_nbr) e = hipMemcpyAsync(d_nbr, b.nbr.data(), b.nbr.size() * 4, hipMemcpyHostToDevice, hs);
+    if (e == hipSuccess && d_j) e = hipMemcpyAsync(d_j, b.jv.data(), b.jv.size() * 4, hipMemcpyHostToDevice, hs);
     if (e == hipSuccess && d_dv) e = hipMemcpyAsync(d_dv, b.dv.data(), b.dv.size() * 4, hipMemcpyHostToDevice, hs);
     if (e != hipSuccess) {
         cleanup();
@@ -306,6 +338,15 @@ extern "C" sdc_status sdc_traj_generate(const float* positions_host, int64_t n_s
     ta.frames = frames_dev;
     ta.n_frames = n_frames;
     ta.work = d_work;
+    ta.stencil = stencil ? 1 : 0;
+    ta.st_dmi = spec->D != 0.0;
+    for (int a = 0; a < 3; ++a) ta.L[a] = spec->cells[a];
+    // the tables' values: J, and D (r_j - r_i) / |r_j - r_i| for steps of +-2 or 0
+    // in doubled coordinates
+    ta.st_j = (float)spec->J;
+    ta.st_dp = (float)(spec->D * 2 / 2.0);
+    ta.st_dn = (float)(spec->D * -2 / 2.0);
+    ta.st_dz = (float)(spec->D * 0 / 2.0);
     int le = sdc::launch_traj(ta, stream);
     hipError_t se = hipStreamSynchronize(hs);
     cleanup();
