@@ -475,15 +475,14 @@ bool mc_is_small(int64_t n, const int64_t* class_start, int n_classes) {
     return true;
 }
 
-int prepare_mc_kernels() {
-    const void* f[] = {(const void*)mc_small_kernel<1, 6>, (const void*)mc_small_kernel<0, 0>,
-                       (const void*)mc_small_kernel<0, 6>, (const void*)mc_small_kernel<0, 8>};
-    for (const void* k : f) {
-        const hipError_t e =
-            hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kMcSmallSites * 3 * (int)sizeof(double));
-        if (e != hipSuccess) return (int)e;
-    }
-    return 0;
+int prepare_mc_small(const McArgs& a) {
+    int e = 0;
+    mc_dispatch(a, [&](auto stencil, auto z) {
+        e = (int)hipFuncSetAttribute(
+            (const void*)mc_small_kernel<decltype(stencil)::value, decltype(z)::value>,
+            hipFuncAttributeMaxDynamicSharedMemorySize, kMcSmallSites * 3 * (int)sizeof(double));
+    });
+    return e;
 }
 
 int launch_mc_small(const McArgs& a, const McSmall& m, long long* history, void* stream) {

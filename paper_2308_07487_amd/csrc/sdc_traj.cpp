@@ -480,10 +480,6 @@ extern "C" sdc_status sdc_mc_create(const float* positions_host, int64_t n_sites
         return sdc::set_error(SDC_ERR_NO_DEVICE, "no HIP device");
     if (device < 0 || device >= dev_count) return sdc::set_error(SDC_ERR_INVALID_ARG, "device out of range");
     if (hipSetDevice(device) != hipSuccess) return sdc::set_error(SDC_ERR_HIP, "hipSetDevice");
-    {
-        const int e = sdc::prepare_mc_kernels();
-        if (e != 0) return sdc::set_error(SDC_ERR_HIP, hipGetErrorString((hipError_t)e));
-    }
     sdc_mc* m = nullptr;
     try {
         m = new sdc_mc();
@@ -577,6 +573,13 @@ extern "C" sdc_status sdc_mc_create(const float* positions_host, int64_t n_sites
         ma.cone = d_cone;
         ma.accepted = d_acc;
         mc_stencil(spec, n_sites, m->n_col, m->start, order, b, &ma);
+        if (sdc::mc_is_small(n_sites, m->start.data(), m->n_col)) {
+            const int pe = sdc::prepare_mc_small(ma);
+            if (pe != 0) {
+                delete m;
+                return sdc::set_error(SDC_ERR_HIP, hipGetErrorString((hipError_t)pe));
+            }
+        }
     } catch (const std::bad_alloc&) {
         delete m;
         return sdc::set_error(SDC_ERR_OOM, "host allocation failed");
