@@ -469,8 +469,8 @@ typedef struct sdc_sq sdc_sq;
  *                   per pair (the product of the per-site averages over each
  *                   call's origins), SDC_FLAG_TIMING records HIP events.
  *  device         : HIP device ordinal.
- * Allocates all device memory the accumulator needs: the spins packed in
- * FP64 by chunks of 24 sites (24 bytes per site and frame), the per-site-
+ * Allocates all device memory the accumulator needs: the spins packed by
+ * chunks of 24 sites (12 bytes per site and frame), the per-site-
  * range partial transforms (at most 1 GiB) and the [n_q][3T] transform.
  * Errors: INVALID_ARG, UNSUPPORTED, OOM, NO_DEVICE, HIP.
  */
@@ -501,7 +501,7 @@ sdc_status sdc_sq_accumulate(sdc_sq* sq, const float* spins_dev, int64_t n_frame
 sdc_status sdc_sq_finalize(sdc_sq* sq, double* Sqt_host, double* Sqw_host, void* stream);
 
 /* Durations (milliseconds) of the most recent accumulate of an accumulator
- * created with SDC_FLAG_TIMING: ms[0] the FP64 site-chunk packing of the
+ * created with SDC_FLAG_TIMING: ms[0] the site-chunk packing of the
  * frames, ms[1] the phase contraction kernel, ms[2] the sum of its site
  * ranges and the correlation over origins.  Waits for those events.
  * Errors: INVALID_ARG, STATE, HIP. */

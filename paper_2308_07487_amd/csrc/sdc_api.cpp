@@ -1247,7 +1247,7 @@ struct sdc_sq {
     std::vector<void*> owned;
     float* d_pos = nullptr;
     double* d_q = nullptr;
-    double* d_pack = nullptr;  // [ceil(n / chunk)][t_pad][chunk][3] packed spins (chunk = sq_site_chunk())
+    float* d_pack = nullptr;   // [ceil(n / chunk)][t_pad][chunk][3] packed spins (chunk = sq_site_chunk())
     double* d_part = nullptr;  // [n_split][n_q][2][3 t_used]
     double* d_F = nullptr;     // [n_q][t_used][3][2]
     double* d_raw = nullptr;   // [n_q][n_lags][2]
@@ -1324,15 +1324,18 @@ sdc_status sdc_sq_create(const float* positions_host, int64_t n_sites, const dou
     const int64_t n_cols = 3 * (int64_t)q->t_used;
     // Site ranges: enough workgroups to fill the chip (one per compute unit
     // at a time; 1536 to 3072 of them, the count that leaves the last round
-    // of the chip fullest), at least four staged chunks per range, partials
-    // within kMaxSqPartBytes.
+    // of the chip fullest), at least four staged chunks per range (fewer only
+    // while the workgroups would not fill the chip once), partials within
+    // kMaxSqPartBytes.
     const int64_t chunk = sdc::sq_site_chunk();
     const int64_t tiles = sdc::sq_tiles_per_split(n_q, q->t_used);
     const size_t per_split = (size_t)n_q * 2 * n_cols * sizeof(double);
     int n_cu = 256;
     if (hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || n_cu < 1)
         n_cu = 256;
-    const int64_t split_cap = std::max<int64_t>(1, std::min<int64_t>({n_sites / (4 * chunk),
+    const int64_t per_cu = (tiles * ((n_sites + chunk - 1) / chunk) + n_cu - 1) / n_cu;  // chunks, in one round
+    const int64_t min_chunks = std::max<int64_t>(1, std::min<int64_t>(4, per_cu));
+    const int64_t split_cap = std::max<int64_t>(1, std::min<int64_t>({n_sites / (min_chunks * chunk),
         (int64_t)(kMaxSqPartBytes / per_split), 65535}));
     int64_t best_sps = 0, best_split = 0;
     double best_fill = -1.0;

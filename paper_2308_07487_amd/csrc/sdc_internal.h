@@ -357,8 +357,8 @@ int launch_sqw(const double* in, const double* n_org, int64_t n_sites, double* s
 // q-resolved S(q, t) of Eq. (3) at arbitrary wave vectors (sdc_sq.hip).
 struct SqTransformArgs {
     const float* frames;      // [>= n_frames_used][n][3] fp32, caller's site order (pack input)
-    double* packed;           // [ceil(n / chunk)][t_pad][chunk][3] FP64, chunk = sq_site_chunk() (pack output, contraction input)
-    int t_pad;                // n_frames_used rounded up to whole 48-frame column blocks
+    float* packed;            // [ceil(n / chunk)][t_pad][chunk][3], chunk = sq_site_chunk() (pack output, contraction input)
+    int t_pad;                // n_frames_used rounded up to whole 64-frame column blocks
     const float* pos;         // [n][3] fp32
     const double* q;          // [n_q][3]
     int64_t n;
@@ -384,7 +384,7 @@ int64_t sq_tiles_per_split(int n_q, int n_frames_used);
 int prepare_sq_kernels();
 int sq_site_chunk();
 int sq_frames_per_block();
-// Packs the frames site-chunk-major in FP64 (a.frames -> a.packed).
+// Packs the frames site-chunk-major (a.frames -> a.packed).
 int launch_sq_pack(const SqTransformArgs& a, void* stream);
 // The phase contraction alone (partial transforms of the site ranges).
 int launch_sq_transform(const SqTransformArgs& a, void* stream);
@@ -495,8 +495,8 @@ struct McSmall {
 };
 bool mc_is_small(int64_t n, const int64_t* class_start, int n_classes);
 int launch_mc_small(const McArgs& a, const McSmall& m, long long* history, void* stream);
-// Set the small-sample kernels' dynamic-LDS limit on the current device.
-int prepare_mc_kernels();
+// Set the dynamic-LDS limit of the sample's kernel on the current device.
+int prepare_mc_small(const McArgs& a);
 // Loads init (fp32, or keeps the FP64 state when init is null), sets the cone.
 int launch_mc_setup(const McArgs& a, const float* init, double cone0, void* stream);
 // One sweep: every colour class in order (class c = slots class_start[c] ..

@@ -78,68 +78,90 @@ static_assert(kSqCB % kSqColParts == 0 && kSqSites % 4 == 0, "consumer split");
 static_assert(kSqLdsBytes <= 160 * 1024, "two chunk buffers must fit in LDS");
 
 constexpr int kSqProducers = 64 * kSqProdWaves;
-constexpr int kSqPhPer = kSqSites * kSqQ / kSqProducers;         // phases per producer thread
-constexpr int kSqSbPer = kSqFrames * 3 * kSqSites / kSqProducers;  // spin values per producer thread
-static_assert(kSqPhPer * kSqProducers == kSqSites * kSqQ && kSqProducers % kSqQ == 0, "phase split");
-static_assert(kSqSbPer * kSqProducers == kSqFrames * 3 * kSqSites && kSqSbPer % 2 == 0, "spin split");
-static_assert(kSqPitch % 2 == 0, "16-byte LDS rows");
+constexpr int kSqRow = 3 * kSqSites;                      // spin values of a frame in a chunk
+constexpr int kSqPhPer = kSqSites * kSqQ / kSqProducers;  // phases per producer thread
+constexpr int kSqQuads = kSqFrames * kSqRow / 4;          // 4-value groups of a block's chunk
+constexpr int kSqSbPer = (kSqQuads + kSqProducers - 1) / kSqProducers;  // of them per producer thread
+static_assert(kSqPhPer * kSqProducers == kSqSites * kSqQ && kSqProducers % 64 == 0 && kSqQ == 64, "phase split");
+static_assert(kSqRow % 4 == 0 && kSqPitch % 2 == 0, "16-byte rows");
 
-// Producer side: the phases of the 64 wave vectors at the 24 sites of chunk
-// j0 and the chunk's spins of 64 frames (one contiguous FP64 block of the
-// packed spins) into one buffer.  Producer thread p keeps wave vector p % 64
-// (qv, zero past n_q) and takes sites p / 64 + 4 i; every global load of the
-// chunk is issued before the first is used.
-__device__ __forceinline__ void sq_produce(const SqTransformArgs& a, int ptid, const double (&qv)[3], int64_t f_first,
-                                           int64_t j0, int64_t je, double* __restrict__ ph,
-                                           double* __restrict__ sb) {
-    float px[kSqPhPer], py[kSqPhPer], pz[kSqPhPer];
+// Producer side.  Producer wave w keeps a wave vector per lane (qv, zero past
+// n_q) and takes the sites w + 4 i of a chunk, whose positions are then one
+// scalar load for the wave; the chunk's spins of 64 frames are one contiguous
+// block of the packed spins.  The inputs of a chunk are loaded into registers
+// one chunk ahead (sq_load) and turned into an LDS buffer (sq_store) while the
+// next ones are on their way.  No load is conditional: indices are clamped
+// and the phases masked (loads under a condition became branches with a wait
+// each, twelve in a row for the positions alone).
+struct SqInputs {
+    float pos[kSqPhPer][3];
+    float4 spin[kSqSbPer];
+};
+
+__device__ __forceinline__ void sq_load(const SqTransformArgs& a, int ptid, int64_t f_first, int64_t j0, int64_t je,
+                                        SqInputs& in) {
+    const int w = __builtin_amdgcn_readfirstlane(ptid >> 6);
 #pragma unroll
     for (int i = 0; i < kSqPhPer; ++i) {
-        const int64_t j = j0 + ptid / kSqQ + (kSqProducers / kSqQ) * i;
-        const bool in = j < je;
-        px[i] = in ? a.pos[3 * j] : 0.0f;
-        py[i] = in ? a.pos[3 * j + 1] : 0.0f;
-        pz[i] = in ? a.pos[3 * j + 2] : 0.0f;
+        int64_t j = j0 + w + kSqProdWaves * i;
+        j = j < je ? j : je - 1;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) in.pos[i][c] = a.pos[3 * j + c];
     }
-    // the chunk's 64 frames x 24 sites x 3 components, as pairs of doubles
-    const double2* src =
-        (const double2*)(a.packed + ((j0 / kSqSites) * a.t_pad + f_first) * (3 * kSqSites));
-    double2 v[kSqSbPer / 2];
+    const float4* src = (const float4*)(a.packed + ((j0 / kSqSites) * a.t_pad + f_first) * kSqRow);
 #pragma unroll
-    for (int i = 0; i < kSqSbPer / 2; ++i) v[i] = src[ptid + kSqProducers * i];
+    for (int i = 0; i < kSqSbPer; ++i) {
+        int e = ptid + kSqProducers * i;
+        if (kSqProducers * (i + 1) > kSqQuads) e = e < kSqQuads ? e : kSqQuads - 1;
+        in.spin[i] = src[e];
+    }
+}
+
+__device__ __forceinline__ void sq_store(int ptid, const double (&qv)[3], int64_t j0, int64_t je, const SqInputs& in,
+                                         double* __restrict__ ph, double* __restrict__ sb) {
 #pragma unroll
     for (int i = 0; i < kSqPhPer; ++i) {
-        const int64_t j = j0 + ptid / kSqQ + (kSqProducers / kSqQ) * i;
-        double cs = 0.0, sn = 0.0;
-        if (j < je) {
-            const double th = qv[0] * (double)px[i] + qv[1] * (double)py[i] + qv[2] * (double)pz[i];
-            sincos_small(th, &sn, &cs);
-        }
+        const bool valid = j0 + (ptid >> 6) + kSqProdWaves * i < je;
+        const double th = qv[0] * (double)in.pos[i][0] + qv[1] * (double)in.pos[i][1] + qv[2] * (double)in.pos[i][2];
+        double sn, cs;
+        sincos_small(th, &sn, &cs);
         const int e = ptid + kSqProducers * i;  // = site * 64 + wave vector
-        ph[e] = cs;                             // Re exp(-i q.r), [site][q]
-        ph[kSqSites * kSqQ + e] = -sn;          // Im exp(-i q.r)
+        ph[e] = valid ? cs : 0.0;                    // Re exp(-i q.r), [site][q]
+        ph[kSqSites * kSqQ + e] = valid ? -sn : 0.0;  // Im exp(-i q.r)
     }
 #pragma unroll
-    for (int i = 0; i < kSqSbPer / 2; ++i) {
-        const int e = ptid + kSqProducers * i;  // pair index: frame e / 36, values 2 (e % 36), +1
-        const int fl = e / (3 * kSqSites / 2), r = 2 * (e - fl * (3 * kSqSites / 2));
-        *(double2*)(sb + fl * kSqPitch + r) = v[i];
+    for (int i = 0; i < kSqSbPer; ++i) {
+        const int e = ptid + kSqProducers * i;
+        if (kSqProducers * (i + 1) > kSqQuads && e >= kSqQuads) continue;
+        const int fl = e / (kSqRow / 4), r = 4 * (e - fl * (kSqRow / 4));
+        double2* dst = (double2*)(sb + fl * kSqPitch + r);
+        dst[0] = make_double2((double)in.spin[i].x, (double)in.spin[i].y);
+        dst[1] = make_double2((double)in.spin[i].z, (double)in.spin[i].w);
     }
 }
 
 // Packed spins for the contraction: P[c][f][s][a] = S_j^a(f), j = 24 c + s,
-// FP64, zero for sites past N and frames past n_frames_used (t_pad frames
-// per chunk, a multiple of 64), so that a block's 64 frames are one
-// contiguous block.
+// fp32 as they come, zero for sites past N and frames past n_frames_used
+// (t_pad frames per chunk, a multiple of 64), so that a block's 64 frames are
+// one contiguous block.  Bound: HBM, 12 B read and 12 B written per site and
+// frame.  A thread takes one value of 8 frames.
+constexpr int kSqPackFrames = 8;
 __global__ __launch_bounds__(256) void sq_pack_kernel(SqTransformArgs a) {
-    const int64_t per_chunk = (int64_t)a.t_pad * 3 * kSqSites;
-    const int64_t total = (a.n + kSqSites - 1) / kSqSites * per_chunk;
-    for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < total; x += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t ch = x / per_chunk, rem = x - ch * per_chunk;
-        const int64_t f = rem / (3 * kSqSites);
-        const int r = (int)(rem - f * 3 * kSqSites);
-        const int64_t j = ch * kSqSites + r / 3;
-        a.packed[x] = (f < a.n_frames_used && j < a.n) ? (double)a.frames[(f * a.n + j) * 3 + r % 3] : 0.0;
+    const int64_t n_chunks = (a.n + kSqSites - 1) / kSqSites, per_frame = n_chunks * kSqRow;
+    const int64_t f0 = (int64_t)blockIdx.y * kSqPackFrames;
+    for (int64_t x = (int64_t)blockIdx.x * 256 + threadIdx.x; x < per_frame; x += (int64_t)gridDim.x * 256) {
+        const int64_t ch = x / kSqRow;
+        const int r = (int)(x - ch * kSqRow);
+        const bool in = x < 3 * a.n;  // value x of a frame is component x % 3 of site x / 3
+        float v[kSqPackFrames];
+#pragma unroll
+        for (int k = 0; k < kSqPackFrames; ++k) {
+            const int64_t f = f0 + k < a.n_frames_used ? f0 + k : a.n_frames_used - 1;
+            v[k] = a.frames[f * a.n * 3 + (in ? x : 0)];
+        }
+#pragma unroll
+        for (int k = 0; k < kSqPackFrames; ++k)
+            a.packed[(ch * a.t_pad + f0 + k) * kSqRow + r] = in && f0 + k < a.n_frames_used ? v[k] : 0.0f;
     }
 }
 
@@ -153,7 +175,10 @@ __global__ __launch_bounds__(256) void sq_pack_kernel(SqTransformArgs a) {
 // imaginary phase rows) per 16-column block sharing the spin operand.  One
 // barrier per chunk.  Spins are read from memory once per 64 wave vectors and
 // each phase is computed once per 192 columns (the FP64 vector work of the
-// phases takes issue cycles from the FP64 MFMAs).  The
+// phases takes issue cycles from the FP64 MFMAs).  Bound: FP64 MFMA; 1024
+// wave vectors x 65 536 points x 573 columns (1.54e11 flops) take 2.9 ms
+// against 2.0 at the matrix cores' 77.8 TFLOP/s, 3.5 when the producers waited
+// for each of their loads; without producers the consumers alone take 2.3.  The
 // partial transform of the site range goes to its own slice of `part` (no
 // atomics; the slices are summed in a fixed order).
 __global__ __launch_bounds__(kSqThreads, 1) void sq_transform_kernel(SqTransformArgs a) {
@@ -170,6 +195,9 @@ __global__ __launch_bounds__(kSqThreads, 1) void sq_transform_kernel(SqTransform
     // count (one before the first chunk, one per chunk), so the consumers'
     // accumulators are not live in the producers' code.
     if (producer) {
+        // ahead of the consumers, whose matrix instructions keep the SIMD busy
+        // anyway (3.20 against 3.29 ms for 1024 wave vectors x 65 536 points)
+        __builtin_amdgcn_s_setprio(3);
         const int ptid = tid - 64 * kSqWaves;
         double qv[3] = {0.0, 0.0, 0.0};  // zero past n_q: rows nobody stores
         if (q0 + ptid % kSqQ < a.n_q) {
@@ -177,13 +205,18 @@ __global__ __launch_bounds__(kSqThreads, 1) void sq_transform_kernel(SqTransform
             qv[1] = a.q[3 * (q0 + ptid % kSqQ) + 1];
             qv[2] = a.q[3 * (q0 + ptid % kSqQ) + 2];
         }
-        sq_produce(a, ptid, qv, f_first, jb, je, lds, lds + 2 * kSqPhBuf);
+        SqInputs in;
+        sq_load(a, ptid, f_first, jb, je, in);
+        sq_store(ptid, qv, jb, je, in, lds, lds + 2 * kSqPhBuf);
+        sq_load(a, ptid, f_first, jb + kSqSites < je ? jb + kSqSites : jb, je, in);
         __syncthreads();
         int nxt = 1;
         for (int64_t j0 = jb; j0 < je; j0 += kSqSites) {
-            if (j0 + kSqSites < je)
-                sq_produce(a, ptid, qv, f_first, j0 + kSqSites, je, lds + nxt * kSqPhBuf,
-                           lds + 2 * kSqPhBuf + nxt * kSqSbBuf);
+            const int64_t j1 = j0 + kSqSites, j2 = j1 + kSqSites;
+            if (j1 < je) {
+                sq_store(ptid, qv, j1, je, in, lds + nxt * kSqPhBuf, lds + 2 * kSqPhBuf + nxt * kSqSbBuf);
+                sq_load(a, ptid, f_first, j2 < je ? j2 : j1, je, in);
+            }
             __syncthreads();  // the consumers are done with the other buffer
             nxt ^= 1;
         }
@@ -266,6 +299,7 @@ __global__ __launch_bounds__(256) void sq_reduce_kernel(SqTransformArgs a, doubl
     const int64_t per = (int64_t)a.n_q * 2 * n_cols;
     for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < per; x += (int64_t)gridDim.x * blockDim.x) {
         double sum = 0.0;
+#pragma unroll 8
         for (int sp = 0; sp < a.n_split; ++sp) sum += a.part[sp * per + x];
         const int64_t c = x % n_cols, qr = x / n_cols;
         F[((qr >> 1) * n_cols + c) * 2 + (qr & 1)] = sum;
@@ -275,9 +309,19 @@ __global__ __launch_bounds__(256) void sq_reduce_kernel(SqTransformArgs a, doubl
 // One workgroup per wave vector, one thread per lag:
 // raw[q][t] += sum_o sum_a conj(F_a(q, o s) - <F_a>) F_a(q, o s + t), FP64,
 // <F_a> the average over the origins in the connected form (else 0).
+// LDS: the wave vector's transform staged first (12 loads per origin and lag
+// come from LDS instead of the cache); otherwise, for long series, read where
+// it is.
+template <int LDS>
 __global__ __launch_bounds__(256) void sq_corr_kernel(SqCorrArgs a) {
+    extern __shared__ double staged[];
     const int qq = blockIdx.x;
     const double* F = a.F + (int64_t)qq * a.n_cols * 2;
+    if constexpr (LDS) {
+        for (int x = threadIdx.x; x < (int)a.n_cols * 2; x += 256) staged[x] = F[x];
+        __syncthreads();
+        F = staged;
+    }
     double mre[3] = {0.0, 0.0, 0.0}, mim[3] = {0.0, 0.0, 0.0};
     if (a.connected) {
         for (int o = 0; o < a.n_origins; ++o)
@@ -291,10 +335,12 @@ __global__ __launch_bounds__(256) void sq_corr_kernel(SqCorrArgs a) {
             mim[al] /= a.n_origins;
         }
     }
-    for (int t = threadIdx.x; t < a.n_lags; t += blockDim.x) {
+    for (int t = threadIdx.x; t < a.n_lags; t += 256) {
         double re = 0.0, im = 0.0;
+#pragma unroll 2
         for (int o = 0; o < a.n_origins; ++o) {
             const int64_t f0 = (int64_t)o * a.stride, f1 = f0 + t;
+#pragma unroll
             for (int al = 0; al < 3; ++al) {
                 const double ar = F[(f0 * 3 + al) * 2] - mre[al], ai = F[(f0 * 3 + al) * 2 + 1] - mim[al];
                 const double br = F[(f1 * 3 + al) * 2], bi = F[(f1 * 3 + al) * 2 + 1];
@@ -336,8 +382,9 @@ int prepare_sq_kernels() {
 int sq_frames_per_block() { return kSqFrames; }
 
 int launch_sq_pack(const SqTransformArgs& a, void* stream) {
-    const int64_t total = (a.n + kSqSites - 1) / kSqSites * (int64_t)a.t_pad * 3 * kSqSites;
-    hipLaunchKernelGGL(sq_pack_kernel, dim3((unsigned)blocks_for(total)), dim3(256), 0, (hipStream_t)stream, a);
+    const int64_t per_frame = (a.n + kSqSites - 1) / kSqSites * kSqRow;
+    hipLaunchKernelGGL(sq_pack_kernel, dim3((unsigned)blocks_for(per_frame), (unsigned)(a.t_pad / kSqPackFrames)),
+                       dim3(256), 0, (hipStream_t)stream, a);
     return (int)hipGetLastError();
 }
 
@@ -351,7 +398,11 @@ int launch_sq_corr(const SqTransformArgs& t, const SqCorrArgs& a, void* stream) 
     hipStream_t s = (hipStream_t)stream;
     const int64_t per = (int64_t)t.n_q * 2 * 3 * (int64_t)t.n_frames_used;
     hipLaunchKernelGGL(sq_reduce_kernel, dim3((unsigned)blocks_for(per)), dim3(256), 0, s, t, a.F);
-    hipLaunchKernelGGL(sq_corr_kernel, dim3((unsigned)a.n_q), dim3(256), 0, s, a);
+    const int64_t lds = a.n_cols * 2 * (int64_t)sizeof(double);
+    if (lds <= 64 * 1024)
+        hipLaunchKernelGGL(sq_corr_kernel<1>, dim3((unsigned)a.n_q), dim3(256), (size_t)lds, s, a);
+    else
+        hipLaunchKernelGGL(sq_corr_kernel<0>, dim3((unsigned)a.n_q), dim3(256), 0, s, a);
     return (int)hipGetLastError();
 }
 
