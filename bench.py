@@ -89,7 +89,7 @@ WORKLOADS = {
 # SHA-256 they record (a changed kernel, layout or tuning file reports
 # traffic null: the tuning file picks the schedule and segment length).
 _CSRC = os.path.join(ROOT, "paper_2308_07487_amd", "csrc")
-_FUSED_SOURCES = [os.path.join(_CSRC, f) for f in ("sdc_kernels.hip", "sdc_internal.h", "sdc_layout.cpp")] + [
+_FUSED_SOURCES = [os.path.join(_CSRC, f) for f in ("sdc_fused.h", "sdc_device.h", "sdc_kernels.hip", "sdc_internal.h", "sdc_layout.cpp")] + [
     os.path.join(ROOT, "paper_2308_07487_amd", "tuning", "gfx950.json")]
 TRAFFIC_PROFILES = {
     "sc36_afm": (os.path.join(ROOT, "profiles", "fused_sc36_traffic.md"), _FUSED_SOURCES),
