@@ -248,12 +248,7 @@ sdc_status fused_args(const sdc_plan* p, const LagSel& sel, sdc::FusedArgs* a) {
     a->e2 = p->d_e2;
     a->n_shells = L.n_shells;
     a->inv_w = L.n_shells ? (float)((double)L.n_shells / (double)p->bins.r_max) : 0.0f;
-    a->kind = L.kind;
-    a->L0 = L.L[0];
-    a->L1 = L.L[1];
-    a->L2 = L.L[2];
-    a->W1 = L.W[1];
-    a->W2 = L.W[2];
+    a->map = sdc::window_map(L);
     a->win = L.win;
     a->H = p->d_H;
     a->det = p->d_Hq != nullptr;
@@ -398,6 +393,11 @@ sdc_status sdc_layout_keys(const float* positions_host, int64_t n_sites, const s
     const int64_t n = n_sites;
     std::vector<uint8_t> seen((size_t)(n * n), 0);
     const float inv_w = lay.n_shells ? (float)((double)lay.n_shells / (double)bins->r_max) : 0.0f;
+    const sdc::WindowMap map = sdc::window_map(lay);
+    auto window = [&](int64_t pi, int a, int64_t pj, int b, int shift) {
+        return lay.linear ? sdc::linear_window(a, lay.gtab[pi], b, lay.gtab[pj], shift)
+                          : lay.gtab[pj] - lay.gtab[pi] + shift;
+    };
     for (const KStream& st : lay.streams) {
         for (int p = st.p0; p < st.p1; ++p) {
             const KPair& pr = lay.pairs[p];
@@ -409,7 +409,7 @@ sdc_status sdc_layout_keys(const float* positions_host, int64_t n_sites, const s
                     if (lay.kind != SDC_BINS_RADIAL) {
                         // every slot, padding included, must land inside the window:
                         // the kernels bin padded slots too (with zero spins)
-                        const int w = lay.gtab[pj] - lay.gtab[pi] + pr.shift;
+                        const int w = window(pi, a, pj, b, pr.shift);
                         if (w < 0 || w >= lay.win)
                             return set_err(SDC_ERR_INVALID_ARG, "window coordinate out of range");
                     }
@@ -421,9 +421,7 @@ sdc_status sdc_layout_keys(const float* positions_host, int64_t n_sites, const s
                         key = sdc::shell_of(sdc::dist2_f32(ri[0], ri[1], ri[2], rj[0], rj[1], rj[2]),
                                             lay.e2.data(), lay.n_shells, inv_w);
                     } else {
-                        const int w = lay.gtab[pj] - lay.gtab[pi] + pr.shift;
-                        if (w < 0 || w >= lay.win) return set_err(SDC_ERR_INVALID_ARG, "window coordinate out of range");
-                        key = sdc::window_bin(lay, st, w);
+                        key = sdc::window_bin(map, st, window(pi, a, pj, b, pr.shift));
                     }
                     const int64_t x = (int64_t)i * n + j;
                     if (seen[x]) return set_err(SDC_ERR_INVALID_ARG, "pair visited twice");
@@ -606,12 +604,7 @@ sdc_status sdc_plan_create_tuned(const float* positions_host, int64_t n_sites, c
     ca.e2 = p->d_e2;
     ca.n_shells = L.n_shells;
     ca.inv_w = L.n_shells ? (float)((double)L.n_shells / (double)bins->r_max) : 0.0f;
-    ca.kind = L.kind;
-    ca.L0 = L.L[0];
-    ca.L1 = L.L[1];
-    ca.L2 = L.L[2];
-    ca.W1 = L.W[1];
-    ca.W2 = L.W[2];
+    ca.map = sdc::window_map(L);
     ca.win = L.win;
     ca.counts = p->d_counts;
     int e = sdc::launch_count(ca, nullptr);

@@ -429,6 +429,13 @@ __device__ __forceinline__ void pair_loop(const TaskCtx& c) {
                         bin[r] = shell_of(d2, c.e2s, a.n_shells, a.inv_w);
                     }
                 }
+            } else if (a.map.linear) {
+                const int gj = a.gtab[sj];
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int row = 8 * (r / 4) + (r % 4);
+                    bin[r] = linear_window(wi * 32 + 4 * h + row, a.gtab[rowbase + row], wj * 32 + l32, gj, pr.shift);
+                }
             } else {
                 const int gj = a.gtab[sj] + pr.shift;
 #pragma unroll
@@ -488,6 +495,9 @@ __device__ __forceinline__ void pair_loop(const TaskCtx& c) {
 // step may straddle two components.
 // SCHED: kSchedOnePass, kSchedTwoPass (hi/lo splits only) or kSchedLagSplit
 // (eight waves: wave w takes quadrant w mod 4 and the lag half w / 4).
+// The last lag group of a phase may hold few lags: in the default schedules a
+// group with none in its upper half, or upper three quarters, multiplies only
+// the rest (50 lags of a phase in 16-lag groups cost 52 instead of 64).
 template <int PREC, int RADIAL, int PAIRED, int SCHED>
 __device__ __forceinline__ void fused_task(const FusedArgs& a, int task, double* hist) {
     constexpr int LG = lag_group(PREC);
@@ -498,8 +508,13 @@ __device__ __forceinline__ void fused_task(const FusedArgs& a, int task, double*
     const int wave = tid >> 6;
     TaskCtx c;
     c.a = &a;
-    c.grp = a.groups[task % a.n_groups];
-    c.st = a.streams[task / a.n_groups];
+    // an even number of lag groups is taken in an order that turns with the
+    // segment: workgroups go to the shader engines in turn, and a short last
+    // group that always met the same engine would leave it idle (FP32 sc
+    // 21x20x19 with 2 x 50 lags: 21.2 instead of 25.0 ms)
+    const int segment = task / a.n_groups;
+    c.grp = a.groups[(task - segment * a.n_groups + (a.n_groups % 2 == 0 ? segment : 0)) % a.n_groups];
+    c.st = a.streams[segment];
     c.hist = hist;
     c.e2s = e2s;
     c.quadrant = wave & 3;
@@ -515,6 +530,10 @@ __device__ __forceinline__ void fused_task(const FusedArgs& a, int task, double*
             pair_loop<PREC, RADIAL, PAIRED, SCHED, LG / 2, 0>(c);
         else
             pair_loop<PREC, RADIAL, PAIRED, SCHED, LG / 2, LG / 2>(c);
+    } else if (SCHED == default_sched(PREC) && c.grp.mask < (1 << LG / 4)) {
+        pair_loop<PREC, RADIAL, PAIRED, SCHED, SCHED == default_sched(PREC) ? LG / 4 : LG, 0>(c);
+    } else if (SCHED == default_sched(PREC) && c.grp.mask < (1 << LG / 2)) {
+        pair_loop<PREC, RADIAL, PAIRED, SCHED, SCHED == default_sched(PREC) ? LG / 2 : LG, 0>(c);
     } else {
         pair_loop<PREC, RADIAL, PAIRED, SCHED, LG, 0>(c);
     }
@@ -533,14 +552,7 @@ __device__ __forceinline__ void fused_task(const FusedArgs& a, int task, double*
             if constexpr (RADIAL) {
                 b = w;
             } else {
-                const int w0 = w / (a.W1 * a.W2);
-                const int w1 = (w / a.W2) % a.W1;
-                const int w2 = w % a.W2;
-                const int k0 = pmod_dev(st.base[0] + w0, a.L0);
-                const int k1 = pmod_dev(st.base[1] + w1, a.L1);
-                const int k2 = pmod_dev(st.base[2] + w2, a.L2);
-                b = ((int64_t)k0 * a.L1 + k1) * a.L2 + k2;
-                if (a.kind == SDC_BINS_PERIODIC_BCC) b = 2 * b + st.parity;
+                b = window_bin(a.map, st, w);
             }
             const int64_t t = (int64_t)a.stride * (grp.u0 + m) + grp.phase;
             if (a.det)

@@ -11,9 +11,10 @@
 namespace sdc {
 
 // Sites are grouped in tiles of 64.  Periodic lattices: a tile is a brick of
-// at most 4x4x4 cells of one sublattice, slot (ox*4 + oy)*4 + oz.  Radial:
-// 64 consecutive points in Morton order.  Unused slots are padding (zero
-// spins, no counts).
+// at most 64 cells of one sublattice, slot (o0 s1 + o1) s2 + o2, or, where
+// bricks would leave more tiles, 64 consecutive cells in box order (see
+// choose_layout).  Radial: 64 consecutive points in Morton order.  Unused
+// slots are padding (zero spins, no counts).
 constexpr int kTile = 64;
 // Lags handled together by one fused task (consecutive lag indices u): 8
 // for the reduced-precision forms (128 accumulator registers per wave for
@@ -25,7 +26,7 @@ constexpr int lag_group(int precision) { return precision == SDC_PREC_FP32 ? 16 
 // one address (with a row per lag each add needs an address of its own), and
 // an odd pitch, so that neighbouring bins lie in different banks.  A window
 // has at most 512 bins (2 s_a per axis for bricks of s_0 s_1 s_2 <= 64
-// cells), a radial one 1024: 78 KB for 8-lag groups, two of which fit in a
+// cells, 508 for tiles in box order), a radial one 1024: 78 KB for 8-lag groups, two of which fit in a
 // CU's LDS, and 143 KB for FP32's 16.  Together with the separate loop of
 // the deterministic mode (one basic block of adds instead of one block per
 // element) this took the fused launch from 1093 to 1081 ms at sc 36^3
@@ -70,6 +71,10 @@ constexpr int wg_per_cu(int sched) { return sched == kSchedTwoPass || sched == k
 // Waves per SIMD at that occupancy: the launch-bounds minimum that sets the
 // register budget (four SIMDs per CU, 64-lane waves).
 constexpr int waves_per_simd(int sched) { return wg_per_cu(sched) * threads_per_wg(sched) / 256; }
+// The schedule a plan takes when nothing is asked for.
+constexpr int default_sched(int precision) {
+    return precision == SDC_PREC_SPLIT_BF16 || precision == SDC_PREC_SPLIT_FP16 ? kSchedTwoPass : kSchedOnePass;
+}
 constexpr bool sched_valid(int precision, int sched) {
     return sched == kSchedOnePass || sched == kSchedLagSplit ||
            (sched == kSchedTwoPass && (precision == SDC_PREC_SPLIT_BF16 || precision == SDC_PREC_SPLIT_FP16)) ||
@@ -90,7 +95,9 @@ struct KPair {
 // A stream is a run of tile pairs whose epilogue shares one LDS histogram.
 // Periodic: all pairs (I, I + db) for a fixed brick offset db and fixed
 // sublattices; the histogram is indexed by the window coordinate and maps to
-// global bins through base/parity.  Radial: all pairs (I, J) of one I; the
+// global bins through base/parity.  Tiles in box order: all pairs of a fixed
+// tile offset d and sublattices, those that wrap around the end apart; base[0]
+// is the bin cell of window 0.  Radial: all pairs (I, J) of one I; the
 // histogram is indexed by shell.
 struct KStream {
     int32_t p0, p1;
@@ -111,11 +118,12 @@ struct Layout {
     int64_t n_bins = 0;
     int64_t n_pad = 0;
     int32_t n_tiles = 0;
-    int W[3] = {1, 1, 1};   // periodic window extents
+    int W[3] = {1, 1, 1};   // periodic window extents (bricks)
+    bool linear = false;    // tiles in box order
     int win = 0;            // histogram bins per lag (window size or n_shells)
     int n_shells = 0;
     std::vector<int32_t> perm;   // [n_pad] original site index, -1 = padding
-    std::vector<int32_t> gtab;   // [n_pad] window coordinate of the slot
+    std::vector<int32_t> gtab;   // [n_pad] window coordinate of the slot (box order: y << 16 | z of its cell)
     std::vector<float> pos4;     // [n_pad][4] radial positions, packed order
     std::vector<float> e2;       // [n_shells] radial squared edges
     std::vector<KPair> pairs;
@@ -153,8 +161,48 @@ void split_streams(Layout* lay, int seg);
 // lag groups by `slots` workgroups at a time (at most cap).
 int fitted_segment(const Layout& lay, int n_groups, int64_t slots, int cap);
 
-// Global bin of window coordinate w of stream s (periodic kinds).
-int64_t window_bin(const Layout& lay, const KStream& s, int w);
+#if defined(__HIPCC__)
+#define SDC_HD __host__ __device__
+#else
+#define SDC_HD
+#endif
+
+// Tiles in box order.  Cell (x, y, z) is number (x L1 + y) L2 + z of its
+// sublattice; a displacement's bin cell b = (kx L1 + ky) L2 + kz, k = (c_j - c_i
+// - s) mod L (s = 1 from the second sublattice to the first, else 0), is
+//   b = (j - i) - s (1 + L2 + L1 L2) + cz L2 + cy L1 L2  (mod the cells),
+// j - i the difference of the cell numbers, cz = [z_j - s < z_i] and cy =
+// [y_j - s < y_i] the borrows.  For a fixed tile offset j - i takes 127 values,
+// so the window is 4 x 127: w = (slot_j - slot_i + 63) + 127 cz + 254 cy.
+constexpr int kLinearSpan = 2 * kTile - 1, kLinearWin = 4 * kLinearSpan;
+SDC_HD inline int linear_window(int slot_i, int gi, int slot_j, int gj, int s) {
+    const int cz = ((gj & 0xFFFF) - s - (gi & 0xFFFF)) >> 31, cy = ((gj >> 16) - s - (gi >> 16)) >> 31;  // -1 or 0
+    return slot_j - slot_i + (kTile - 1) - kLinearSpan * cz - 2 * kLinearSpan * cy;
+}
+
+// What maps a stream's window coordinates to global bins (periodic kinds).
+struct WindowMap {
+    int kind, linear, L0, L1, L2, W1, W2;
+};
+
+// Global bin of window coordinate w of stream s.
+SDC_HD inline int64_t window_bin(const WindowMap& m, const KStream& s, int w) {
+    int64_t b;
+    if (m.linear) {
+        const int q = w / kLinearSpan, r = w - q * kLinearSpan;
+        const int64_t plane = (int64_t)m.L1 * m.L2;
+        b = (s.base[0] + r + (int64_t)(q & 1) * m.L2 + (q >> 1) * plane) % (m.L0 * plane);
+    } else {
+        const int w0 = w / (m.W1 * m.W2), w1 = (w / m.W2) % m.W1, w2 = w % m.W2;
+        int k0 = (s.base[0] + w0) % m.L0, k1 = (s.base[1] + w1) % m.L1, k2 = (s.base[2] + w2) % m.L2;
+        if (k0 < 0) k0 += m.L0;
+        if (k1 < 0) k1 += m.L1;
+        if (k2 < 0) k2 += m.L2;
+        b = ((int64_t)k0 * m.L1 + k1) * m.L2 + k2;
+    }
+    return m.kind == SDC_BINS_PERIODIC_BCC ? 2 * b + s.parity : b;
+}
+WindowMap window_map(const Layout& lay);
 
 // Radial shell of a squared distance: the largest k with e2[k] <= d2.
 #if defined(__HIPCC__)
@@ -246,7 +294,8 @@ struct FusedArgs {
     const float* e2;
     int n_shells;
     float inv_w;
-    int kind, L0, L1, L2, W1, W2, win;
+    WindowMap map;                 // periodic kinds
+    int win;
     double* H;
     int det;                       // deterministic mode: fixed-point bins in Hq
     unsigned long long* Hq;
@@ -285,7 +334,8 @@ struct CountArgs {
     const float* e2;
     int n_shells;
     float inv_w;
-    int kind, L0, L1, L2, W1, W2, win;
+    WindowMap map;
+    int win;
     unsigned long long* counts;
 };
 int launch_count(const CountArgs& a, void* stream);

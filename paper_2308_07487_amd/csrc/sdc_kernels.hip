@@ -193,7 +193,7 @@ static const void* fused_kernel_of(int precision, int sched, int radial, int pai
 int launch_fused(const FusedArgs& a, void* stream) {
     if (a.n_groups * a.n_streams == 0) return 0;
     if (!sched_valid(a.precision, a.sched)) return (int)hipErrorInvalidValue;
-    const void* fn = fused_kernel_of(a.precision, a.sched, a.kind == SDC_BINS_RADIAL, a.O8 % 2 == 0, false);
+    const void* fn = fused_kernel_of(a.precision, a.sched, a.map.kind == SDC_BINS_RADIAL, a.O8 % 2 == 0, false);
     if (!fn) return (int)hipErrorInvalidValue;
     const int lds = fused_lds_bytes(a.win, a.precision);
     const int n_tasks = a.n_groups * a.n_streams;
@@ -263,7 +263,8 @@ __global__ __launch_bounds__(256) void count_kernel(CountArgs a) {
                 const float4 rj = *(const float4*)(a.pos4 + 4 * pj);
                 w = shell_of(dist2_f32(ri.x, ri.y, ri.z, rj.x, rj.y, rj.z), e2s, a.n_shells, a.inv_w);
             } else {
-                w = a.gtab[pj] - a.gtab[pi] + pr.shift;
+                w = a.map.linear ? linear_window(e >> 6, a.gtab[pi], e & 63, a.gtab[pj], pr.shift)
+                                 : a.gtab[pj] - a.gtab[pi] + pr.shift;
             }
             atomicAdd(&hcount[w], 1u);
         }
@@ -276,14 +277,7 @@ __global__ __launch_bounds__(256) void count_kernel(CountArgs a) {
         if constexpr (RADIAL) {
             b = w;
         } else {
-            const int w0 = w / (a.W1 * a.W2);
-            const int w1 = (w / a.W2) % a.W1;
-            const int w2 = w % a.W2;
-            const int k0 = pmod_dev(st.base[0] + w0, a.L0);
-            const int k1 = pmod_dev(st.base[1] + w1, a.L1);
-            const int k2 = pmod_dev(st.base[2] + w2, a.L2);
-            b = ((int64_t)k0 * a.L1 + k1) * a.L2 + k2;
-            if (a.kind == SDC_BINS_PERIODIC_BCC) b = 2 * b + st.parity;
+            b = window_bin(a.map, st, w);
         }
         atomicAdd(&a.counts[b], (unsigned long long)v);
     }
@@ -330,9 +324,9 @@ int launch_radial_keys(const CountArgs& a, int64_t n_pairs, uint16_t* keys, void
 int launch_count(const CountArgs& a, void* stream) {
     if (a.n_streams == 0) return 0;
     hipStream_t s = (hipStream_t)stream;
-    const int lds = a.win * 4 + (a.kind == SDC_BINS_RADIAL ? a.n_shells * 4 : 0);
+    const int lds = a.win * 4 + (a.map.kind == SDC_BINS_RADIAL ? a.n_shells * 4 : 0);
     hipError_t e;
-    if (a.kind == SDC_BINS_RADIAL) {
+    if (a.map.kind == SDC_BINS_RADIAL) {
         e = hipFuncSetAttribute((const void*)count_kernel<1>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (e != hipSuccess) return (int)e;
         hipLaunchKernelGGL(count_kernel<1>, dim3(a.n_streams), dim3(256), lds, s, a);

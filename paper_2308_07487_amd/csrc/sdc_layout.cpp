@@ -2,7 +2,7 @@
 // and the stream/pair work lists of the fused kernel.
 //
 // Periodic lattices (bins = displacements modulo the box): sites are grouped
-// in bricks of at most 4x4x4 cells of one sublattice.  For a fixed brick
+// in bricks of at most 64 cells of one sublattice, or 64 by 64 in box order.  For a fixed brick
 // offset db every pair of bricks (I, I + db) sees displacements inside one
 // small window, so one LDS histogram of window coordinates serves a whole
 // stream of tile pairs and is mapped to global bins once.  This is the
@@ -83,25 +83,92 @@ uint64_t spread3(uint64_t v) {
     return v;
 }
 
-sdc_status build_periodic(const float* pos, int64_t n, const sdc_bin_spec* spec, int seg, Layout* lay,
-                          std::string* err) {
-    const bool bcc = spec->kind == SDC_BINS_PERIODIC_BCC;
-    const int nsub = bcc ? 2 : 1;
-    int L[3];
-    for (int a = 0; a < 3; ++a) {
-        L[a] = spec->cells[a];
-        if (L[a] < 1 || L[a] > 4096) return fail(err, SDC_ERR_INVALID_ARG, "cells must be in [1, 4096]");
-        lay->L[a] = L[a];
-    }
+// Cell and sublattice of every site; errors as the public entry points report
+// them.  cell[i] = (x L1 + y) L2 + z.
+sdc_status lattice_cells(const float* pos, int64_t n, bool bcc, const int L[3], std::vector<int32_t>* cell,
+                         std::vector<uint8_t>* sub, std::string* err) {
     const int64_t cells = (int64_t)L[0] * L[1] * L[2];
-    if (n != nsub * cells)
-        return fail(err, SDC_ERR_INVALID_ARG, "n_sites must equal the number of lattice sites of the box");
-    lay->n_bins = n;
+    cell->resize((size_t)n);
+    sub->assign((size_t)n, 0);
+    std::vector<uint8_t> seen((size_t)n, 0);
+    for (int64_t i = 0; i < n; ++i) {
+        int c[3], beta = 0;
+        if (!bcc) {
+            for (int a = 0; a < 3; ++a) {
+                double p = pos[3 * i + a];
+                double r = std::floor(p + 0.5);
+                if (!(std::fabs(p - r) <= 1e-3))
+                    return fail(err, SDC_ERR_INVALID_ARG, "position is not a lattice point");
+                c[a] = (int)pmod((int64_t)r, L[a]);
+            }
+        } else {
+            int64_t d[3];
+            for (int a = 0; a < 3; ++a) {
+                double p = 2.0 * pos[3 * i + a];
+                double r = std::floor(p + 0.5);
+                if (!(std::fabs(p - r) <= 2e-3))
+                    return fail(err, SDC_ERR_INVALID_ARG, "position is not a bcc lattice point");
+                d[a] = (int64_t)r;
+            }
+            beta = (int)pmod(d[0], 2);
+            if (pmod(d[1], 2) != beta || pmod(d[2], 2) != beta)
+                return fail(err, SDC_ERR_INVALID_ARG, "position is not a bcc lattice point");
+            for (int a = 0; a < 3; ++a) c[a] = (int)pmod((d[a] - beta) / 2, L[a]);
+        }
+        const int64_t x = ((int64_t)c[0] * L[1] + c[1]) * L[2] + c[2];
+        if (seen[(size_t)(beta * cells + x)]) return fail(err, SDC_ERR_INVALID_ARG, "duplicate lattice site");
+        seen[(size_t)(beta * cells + x)] = 1;
+        (*cell)[(size_t)i] = (int32_t)x;
+        (*sub)[(size_t)i] = (uint8_t)beta;
+    }
+    return SDC_OK;
+}
 
+// Tiles in box order (see linear_window): the last tile of a sublattice is the
+// only one with padding.
+void layout_linear(int64_t n, int nsub, const std::vector<int32_t>& cell, const std::vector<uint8_t>& sub, Layout* lay) {
+    const int* L = lay->L;
+    const int64_t plane = (int64_t)L[1] * L[2], cells = L[0] * plane;
+    const int T = (int)((cells + kTile - 1) / kTile);
+    lay->linear = true;
+    lay->win = kLinearWin;
+    lay->n_tiles = nsub * T;
+    lay->n_pad = (int64_t)lay->n_tiles * kTile;
+    lay->perm.assign(lay->n_pad, -1);
+    lay->gtab.assign(lay->n_pad, 0);
+    for (int64_t i = 0; i < n; ++i) lay->perm[(int64_t)sub[i] * T * kTile + cell[i]] = (int32_t)i;
+    for (int beta = 0; beta < nsub; ++beta)
+        for (int64_t c = 0; c < cells; ++c)
+            lay->gtab[(int64_t)beta * T * kTile + c] = (int32_t)(((c / L[2]) % L[1]) << 16 | (c % L[2]));
+    lay->streams.reserve((size_t)nsub * nsub * 2 * T);
+    lay->pairs.reserve((size_t)nsub * nsub * T * T);
+    for (int bi = 0; bi < nsub; ++bi)
+        for (int bj = 0; bj < nsub; ++bj) {
+            const int shift = bj < bi ? 1 : 0;
+            for (int d = 0; d < T; ++d)
+                for (int wrap = 0; wrap < 2; ++wrap) {
+                    // I + d < T, or past the end: J = I + d - T
+                    const int lo = wrap ? T - d : 0, hi = wrap ? T : T - d;
+                    if (lo >= hi) continue;
+                    KStream s{};
+                    s.p0 = (int32_t)lay->pairs.size();
+                    s.base[0] = (int32_t)pmod((int64_t)kTile * (wrap ? d - T : d) - (kTile - 1) -
+                                                  shift * (1 + L[2] + plane), cells);
+                    s.parity = (int)pmod(bj - bi, 2);
+                    for (int ti = lo; ti < hi; ++ti)
+                        lay->pairs.push_back(KPair{bi * T + ti, bj * T + (wrap ? ti + d - T : ti + d), shift, 0});
+                    s.p1 = (int32_t)lay->pairs.size();
+                    lay->streams.push_back(s);
+                }
+        }
+}
+
+void layout_bricks(int64_t n, int nsub, const int nb[3], const std::vector<int32_t>& cell,
+                   const std::vector<uint8_t>& sub, Layout* lay) {
+    const int* L = lay->L;
     std::vector<int> st[3];
     std::vector<int> chunk_of[3];
-    int nb[3], maxsz[3];
-    choose_bricks(L, nb);
+    int maxsz[3];
     for (int a = 0; a < 3; ++a) {
         chunks(L[a], nb[a], &st[a]);
         maxsz[a] = 0;
@@ -149,36 +216,13 @@ sdc_status build_periodic(const float* pos, int64_t n, const sdc_bin_spec* spec,
         lay->gtab[p] = (o0 * W1 + o1) * W2 + o2;
     }
     for (int64_t i = 0; i < n; ++i) {
-        int c[3], beta = 0;
-        if (!bcc) {
-            for (int a = 0; a < 3; ++a) {
-                double p = pos[3 * i + a];
-                double r = std::floor(p + 0.5);
-                if (!(std::fabs(p - r) <= 1e-3))
-                    return fail(err, SDC_ERR_INVALID_ARG, "position is not a lattice point");
-                c[a] = (int)pmod((int64_t)r, L[a]);
-            }
-        } else {
-            int64_t d[3];
-            for (int a = 0; a < 3; ++a) {
-                double p = 2.0 * pos[3 * i + a];
-                double r = std::floor(p + 0.5);
-                if (!(std::fabs(p - r) <= 2e-3))
-                    return fail(err, SDC_ERR_INVALID_ARG, "position is not a bcc lattice point");
-                d[a] = (int64_t)r;
-            }
-            beta = (int)pmod(d[0], 2);
-            if (pmod(d[1], 2) != beta || pmod(d[2], 2) != beta)
-                return fail(err, SDC_ERR_INVALID_ARG, "position is not a bcc lattice point");
-            for (int a = 0; a < 3; ++a) c[a] = (int)pmod((d[a] - beta) / 2, L[a]);
-        }
+        const int c[3] = {cell[i] / (L[1] * L[2]), (cell[i] / L[2]) % L[1], cell[i] % L[2]};
         int k[3], o[3];
         for (int a = 0; a < 3; ++a) {
             k[a] = chunk_of[a][c[a]];
             o[a] = c[a] - st[a][k[a]];
         }
-        int64_t p = (int64_t)tile_of(beta, k[0], k[1], k[2]) * kTile + (o[0] * maxsz[1] + o[1]) * maxsz[2] + o[2];
-        if (lay->perm[p] >= 0) return fail(err, SDC_ERR_INVALID_ARG, "duplicate lattice site");
+        const int64_t p = (int64_t)tile_of(sub[i], k[0], k[1], k[2]) * kTile + (o[0] * maxsz[1] + o[1]) * maxsz[2] + o[2];
         lay->perm[p] = (int32_t)i;
     }
     const int stride[3] = {W1 * W2, W2, 1};
@@ -192,7 +236,7 @@ sdc_status build_periodic(const float* pos, int64_t n, const sdc_bin_spec* spec,
                         const int d[3] = {d0, d1, d2};
                         KStream s{};
                         s.p0 = (int32_t)lay->pairs.size();
-                        const int cshift = (bcc && bj < bi) ? 1 : 0;
+                        const int cshift = bj < bi ? 1 : 0;
                         for (int a = 0; a < 3; ++a) s.base[a] = amin[a][d[a]] - (maxsz[a] - 1) - cshift;
                         s.parity = (int)pmod(bj - bi, 2);
                         for (int k0 = 0; k0 < nb[0]; ++k0)
@@ -214,6 +258,40 @@ sdc_status build_periodic(const float* pos, int64_t n, const sdc_bin_spec* spec,
                         s.p1 = (int32_t)lay->pairs.size();
                         lay->streams.push_back(s);
                     }
+}
+
+// Bricks or box order: whichever needs fewer tiles (the product costs
+// O(tiles^2)); on a tie bricks, whose windows are smaller.  Bricks fill their
+// slots when the edges have divisors that multiply to 64; the box order always
+// does but for the last tile, at the price of two compares per element and a
+// window of 508 bins.  Fused launch with bricks only / this rule: bcc 13x14x15
+// (98 / 86 tiles) 7.2 / 5.7 ms, bcc 9x10x11 with stride 3 0.77 / 0.40 ms, sc 30^3
+// x 100 lags 147 / 122 ms, ten samples of edges 10 to 22 in one batch 290 / 218
+// ms, 90 x 90 (130 / 127 tiles) 8.3 / 8.1 ms, 200 x 200 102 / 101 ms.
+sdc_status build_periodic(const float* pos, int64_t n, const sdc_bin_spec* spec, int seg, Layout* lay,
+                          std::string* err) {
+    const bool bcc = spec->kind == SDC_BINS_PERIODIC_BCC;
+    const int nsub = bcc ? 2 : 1;
+    int L[3];
+    for (int a = 0; a < 3; ++a) {
+        L[a] = spec->cells[a];
+        if (L[a] < 1 || L[a] > 4096) return fail(err, SDC_ERR_INVALID_ARG, "cells must be in [1, 4096]");
+        lay->L[a] = L[a];
+    }
+    const int64_t cells = (int64_t)L[0] * L[1] * L[2];
+    if (n != nsub * cells)
+        return fail(err, SDC_ERR_INVALID_ARG, "n_sites must equal the number of lattice sites of the box");
+    lay->n_bins = n;
+    std::vector<int32_t> cell;
+    std::vector<uint8_t> sub;
+    const sdc_status s = lattice_cells(pos, n, bcc, L, &cell, &sub, err);
+    if (s != SDC_OK) return s;
+    int nb[3];
+    choose_bricks(L, nb);
+    if ((cells + kTile - 1) / kTile < (int64_t)nb[0] * nb[1] * nb[2])
+        layout_linear(n, nsub, cell, sub, lay);
+    else
+        layout_bricks(n, nsub, nb, cell, sub, lay);
     split_streams(lay, seg);
     return SDC_OK;
 }
@@ -364,16 +442,8 @@ sdc_status build_layout(const float* pos, int64_t n, const sdc_bin_spec* spec, i
     return SDC_OK;
 }
 
-int64_t window_bin(const Layout& lay, const KStream& s, int w) {
-    const int w0 = w / (lay.W[1] * lay.W[2]);
-    const int w1 = (w / lay.W[2]) % lay.W[1];
-    const int w2 = w % lay.W[2];
-    const int64_t k0 = pmod((int64_t)s.base[0] + w0, lay.L[0]);
-    const int64_t k1 = pmod((int64_t)s.base[1] + w1, lay.L[1]);
-    const int64_t k2 = pmod((int64_t)s.base[2] + w2, lay.L[2]);
-    int64_t b = (k0 * lay.L[1] + k1) * lay.L[2] + k2;
-    if (lay.kind == SDC_BINS_PERIODIC_BCC) b = 2 * b + s.parity;
-    return b;
+WindowMap window_map(const Layout& lay) {
+    return WindowMap{lay.kind, lay.linear ? 1 : 0, lay.L[0], lay.L[1], lay.L[2], lay.W[1], lay.W[2]};
 }
 
 }  // namespace sdc
