@@ -236,6 +236,7 @@ sdc_status fused_args(const sdc_plan* p, const LagSel& sel, sdc::FusedArgs* a) {
     a->O8 = p->O8;
     a->F8 = p->F8;
     a->nk = p->nk;
+    a->n_phase = p->corr.origin_stride;
     a->phase_stride = (int64_t)3 * p->F8 * L.n_pad;
     a->pairs = p->d_pairs;
     a->streams = p->d_streams;

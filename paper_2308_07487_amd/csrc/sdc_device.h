@@ -15,17 +15,40 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-// 32-byte pack element: 8 time samples of one component of one site.
-// Split precisions: 8 hi halves then 8 lo halves.  FP32: 8 floats.
+// Pack element: 8 time samples of one component of one site, in pieces of 16
+// bytes.  Split precisions: 8 hi halves, then 8 lo halves.  FP32: 4 + 4 floats.
 struct alignas(16) Chunk {
     uint4 x, y;
 };
-// 48-byte pack element of the three-piece BF16 form: 8 hi, 8 mid, 8 lo.
+// Three-piece BF16 form: 8 hi, 8 mid, 8 lo.
 struct alignas(16) Chunk3 {
     uint4 x, y, z;
 };
 template <int PREC>
 using PackElem = typename std::conditional<PREC == SDC_PREC_BF16X3, Chunk3, Chunk>::type;
+
+// The packs of the two-piece splits hold a plane of hi and a plane of lo
+// halves: the pass over the hi halves alone then fetches no lo halves in its
+// cache lines.  The other forms multiply all pieces of an element at once and
+// keep them side by side.  Fused time side by side / in planes: BF16 sc 36^3 x
+// 500 origins 1028 / 1018 ms, sc 30^3 x 100 origins 124.6 / 120.6, ball of
+// 20011 sites 53.1 / 52.6; FP32 sc 21x20x19 20.9 / 21.3, BF16x3 sq 90x90
+// 8.10 / 8.20.
+__host__ __device__ constexpr bool pack_planes(int prec) {
+    return prec == SDC_PREC_SPLIT_BF16 || prec == SDC_PREC_SPLIT_FP16;
+}
+// What a pack's index counts: pieces of a plane, or elements.
+template <int PREC>
+using PackUnit = typename std::conditional<pack_planes(PREC), uint4, PackElem<PREC>>::type;
+// Pieces per plane of the A and the B pack.
+template <class Args>
+__device__ __forceinline__ int64_t pack_plane_a(const Args& a) {
+    return ((int64_t)3 * a.O8 + 1) * a.n_pad;
+}
+template <class Args>
+__device__ __forceinline__ int64_t pack_plane_b(const Args& a) {
+    return (int64_t)a.n_phase * 3 * a.F8 * a.n_pad;
+}
 
 __device__ inline uint32_t bf16_bits(float v) {
     __bf16 b = (__bf16)v;  // round to nearest even

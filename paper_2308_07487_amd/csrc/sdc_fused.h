@@ -338,7 +338,7 @@ __device__ __forceinline__ void pair_loop(const TaskCtx& c) {
     const int lane = threadIdx.x & 63;
     const int wi = c.quadrant >> 1, wj = c.quadrant & 1, h = lane >> 5, l32 = lane & 31;
 
-    using Elem = PackElem<PREC>;
+    using Elem = PackUnit<PREC>;
     const Elem* Ab = (const Elem*)a.A;
     const Elem* Bb = (const Elem*)a.B + (int64_t)grp.phase * a.phase_stride;
     // K-steps run over the 3 O8 origin blocks of all components, two blocks
@@ -400,9 +400,19 @@ __device__ __forceinline__ void pair_loop(const TaskCtx& c) {
                 // offB holds one block for the upper half; it needs b1 - b0
                 ob += h ? (uint32_t)((int64_t)(b1 - b0 - 1) * np * (int64_t)sizeof(Elem)) : 0u;
             }
-            b.a = *(const Elem*)((const char*)pa + offA);
+            if constexpr (pack_planes(PREC)) {
+                b.a.x = *(const Elem*)((const char*)pa + offA);
+                b.a.y = *(const Elem*)((const char*)(pa + pack_plane_a(a)) + offA);
 #pragma unroll
-            for (int q = 0; q < NB; ++q) b.b[q] = *(const Elem*)((const char*)(pb + q * np) + ob);
+                for (int q = 0; q < NB; ++q) {
+                    b.b[q].x = *(const Elem*)((const char*)(pb + q * np) + ob);
+                    b.b[q].y = *(const Elem*)((const char*)(pb + q * np + pack_plane_b(a)) + ob);
+                }
+            } else {
+                b.a = *(const PackElem<PREC>*)((const char*)pa + offA);
+#pragma unroll
+                for (int q = 0; q < NB; ++q) b.b[q] = *(const PackElem<PREC>*)((const char*)(pb + q * np) + ob);
+            }
         };
 
         // Epilogue: bin of each accumulator element, LDS FP64 add per lag.

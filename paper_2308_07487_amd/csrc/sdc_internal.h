@@ -269,8 +269,8 @@ struct PackArgs {
     int n_phase;          // = stride
     int64_t frames_valid; // frames usable: min(n_frames, required)
     const float* mean;    // [n][4] per-site origin averages subtracted from A, or null
-    void* A;              // [3][O8][n_pad] x 32 B
-    void* B;              // [n_phase][3][F8][n_pad] x 32 B
+    void* A;              // [3 O8 + 1][n_pad] elements, or as many pieces per plane
+    void* B;              // [n_phase][3][F8][n_pad], likewise
     double* mframe;       // [n_sums][3]: site-summed spin of the first n_sums frames
     int64_t n_sums;
 };
@@ -282,7 +282,8 @@ struct FusedArgs {
     int64_t n_pad;
     int O8, F8;                    // origin blocks per component (A), window blocks (B)
     int nk;                        // K-steps: ceil(3 O8 / 2)
-    int64_t phase_stride;          // elements of 32 B per B phase
+    int n_phase;                   // B phases (the origin stride)
+    int64_t phase_stride;          // pieces (of a plane) or elements per B phase
     const KPair* pairs;
     const KStream* streams;
     int n_streams;

@@ -134,19 +134,29 @@ __global__ __launch_bounds__(256) void pack_kernel(PackArgs a) {
             v[2][e] -= a.mean[4 * orig + 2];
         }
     }
-    PackElem<PREC>* dst;
-    int64_t comp_stride;
+    PackUnit<PREC>* dst;
+    int64_t comp_stride, plane;
     if (isA) {
-        dst = (PackElem<PREC>*)a.A + (int64_t)row * a.n_pad + p;
+        dst = (PackUnit<PREC>*)a.A + (int64_t)row * a.n_pad + p;
         comp_stride = (int64_t)a.O8 * a.n_pad;
+        plane = pack_plane_a(a);
     } else {
         const int r = row - a.O8;
         const int ph = r / a.F8;
-        dst = (PackElem<PREC>*)a.B + ((int64_t)ph * 3 * a.F8 + (r % a.F8)) * a.n_pad + p;
+        dst = (PackUnit<PREC>*)a.B + ((int64_t)ph * 3 * a.F8 + (r % a.F8)) * a.n_pad + p;
         comp_stride = (int64_t)a.F8 * a.n_pad;
+        plane = pack_plane_b(a);
     }
 #pragma unroll
-    for (int c = 0; c < 3; ++c) dst[c * comp_stride] = make_chunk<PREC>(v[c]);
+    for (int c = 0; c < 3; ++c) {
+        const PackElem<PREC> e = make_chunk<PREC>(v[c]);
+        if constexpr (pack_planes(PREC)) {
+            dst[c * comp_stride] = e.x;
+            dst[c * comp_stride + plane] = e.y;
+        } else {
+            dst[c * comp_stride] = e;
+        }
+    }
 }
 
 int launch_pack(const PackArgs& a, void* stream) {
