@@ -236,6 +236,8 @@ sdc_status fused_args(const sdc_plan* p, const LagSel& sel, sdc::FusedArgs* a) {
     a->O8 = p->O8;
     a->F8 = p->F8;
     a->nk = p->nk;
+    // an odd block count leaves the last K-step one component's last origins
+    a->tail = p->O8 % 2 ? p->corr.n_origins - (p->O8 - 1) * sdc::kOriginBlock : sdc::kOriginBlock;
     a->n_phase = p->corr.origin_stride;
     a->phase_stride = (int64_t)3 * p->F8 * L.n_pad;
     a->pairs = p->d_pairs;

@@ -169,6 +169,17 @@ __device__ inline void f32_all(const float (&a)[8], const float (&w)[NF], f32x16
                                std::integer_sequence<int, Qs...>) {
     (f32_q<Qs, OFF, NF, LW>(a, w, acc, std::make_integer_sequence<int, LW>{}), ...);
 }
+// The first nq (uniform) of them; the operands move down a register per turn.
+template <int OFF, int NF, int LW>
+__device__ inline void f32_first(int nq, float (&a)[8], float (&w)[NF], f32x16 (&acc)[LW]) {
+    for (int q = 0; q < nq; ++q) {
+        f32_q<0, OFF, NF, LW>(a, w, acc, std::make_integer_sequence<int, LW>{});
+#pragma unroll
+        for (int e = 0; e < 7; ++e) a[e] = a[e + 1];
+#pragma unroll
+        for (int e = 0; e < NF - 1; ++e) w[e] = w[e + 1];
+    }
+}
 
 // Accumulators of one wave: LW 32x32 tiles, and for the schedules that
 // keep them apart a second set for the small products of the reduced forms.
@@ -187,7 +198,7 @@ struct Stage {
 };
 
 template <int PREC, int PASS, int SCHED, int NB, int LW, int OFF>
-__device__ inline void stage_mma(const Stage<PREC, NB>& s, Acc<PREC, SCHED, LW>& ac) {
+__device__ inline void stage_mma(const Stage<PREC, NB>& s, Acc<PREC, SCHED, LW>& ac, int nq = 8) {
     f32x16 (&acc)[LW] = ac.v;
     constexpr int NW = 4 * NB;
     if constexpr (PREC == SDC_PREC_BF16X3) {
@@ -220,7 +231,10 @@ __device__ inline void stage_mma(const Stage<PREC, NB>& s, Acc<PREC, SCHED, LW>&
 #pragma unroll
             for (int e = 0; e < 8; ++e) w[8 * k + e] = __uint_as_float(r[e]);
         }
-        f32_all<OFF, 8 * NB, LW>(af, w, acc, std::make_integer_sequence<int, 8>{});
+        if (__builtin_constant_p(nq) && nq == 8)
+            f32_all<OFF, 8 * NB, LW>(af, w, acc, std::make_integer_sequence<int, 8>{});
+        else
+            f32_first<OFF, 8 * NB, LW>(nq, af, w, acc);
     } else {
         uint32_t wh[NW], wl[NW];
 #pragma unroll
@@ -279,15 +293,23 @@ __device__ __forceinline__ void interleave() {
 // scheduling region, and the fewer than NS steps left after it (loaded
 // already) follow; the others skip the steps past the end inside the loop
 // and fence the loads off from the MFMAs.
+// FP32, one-pass: the samples of the last step past `tail` are zero in both
+// lane halves (a component's last origins and the zero block) and are left
+// out: a sum is the same without a zero product.  The steps after the loop
+// share one short body for it.  Fused ms before / after: sc 21x20x19 x 100
+// lags, 50 origins (2 of the last step's 8) 21.0 / 19.9; 64 origins, where it
+// is the short body alone, sc 30^3 x 128 lags 290 / 283, 24^3 x 40 25.4 / 24.7
+// (lag-split had it cost 4% at the first of these and keeps its own steps).
 template <int PREC, int PASS, int SCHED, int NB, int LW, int OFF, int NS, class Load>
-__device__ __forceinline__ void k_loop(int nk, const Load& load, Acc<PREC, SCHED, LW>& acc) {
+__device__ __forceinline__ void k_loop(int nk, int tail, const Load& load, Acc<PREC, SCHED, LW>& acc) {
     Stage<PREC, NB> s[NS];
 #pragma unroll
     for (int j = 0; j < NS - 1; ++j) load(s[j], j);
     if constexpr (SCHED == kSchedOnePass || SCHED == kSchedLagSplit) {
         constexpr int NMF = mfma_per_stage<PREC, PASS, LW>();
+        constexpr bool TAIL = PREC == SDC_PREC_FP32 && SCHED == kSchedOnePass;  // the loop leaves the last step
         int kk = 0;
-        for (; kk + NS <= nk; kk += NS) {
+        for (; kk + NS + TAIL <= nk; kk += NS) {
 #pragma unroll
             for (int j = 0; j < NS; ++j) {
                 load(s[(j + NS - 1) % NS], kk + j + NS - 1);
@@ -296,9 +318,16 @@ __device__ __forceinline__ void k_loop(int nk, const Load& load, Acc<PREC, SCHED
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
+        if constexpr (TAIL) {
+            load(s[NS - 1], kk + NS - 1);
 #pragma unroll
-        for (int j = 0; j < NS - 1; ++j)
-            if (kk + j < nk) stage_mma<PREC, PASS, SCHED, NB, LW, OFF>(s[j], acc);
+            for (int j = 0; j < NS; ++j)
+                if (kk + j < nk) stage_mma<PREC, PASS, SCHED, NB, LW, OFF>(s[j], acc, kk + j + 1 < nk ? 8 : tail);
+        } else {
+#pragma unroll
+            for (int j = 0; j < NS - 1; ++j)
+                if (kk + j < nk) stage_mma<PREC, PASS, SCHED, NB, LW, OFF>(s[j], acc);
+        }
     } else {
         for (int kk = 0; kk < nk; kk += NS) {
 #pragma unroll
@@ -483,14 +512,14 @@ __device__ __forceinline__ void pair_loop(const TaskCtx& c) {
         if constexpr (TWO) {
             // small products first, while the sums are still small, then the
             // large ones on top (see the pass constants)
-            k_loop<PREC, kPassSmall, SCHED, NB, LW, OFF, kStagesTwoPassSmall>(nk, load, acc);
-            k_loop<PREC, kPassLarge, SCHED, NB, LW, OFF, kStagesTwoPassLarge>(nk, load, acc);
+            k_loop<PREC, kPassSmall, SCHED, NB, LW, OFF, kStagesTwoPassSmall>(nk, a.tail, load, acc);
+            k_loop<PREC, kPassLarge, SCHED, NB, LW, OFF, kStagesTwoPassLarge>(nk, a.tail, load, acc);
             epilogue(std::false_type{});
         } else if constexpr (FOLD) {
-            k_loop<PREC, kPassFold, SCHED, NB, LW, OFF, kStagesFold>(nk, load, acc);
+            k_loop<PREC, kPassFold, SCHED, NB, LW, OFF, kStagesFold>(nk, a.tail, load, acc);
             epilogue(std::false_type{});
         } else {
-            k_loop<PREC, kPassAll, SCHED, NB, LW, OFF, kStagesOnePass>(nk, load, acc);
+            k_loop<PREC, kPassAll, SCHED, NB, LW, OFF, kStagesOnePass>(nk, a.tail, load, acc);
             epilogue(std::integral_constant<bool, PREC != SDC_PREC_FP32>{});
         }
     }

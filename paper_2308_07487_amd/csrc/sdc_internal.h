@@ -13,25 +13,29 @@ namespace sdc {
 // Sites are grouped in tiles of 64.  Periodic lattices: a tile is a brick of
 // at most 64 cells of one sublattice, slot (o0 s1 + o1) s2 + o2, or, where
 // bricks would leave more tiles, 64 consecutive cells in box order (see
-// choose_layout).  Radial: 64 consecutive points in Morton order.  Unused
+// layout_linear).  Radial: 64 consecutive points in Morton order.  Unused
 // slots are padding (zero spins, no counts).
 constexpr int kTile = 64;
 // Lags handled together by one fused task (consecutive lag indices u): 8
 // for the reduced-precision forms (128 accumulator registers per wave for
-// one set of sums), 16 for FP32 (its MFMA is 16x slower per flop, so operand
-// reuse across more lags matters more than overlap).
+// one set of sums), 16 for FP32: its MFMAs cover one workgroup's loads by
+// themselves, and 8-lag groups in two workgroups per CU, which hide the
+// epilogue, read three times the operands (fused ms with 16 / 8: sc 30^3 x 64
+// origins x 128 lags 290 / 404, sq 100x100 31.7 / 35.1, sc 21x20x19 with
+// stride 2, where 16 pads more, 21.0 / 19.4).
 constexpr int lag_group(int precision) { return precision == SDC_PREC_FP32 ? 16 : 8; }
 // Doubles between the LDS histogram rows of two bins: the group's lags side
 // by side, so that the adds of an element's lags take constant offsets from
 // one address (with a row per lag each add needs an address of its own), and
 // an odd pitch, so that neighbouring bins lie in different banks.  A window
 // has at most 512 bins (2 s_a per axis for bricks of s_0 s_1 s_2 <= 64
-// cells, 508 for tiles in box order), a radial one 1024: 78 KB for 8-lag groups, two of which fit in a
-// CU's LDS, and 143 KB for FP32's 16.  Together with the separate loop of
+// cells, 508 for tiles in box order), a radial one 1024: 78 KB for 8-lag
+// groups, two of which fit in a CU's LDS, and 143 KB for FP32's 16.  Together with the separate loop of
 // the deterministic mode (one basic block of adds instead of one block per
 // element) this took the fused launch from 1093 to 1081 ms at sc 36^3
 // split-BF16, 58.8 to 57.3 ms on 20 011 points in 1024 shells, 30.8 to 28.2
-// ms for FP32 at sc 21x20x19 and 9.0 to 8.5 ms for BF16x3 at 90x90.
+// ms for FP32 at sc 21x20x19 and 9.0 to 8.5 ms for BF16x3 at 90x90 (each
+// before the box-order tiles and the plane-wise packs).
 constexpr int hist_pitch(int precision) { return lag_group(precision) + 1; }
 // Schedules of the fused product (a tuning choice per plan and batch; the
 // results differ only by rounding).  The small products of the reduced forms
@@ -304,6 +308,7 @@ struct FusedArgs {
     int stride;
     int precision;
     int sched;                     // kSchedOnePass / kSchedTwoPass
+    int tail;                      // samples of the last K-step with an origin in either lane half
 };
 int launch_fused(const FusedArgs& a, void* stream);
 

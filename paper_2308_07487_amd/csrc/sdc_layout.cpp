@@ -267,7 +267,8 @@ void layout_bricks(int64_t n, int nsub, const int nb[3], const std::vector<int32
 // window of 508 bins.  Fused launch with bricks only / this rule: bcc 13x14x15
 // (98 / 86 tiles) 7.2 / 5.7 ms, bcc 9x10x11 with stride 3 0.77 / 0.40 ms, sc 30^3
 // x 100 lags 147 / 122 ms, ten samples of edges 10 to 22 in one batch 290 / 218
-// ms, 90 x 90 (130 / 127 tiles) 8.3 / 8.1 ms, 200 x 200 102 / 101 ms.
+// ms, 90 x 90 (130 / 127 tiles) 8.3 / 8.1 ms, 200 x 200 102 / 101 ms (before
+// the split packs' planes, which take another 1 to 3%).
 sdc_status build_periodic(const float* pos, int64_t n, const sdc_bin_spec* spec, int seg, Layout* lay,
                           std::string* err) {
     const bool bcc = spec->kind == SDC_BINS_PERIODIC_BCC;
@@ -387,7 +388,7 @@ void split_streams(Layout* lay, int seg) {
 // of the least ceil(tasks / slots) (length + 1).  Fused launch, whole streams
 // or 96-pair segments against the length chosen: sc 8^3 x 64 lags 69 -> 30 us
 // (1 pair), sc 12^3 x 70 lags 283 -> 190 us (14), bcc 13x14x15 x 130 lags 7.63
-// -> 7.15 ms (18), 3001 points x 100 lags 1.27 -> 0.89 ms (7), 20 011 points x
+// -> 7.15 ms (18; with bricks), 3001 points x 100 lags 1.27 -> 0.89 ms (7), 20 011 points x
 // 128 lags 58.0 -> 56.1 ms (55).  Never above 32 pairs (radial 64): over
 // longer ones the lag groups lose step and their operand re-reads miss L2
 // (periodic samples of 25 000 to 100 000 sites with 32 pairs are up to 4%
