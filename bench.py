@@ -657,7 +657,7 @@ def run_mc(args, wl, torch, sdc):
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": 8000.0, "unit": "GB/s",
                      "frac": achieved / 8000.0, "traffic": traffic,
                      "kernel": "mc_colour_kernel<%d> (%s sweeps; 2 classes x 20 sweeps per step, with the "
-                               "one-wave cone kernel after each sweep inside the timed loop)"
+                               "cone adapted by the last workgroup of each sweep)"
                                % (int(stencil), "lattice-stencil" if stencil else "bond-table"),
                      "sweeps_ms_per_step": s_ms, "bytes_per_update": per_update,
                      "traffic_scope": "HBM bytes per step (40 colour-class launches)"},
