@@ -520,7 +520,7 @@ struct McArgs {
     uint64_t seed;             // Philox key of the moves
     double acc_target;         // acceptance-rate target of the cone adaptation
     double* S;                 // [n slots][3] FP64 state
-    double* cone;              // [2]: cone half-angle, its cosine
+    double* cone;              // [2][2]: cone half-angle and its cosine before even and odd sweeps
     unsigned long long* accepted;  // accepted moves of the current sweep (mc_counter_bytes())
     // Lattice stencil (set only when the host has checked that it reproduces
     // the tables above slot for slot): periodic sc box L0 x L1 x L2, every edge
@@ -560,8 +560,10 @@ int launch_mc_setup(const McArgs& a, const float* init, double cone0, void* stre
 // (history[sweep] receives the accepted moves when history is not null).
 int launch_mc_sweep(const McArgs& a, const int64_t* class_start, int n_classes, double T, int64_t sweep,
                     long long* history, void* stream);
-// Energy per site, final cone and temperature into info[0..2]; state as fp32.
-int launch_mc_finish(const McArgs& a, double* partial, double T_last, float* out, double* info, void* stream);
+// Energy per site, cone after n_sweeps sweeps and temperature into
+// info[0..2]; state as fp32.
+int launch_mc_finish(const McArgs& a, double* partial, int64_t n_sweeps, double T_last, float* out, double* info,
+                     void* stream);
 
 int fused_lds_bytes(int win, int precision);
 // Largest dynamic LDS of a fused launch (the CU's 160 KB less room for the

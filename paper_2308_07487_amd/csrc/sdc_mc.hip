@@ -28,7 +28,10 @@ constexpr double kPi = 3.14159265358979323846;
 // workgroups' atomics do not all queue on one address.  The workgroups of a
 // sweep's last class also count themselves in the bits from kMcTicketBit on
 // (a sweep accepts at most 2^26 moves); the one that completes its counter
-// takes a ticket of the line after the counters.
+// adds what it counted, and a ticket, to the line after the counters.  The
+// counts thus travel in the values of the atomics alone, and no order between
+// different addresses is assumed (a fence per workgroup would write back its
+// L2: 280 us against 22 where the energy sum did it).
 constexpr int kMcCounters = 64;
 constexpr int kMcCounterStride = 16;  // u64 words between counters
 constexpr int kMcTicketBit = 40;
@@ -215,6 +218,9 @@ __device__ inline bool mc_move(const McArgs& a, int64_t i, int64_t sweep, double
     return true;
 }
 
+// Cone half-angle and its cosine before a sweep.
+__device__ inline double* mc_cone(const McArgs& a, int64_t sweep) { return a.cone + 2 * (sweep & 1); }
+
 // The cone after a sweep with the given number of accepted moves.
 __device__ inline double next_cone(const McArgs& a, double c, unsigned long long acc) {
     const double rate = (double)acc / (double)a.n;
@@ -223,22 +229,40 @@ __device__ inline double next_cone(const McArgs& a, double c, unsigned long long
     return c;
 }
 
-// Last workgroup of a sweep (one wave): gather the counters, clear them,
-// record the accepted moves, adapt the cone.
-__device__ inline void mc_end_sweep(const McArgs& a, long long* history, int64_t sweep) {
-    const int t = threadIdx.x;  // < 64 = kMcCounters
-    unsigned long long acc = __hip_atomic_load(a.accepted + t * kMcCounterStride, __ATOMIC_RELAXED,
-                                               __HIP_MEMORY_SCOPE_AGENT) &
-                             ((1ull << kMcTicketBit) - 1);
-    a.accepted[t * kMcCounterStride] = 0ull;
-    if (t == 0) a.accepted[kMcTickets] = 0ull;
+// End of the sweep's last class for one workgroup, by its first wave: `sum` (of
+// lane 0) accepted moves.  The workgroup that takes the last ticket records
+// the sweep's moves and adapts the cone.  The cone before sweep v is in pair
+// v mod 2, so the update is to words that this sweep's workgroups do not read.
+__device__ inline void mc_end_sweep(const McArgs& a, unsigned long long sum, long long* history, int64_t sweep) {
+    constexpr unsigned long long kOne = 1ull << kMcTicketBit;
+    const uint32_t nb = gridDim.x, line = blockIdx.x % kMcCounters;
+    if (nb < kMcCounters) {
+        // counters past this class's workgroups, from the launches before:
+        // every workgroup completes a counter and takes its share of them
+        unsigned long long rest = 0ull;
+        if (threadIdx.x >= nb && threadIdx.x % nb == blockIdx.x) {
+            rest = a.accepted[threadIdx.x * kMcCounterStride];
+            a.accepted[threadIdx.x * kMcCounterStride] = 0ull;
+        }
 #pragma unroll
-    for (int w = 32; w > 0; w >>= 1) acc += __shfl_down(acc, w);
-    if (t != 0) return;
-    if (history) history[sweep] = (long long)acc;
-    const double c = next_cone(a, a.cone[0], acc);
-    a.cone[0] = c;
-    a.cone[1] = cos(c);
+        for (int w = 32; w > 0; w >>= 1) rest += __shfl_down(rest, w);
+        sum += rest;
+    }
+    if (threadIdx.x != 0) return;
+    // adds to a word (after its `total` adds cleared) and tells whether all are in
+    auto add = [](unsigned long long* word, unsigned long long& v, uint32_t total) {
+        v = atomicAdd(word, v + kOne) + v + kOne;
+        if ((v >> kMcTicketBit) != total) return false;
+        v &= kOne - 1;
+        __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return true;
+    };
+    if (!add(a.accepted + line * kMcCounterStride, sum, (nb - line + kMcCounters - 1) / kMcCounters)) return;
+    if (!add(a.accepted + kMcTickets, sum, nb < kMcCounters ? nb : kMcCounters)) return;
+    if (history) history[sweep] = (long long)sum;
+    const double c = next_cone(a, mc_cone(a, sweep)[0], sum);
+    mc_cone(a, sweep + 1)[0] = c;
+    mc_cone(a, sweep + 1)[1] = cos(c);
 }
 
 // One colour class of one sweep, one thread per site.  Bound: FP64 vector
@@ -269,7 +293,7 @@ __global__ __launch_bounds__(256) void mc_colour_kernel(McArgs a, int64_t k0, in
         double* si = a.S + 3 * k;
         double s[3] = {si[0], si[1], si[2]}, w[3];
         mc_field_of<STENCIL, Z>(a, a.S, cls, cell, k, w);
-        accepted = mc_move(a, STENCIL ? cell.site : a.site_of[k], sweep, T, a.cone[1], w, s);
+        accepted = mc_move(a, STENCIL ? cell.site : a.site_of[k], sweep, T, mc_cone(a, sweep)[1], w, s);
         if (accepted) {
             si[0] = s[0];
             si[1] = s[1];
@@ -277,28 +301,15 @@ __global__ __launch_bounds__(256) void mc_colour_kernel(McArgs a, int64_t k0, in
         }
     }
     __shared__ unsigned int wave_acc[4];
-    __shared__ int ends;
     const unsigned long long ball = __ballot(accepted);
     if ((threadIdx.x & 63) == 0) wave_acc[threadIdx.x >> 6] = (unsigned int)__popcll(ball);
     __syncthreads();
-    if (threadIdx.x == 0) {
-        const unsigned long long sum = (unsigned long long)wave_acc[0] + wave_acc[1] + wave_acc[2] + wave_acc[3];
-        const uint32_t line = blockIdx.x % kMcCounters;
-        int e = 0;
-        if (!last) {
-            if (sum) atomicAdd(a.accepted + line * kMcCounterStride, sum);
-        } else {
-            const unsigned long long old = atomicAdd(a.accepted + line * kMcCounterStride, sum + (1ull << kMcTicketBit));
-            if ((old >> kMcTicketBit) + 1 == (nb - line + kMcCounters - 1) / kMcCounters) {
-                const uint32_t lines = nb < kMcCounters ? nb : kMcCounters;
-                e = atomicAdd(a.accepted + kMcTickets, 1ull) + 1 == lines;
-            }
-        }
-        ends = e;
-    }
-    if (!last) return;
-    __syncthreads();
-    if (ends && threadIdx.x < kMcCounters) mc_end_sweep(a, history, sweep);
+    if (threadIdx.x >= 64) return;
+    const unsigned long long sum = (unsigned long long)wave_acc[0] + wave_acc[1] + wave_acc[2] + wave_acc[3];
+    if (last)
+        mc_end_sweep(a, sum, history, sweep);
+    else if (threadIdx.x == 0 && sum)
+        atomicAdd(a.accepted + (blockIdx.x % kMcCounters) * kMcCounterStride, sum);
 }
 
 // `count` sweeps of a small sample by one workgroup, the state in LDS.  Bound:
@@ -315,7 +326,7 @@ __global__ __launch_bounds__(kMcSmallThreads) void mc_small_kernel(McArgs a, McS
     __shared__ unsigned int acc[2];
     const int tid = threadIdx.x;
     for (int x = tid; x < 3 * (int)a.n; x += kMcSmallThreads) S[x] = a.S[x];
-    double T = m.T, cone = a.cone[0], cos_cone = a.cone[1];
+    double T = m.T, cone = mc_cone(a, m.sweep)[0], cos_cone = mc_cone(a, m.sweep)[1];
     int64_t done = m.done;
     if (tid < 2) acc[tid] = 0;
     __syncthreads();
@@ -355,8 +366,8 @@ __global__ __launch_bounds__(kMcSmallThreads) void mc_small_kernel(McArgs a, McS
     }
     for (int x = tid; x < 3 * (int)a.n; x += kMcSmallThreads) a.S[x] = S[x];
     if (tid == 0) {
-        a.cone[0] = cone;
-        a.cone[1] = cos_cone;
+        mc_cone(a, m.sweep + m.count)[0] = cone;
+        mc_cone(a, m.sweep + m.count)[1] = cos_cone;
     }
 }
 
@@ -366,8 +377,8 @@ __global__ __launch_bounds__(256) void mc_setup_kernel(McArgs a, const float* __
         if (threadIdx.x < kMcCounters) a.accepted[threadIdx.x * kMcCounterStride] = 0ull;
         if (threadIdx.x == 0) {
             a.accepted[kMcTickets] = 0ull;
-            a.cone[0] = cone0;
-            a.cone[1] = cos(cone0);
+            mc_cone(a, 0)[0] = cone0;
+            mc_cone(a, 0)[1] = cos(cone0);
         }
     }
     if (!init) return;
@@ -417,14 +428,14 @@ __global__ __launch_bounds__(256) void mc_finish_kernel(McArgs a, double* __rest
 // t + 256, ... in order, then a fixed tree, the same result on every run),
 // cone, last temperature.
 __global__ __launch_bounds__(256) void mc_info_kernel(McArgs a, const double* __restrict__ partial, int n_partial,
-                                                      double T_last, double* __restrict__ info) {
+                                                      int64_t n_sweeps, double T_last, double* __restrict__ info) {
     __shared__ double red[256];
     double e = 0.0;
     for (int b = threadIdx.x; b < n_partial; b += 256) e += partial[b];
     e = mc_block_sum(e, red);
     if (threadIdx.x != 0) return;
     info[0] = e / (double)a.n;
-    info[1] = a.cone[0];
+    info[1] = mc_cone(a, n_sweeps)[0];
     info[2] = T_last;
 }
 
@@ -494,13 +505,14 @@ int launch_mc_small(const McArgs& a, const McSmall& m, long long* history, void*
     return (int)hipGetLastError();
 }
 
-int launch_mc_finish(const McArgs& a, double* partial, double T_last, float* out, double* info, void* stream) {
+int launch_mc_finish(const McArgs& a, double* partial, int64_t n_sweeps, double T_last, float* out, double* info,
+                     void* stream) {
     mc_dispatch(a, [&](auto stencil, auto z) {
         hipLaunchKernelGGL((mc_finish_kernel<decltype(stencil)::value, decltype(z)::value>), dim3(grid_of(a.n)),
                            dim3(256), 0, (hipStream_t)stream, a, partial, out);
     });
     hipLaunchKernelGGL(mc_info_kernel, dim3(1), dim3(256), 0, (hipStream_t)stream, a, (const double*)partial,
-                       (int)grid_of(a.n), T_last, info);
+                       (int)grid_of(a.n), n_sweeps, T_last, info);
     return (int)hipGetLastError();
 }
 

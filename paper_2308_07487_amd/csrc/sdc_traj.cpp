@@ -543,7 +543,7 @@ extern "C" sdc_status sdc_mc_create(const float* positions_host, int64_t n_sites
         const bool ok = mc_alloc(m, (void**)&d_nbr, b.nbr.size() * 4) && mc_alloc(m, (void**)&d_j, b.jv.size() * 4) &&
                         (b.dv.empty() || mc_alloc(m, (void**)&d_dv, b.dv.size() * 4)) &&
                         mc_alloc(m, (void**)&d_order, (size_t)n_sites * 4) &&
-                        mc_alloc(m, (void**)&d_S, (size_t)n_sites * 24) && mc_alloc(m, (void**)&d_cone, 16) &&
+                        mc_alloc(m, (void**)&d_S, (size_t)n_sites * 24) && mc_alloc(m, (void**)&d_cone, 32) &&
                         mc_alloc(m, (void**)&d_acc, sdc::mc_counter_bytes()) && mc_alloc(m, (void**)&m->d_partial, (size_t)n_part * 8) &&
                         mc_alloc(m, (void**)&m->d_info, 24);
         if (!ok) {
@@ -647,7 +647,7 @@ extern "C" sdc_status sdc_mc_run(sdc_mc* m, const sdc_mc_spec* schedule, const f
         });
     }
     if (le == 0) le = (int)hipEventRecord(m->ev[1], hs);
-    if (le == 0) le = sdc::launch_mc_finish(ma, m->d_partial, T_last, state_dev, m->d_info, stream);
+    if (le == 0) le = sdc::launch_mc_finish(ma, m->d_partial, n_sweeps, T_last, state_dev, m->d_info, stream);
     if (le != 0) return sdc::set_error(SDC_ERR_HIP, hipGetErrorString((hipError_t)le));
     m->loaded = true;
     m->timed = true;
