@@ -1,0 +1,71 @@
+"""RK4 steps of boxes with axes short enough for one brick to span, whose bonds
+wrap inside the tile: edges of two (both bonds to the same neighbour), three and
+up to 16 cells beside long ones, boxes that one brick holds; and other bond
+counts of the table stages, which load four bonds at a time."""
+import time
+
+import numpy as np
+import pytest
+
+from paper_2308_07487_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+def _both(S, torch, L, T, D, seed=3):
+    """The frames in box order (bricks) and from the same sites permuted (tables)."""
+    pos = inputs.sc_positions(L)
+    n = pos.shape[0]
+    kw = dict(cells=L, J=-1.0, dt=0.02, D=D, A=0.2, Hz=0.3, init=S.INIT_GIVEN)
+    init = inputs.random_unit_frames(1, n, seed=seed)[0]
+    perm = np.random.default_rng(5).permutation(n)
+    a, b = torch.empty(T, n, 3, device="cuda"), torch.empty(T, n, 3, device="cuda")
+    x, y = torch.from_numpy(init).cuda(), torch.from_numpy(init[perm]).cuda()
+    return (lambda: S.traj_generate(pos, S.BINS_SC, a, init_state=x, **kw), a,
+            lambda: S.traj_generate(pos[perm], S.BINS_SC, b, init_state=y, **kw), b, perm)
+
+
+@pytest.mark.parametrize("D", [0.0, 0.4])
+@pytest.mark.parametrize("L", [(40, 2, 2), (2, 90, 3), (3, 50, 41), (17, 16, 16), (16, 15, 14), (2, 2, 600), (1, 16, 300),
+                               (5, 4, 3), (18, 1, 1), (16, 17, 18)])
+def test_spanned_axes_equal_table_stages(L, D):
+    """The same expressions per site in the same order; the compiler may contract
+    a product and a sum differently: one fp32 rounding (2^-24) per stage of the
+    12 steps, on unit spins."""
+    import torch
+    from paper_2308_07487_amd import sdc as S
+    print(f"[case] rk4 spanned {L} D={D}", flush=True)
+    run_a, a, run_b, b, perm = _both(S, torch, L, 13, D)
+    run_a()
+    run_b()
+    back = np.empty_like(a.cpu().numpy())
+    back[:, perm] = b.cpu().numpy()
+    assert np.abs(a.cpu().numpy() - back).max() <= 12 * 4 * 2.0 ** -24
+
+
+def test_thin_box_is_not_slower_than_its_tables():
+    """40 000 x 2 x 2 cells: a halo of four cells on the edges of two made the
+    step 25 times the sites' own work and 2.5 times the table launches' time."""
+    import torch
+    from paper_2308_07487_amd import sdc as S
+    print("[case] rk4 thin box times", flush=True)
+
+    def step(run_of):
+        t = []
+        for T in (1, 101):
+            run = run_of(T)
+            run()
+            best = 1e9
+            for _ in range(4):
+                torch.cuda.synchronize()
+                t0 = time.perf_counter()
+                run()
+                torch.cuda.synchronize()
+                best = min(best, time.perf_counter() - t0)
+            t.append(best)
+        return t[1] - t[0]
+
+    bricks = step(lambda T: _both(S, torch, (40000, 2, 2), T, 0.0)[0])
+    tables = step(lambda T: _both(S, torch, (40000, 2, 2), T, 0.0)[2])
+    print(f"  100 steps: bricks {bricks * 1e3:.2f} ms, tables {tables * 1e3:.2f} ms", flush=True)
+    assert bricks < tables
