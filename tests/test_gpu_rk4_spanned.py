@@ -69,3 +69,26 @@ def test_thin_box_is_not_slower_than_its_tables():
     tables = step(lambda T: _both(S, torch, (40000, 2, 2), T, 0.0)[2])
     print(f"  100 steps: bricks {bricks * 1e3:.2f} ms, tables {tables * 1e3:.2f} ms", flush=True)
     assert bricks < tables
+
+
+@pytest.mark.parametrize("n,r_cut", [(2, 9.0), (150, 0.9), (150, 1.6), (6, 9.0), (9, 9.0), (60, 9.0)])
+def test_table_stages_of_any_bond_count(orc, n, r_cut):
+    """1, 5, 8 and 59 bonds per site, and ragged counts, against the oracle."""
+    import torch
+    from paper_2308_07487_amd import sdc as S
+    print(f"[case] rk4 tables n={n} r_cut={r_cut}", flush=True)
+    pos = inputs.ball_positions(n, 2.0, seed=9)
+    d = (pos[None] - pos[:, None]).astype(np.float32)
+    d2 = (d[..., 0] * d[..., 0] + d[..., 1] * d[..., 1]) + d[..., 2] * d[..., 2]
+    hit = (d2 <= np.float32(r_cut) * np.float32(r_cut)) & ~np.eye(n, dtype=bool)
+    row = np.concatenate([[0], np.cumsum(hit.sum(1))]).astype(np.int64)
+    col = np.nonzero(hit)[1].astype(np.int32)
+    J = np.exp(-np.sqrt(d2[hit].astype(np.float64)))
+    u = d.astype(np.float64)[hit]
+    Dv = 0.3 * u / np.linalg.norm(u, axis=1, keepdims=True)
+    init = inputs.random_unit_frames(1, n, seed=9)[0]
+    ref = orc.ll_rk4(row, col, J, init, 0.01, 15, D=Dv, A=0.2, Hz=0.3)
+    fr = torch.empty(15, n, 3, device="cuda")
+    S.traj_generate(pos, S.BINS_RADIAL, fr, coupling=S.COUPLING_EXP_CUTOFF, r_cut=r_cut, J=1.0, dt=0.01,
+                    init=S.INIT_GIVEN, init_state=torch.from_numpy(init).cuda(), D=0.3, A=0.2, Hz=0.3)
+    np.testing.assert_allclose(fr.cpu().numpy(), ref, atol=5e-6)
