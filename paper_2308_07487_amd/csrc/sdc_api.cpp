@@ -488,7 +488,8 @@ sdc_status sdc_plan_create_tuned(const float* positions_host, int64_t n_sites, c
             std::vector<int> lags((size_t)corr->n_lags);
             for (int t = 0; t < corr->n_lags; ++t) lags[t] = t;
             const int n_groups = (int)make_groups(lags, corr->origin_stride, sdc::lag_group(corr->precision)).size();
-            sdc::split_streams(&p->lay, sdc::fitted_segment(p->lay, n_groups, slots, tu.segment_pairs));
+            const int seg = sdc::fitted_segment(p->lay, n_groups, slots, sdc::max_fused_tasks(sdc::sched_index(tu.schedule)));
+            sdc::split_streams(&p->lay, seg);
         } catch (const std::bad_alloc&) {
             delete p;
             return set_err(SDC_ERR_OOM, "host allocation failed");

@@ -395,29 +395,46 @@ void split_streams(Layout* lay, int seg) {
 // faster than with 96 and at most 3% slower than with their best of 16, 32
 // and 48; 65 536 points in 1024 shells take 588 ms with 64 and 600 ms with
 // 181 or whole streams).
-int fitted_segment(const Layout& lay, int n_groups, int64_t slots, int cap) {
-    cap = std::min(cap, lay.kind == SDC_BINS_RADIAL ? 64 : 32);
-    const double q = (double)lay.pairs.size() * n_groups / (double)slots;
-    if (q >= 32.0) return std::max(1, (int)std::min((double)cap, std::sqrt(q) + 0.5));
+int fitted_segment(const Layout& lay, int n_groups, int64_t slots, int64_t max_tasks) {
+    const bool radial = lay.kind == SDC_BINS_RADIAL;
+    const int cap = radial ? kFittedSegmentRadial : kFittedSegmentPeriodic;
+    int64_t pairs = 0;
     int longest = 1;
-    for (const KStream& s : lay.streams) longest = std::max(longest, s.p1 - s.p0);
-    longest = std::min(longest, cap);
-    int best = longest;
-    double best_cost = -1.0;
-    for (int seg = longest; seg >= 1; --seg) {
+    for (const KStream& s : lay.streams) {
+        pairs += s.p1 - s.p0;
+        longest = std::max(longest, s.p1 - s.p0);
+    }
+    // tasks per lag group and the longest segment at a length
+    auto cut = [&](int seg, int* len) {
         int64_t tasks = 0;
-        int len = 1;
+        int l = 1;
         for (const KStream& s : lay.streams) {
             const int n = s.p1 - s.p0, k = (n + seg - 1) / seg;
             tasks += k;
-            len = std::max(len, (n + k - 1) / k);
+            l = std::max(l, (n + k - 1) / k);
         }
-        const double cost = std::ceil((double)tasks * n_groups / (double)slots) * (len + 1);
-        if (best_cost < 0.0 || cost < best_cost) {
-            best_cost = cost;
-            best = seg;
+        if (len) *len = l;
+        return tasks;
+    };
+    const double q = (double)pairs * n_groups / (double)slots;
+    int best = std::min(longest, cap);
+    if (q >= 32.0) {
+        best = std::max(1, (int)std::min((double)cap, std::sqrt(q) + 0.5));
+    } else {
+        double best_cost = -1.0;
+        for (int seg = best; seg >= 1; --seg) {
+            int len;
+            const int64_t tasks = cut(seg, &len);
+            const double cost = std::ceil((double)tasks * n_groups / (double)slots) * (len + 1);
+            if (best_cost < 0.0 || cost < best_cost) {
+                best_cost = cost;
+                best = seg;
+            }
         }
     }
+    // a sample whose tasks would not fit one launch takes longer segments
+    const int limit = radial ? longest : std::min(longest, kLongestSegmentPeriodic);
+    while (best < limit && cut(best, nullptr) * n_groups > max_tasks) best = std::min(limit, best + std::max(1, best / 8));
     return best;
 }
 
