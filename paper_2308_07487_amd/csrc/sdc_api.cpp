@@ -1075,7 +1075,7 @@ sdc_status sdc_batch_create_tuned(sdc_plan* const* plans, int32_t n_plans, int32
         start[k + 1] = start[k] + (int64_t)args[k].n_groups * args[k].n_streams;
         lds = std::max(lds, sdc::fused_lds_bytes(args[k].win, prec));
     }
-    if (start[n_plans] > (int64_t)INT32_MAX / 2) {
+    if (start[n_plans] > sdc::kMaxBatchTasks) {
         delete b;
         return set_err(SDC_ERR_UNSUPPORTED, "too many fused tasks in the batch");
     }
@@ -1083,7 +1083,7 @@ sdc_status sdc_batch_create_tuned(sdc_plan* const* plans, int32_t n_plans, int32
     // lag groups of a stream segment in one queue).  Work of a stream's task:
     // its tile pairs times (K-steps + 4), the 4 standing for the per-pair
     // epilogue.
-    std::vector<int32_t> ranges(9, 0);
+    std::vector<int64_t> ranges(9, 0);
     {
         std::vector<int64_t> cut;     // task index at the end of every stream, in list order
         std::vector<double> cum;      // work up to there
@@ -1104,14 +1104,14 @@ sdc_status sdc_batch_create_tuned(sdc_plan* const* plans, int32_t n_plans, int32
             // the stream end nearest to the target, never before the previous cut
             int64_t r = c < cut.size() ? cut[c] : start[n_plans];
             if (c > 0 && c < cum.size() && target - cum[c - 1] < cum[c] - target) r = cut[c - 1];
-            ranges[x] = (int32_t)std::max<int64_t>(r, ranges[x - 1]);
+            ranges[x] = std::max(r, ranges[x - 1]);
         }
-        ranges[8] = (int32_t)start[n_plans];
+        ranges[8] = start[n_plans];
     }
     sdc::FusedArgs* d_args = nullptr;
     int64_t* d_start = nullptr;
     unsigned* d_queue = nullptr;
-    int32_t* d_ranges = nullptr;
+    int64_t* d_ranges = nullptr;
     sdc_status s = dalloc(&d_args, args.size(), &b->owned);
     if (s == SDC_OK) s = dalloc(&d_start, start.size(), &b->owned);
     if (s == SDC_OK) s = dalloc(&d_queue, 8, &b->owned);
@@ -1123,7 +1123,7 @@ sdc_status sdc_batch_create_tuned(sdc_plan* const* plans, int32_t n_plans, int32
     hipError_t he = hipMemcpy(d_args, args.data(), args.size() * sizeof(sdc::FusedArgs), hipMemcpyHostToDevice);
     if (he == hipSuccess)
         he = hipMemcpy(d_start, start.data(), start.size() * sizeof(int64_t), hipMemcpyHostToDevice);
-    if (he == hipSuccess) he = hipMemcpy(d_ranges, ranges.data(), 9 * sizeof(int32_t), hipMemcpyHostToDevice);
+    if (he == hipSuccess) he = hipMemcpy(d_ranges, ranges.data(), 9 * sizeof(int64_t), hipMemcpyHostToDevice);
     if (he != hipSuccess) {
         delete b;
         return hip_err((int)he, "upload batch tables");
@@ -1134,13 +1134,13 @@ sdc_status sdc_batch_create_tuned(sdc_plan* const* plans, int32_t n_plans, int32
     bl.n_plans = n_plans;
     bl.queue = d_queue;
     bl.ranges = d_ranges;
-    bl.total = (int)start[n_plans];
+    bl.total = start[n_plans];
     bl.precision = prec;
     bl.radial = radial;
     bl.sched = sdc::sched_index(schedule);
     bl.lds = lds;
     b->schedule = schedule;
-    const int e = sdc::batch_grid(prec, bl.sched, radial, lds, device, std::max(bl.total, 1), &bl.grid);
+    const int e = sdc::batch_grid(prec, bl.sched, radial, lds, device, std::max<int64_t>(bl.total, 1), &bl.grid);
     if (e != 0) {
         delete b;
         return hip_err(e, "batch occupancy");

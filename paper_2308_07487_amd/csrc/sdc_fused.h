@@ -633,7 +633,7 @@ __global__ __launch_bounds__(threads_per_wg(SCHED), waves_per_simd(SCHED)) void 
 template <int PREC, int RADIAL, int SCHED>
 __global__ __launch_bounds__(threads_per_wg(SCHED), waves_per_simd(SCHED)) void fused_batch_kernel(
     const FusedArgs* __restrict__ args, const int64_t* __restrict__ task_start, int n_plans,
-    unsigned* __restrict__ queue, const int32_t* __restrict__ ranges, int total) {
+    unsigned* __restrict__ queue, const int64_t* __restrict__ ranges, int64_t total) {
     extern __shared__ double hist[];
     __shared__ int s_task, s_plan, s_queue, s_exhausted;
     if (threadIdx.x == 0) {
@@ -644,14 +644,14 @@ __global__ __launch_bounds__(threads_per_wg(SCHED), waves_per_simd(SCHED)) void 
         if (threadIdx.x == 0) {
             // queue state in LDS: no registers stay live across a task
             int x = s_queue, exhausted = s_exhausted;
-            int t = -1;
+            int64_t t = -1;
             while (exhausted < 8) {
-                const int lo = ranges[x];
-                const int hi = min(ranges[x + 1], total);
+                const int64_t lo = ranges[x];
+                const int64_t hi = ranges[x + 1] < total ? ranges[x + 1] : total;
                 if (lo < hi) {
                     const unsigned k = atomicAdd(&queue[x], 1u);
-                    if (k < (unsigned)(hi - lo)) {
-                        t = lo + (int)k;
+                    if ((int64_t)k < hi - lo) {
+                        t = lo + k;
                         break;
                     }
                 }
@@ -667,9 +667,9 @@ __global__ __launch_bounds__(threads_per_wg(SCHED), waves_per_simd(SCHED)) void 
                     else hi = mid - 1;
                 }
                 pl = lo;
-                t -= (int)task_start[pl];
+                t -= task_start[pl];
             }
-            s_task = t;
+            s_task = (int)t;
             s_plan = pl;
             s_queue = x;
             s_exhausted = exhausted;

@@ -317,6 +317,9 @@ struct FusedArgs {
 };
 int launch_fused(const FusedArgs& a, void* stream);
 
+// Most tasks of a batch: the claims of a queue, one too many per workgroup,
+// stay within its 32-bit counter.
+constexpr int64_t kMaxBatchTasks = 4000000000;
 // One persistent launch over the tasks of several plans (same precision and
 // bin class): args[n_plans] and task_start[n_plans + 1] in device memory,
 // queue = 8 device counters (zeroed by the launch itself).
@@ -325,15 +328,15 @@ struct BatchLaunch {
     const int64_t* task_start;
     int n_plans;
     unsigned* queue;
-    const int32_t* ranges;  // [9]: XCD queue x holds tasks [ranges[x], ranges[x + 1])
-    int total;
+    const int64_t* ranges;  // [9]: XCD queue x holds tasks [ranges[x], ranges[x + 1])
+    int64_t total;          // at most kMaxBatchTasks
     int precision, radial, sched;
     int lds, grid;
 };
 int launch_fused_batch(const BatchLaunch& b, void* stream);
 // Workgroups that fit on the device at once (a multiple of 8, at most `total`
 // rounded up to 8).
-int batch_grid(int precision, int sched, int radial, int lds, int device, int total, int* grid);
+int batch_grid(int precision, int sched, int radial, int lds, int device, int64_t total, int* grid);
 
 struct CountArgs {
     const KPair* pairs;

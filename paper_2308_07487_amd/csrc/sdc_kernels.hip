@@ -212,7 +212,7 @@ int launch_fused(const FusedArgs& a, void* stream) {
     return (int)hipLaunchKernel(fn, dim3(grid), dim3(threads_per_wg(a.sched)), params, lds, (hipStream_t)stream);
 }
 
-int batch_grid(int precision, int sched, int radial, int lds, int device, int total, int* grid) {
+int batch_grid(int precision, int sched, int radial, int lds, int device, int64_t total, int* grid) {
     const void* fn = fused_kernel_of(precision, sched, radial, 0, true);
     if (!fn) return (int)hipErrorInvalidValue;
     int per_cu = 0, n_cu = 0;
@@ -238,8 +238,8 @@ int launch_fused_batch(const BatchLaunch& b, void* stream) {
     const int64_t* task_start = b.task_start;
     int n_plans = b.n_plans;
     unsigned* queue = b.queue;
-    const int32_t* ranges = b.ranges;
-    int total = b.total;
+    const int64_t* ranges = b.ranges;
+    int64_t total = b.total;
     void* params[] = {(void*)&args, (void*)&task_start, (void*)&n_plans, (void*)&queue, (void*)&ranges,
                       (void*)&total};
     return (int)hipLaunchKernel(fn, dim3(b.grid), dim3(threads_per_wg(b.sched)), params, b.lds,
