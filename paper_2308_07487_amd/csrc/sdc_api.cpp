@@ -482,14 +482,12 @@ sdc_status sdc_plan_create_tuned(const float* positions_host, int64_t n_sites, c
         int n_cu = 0;
         if (hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || n_cu < 1)
             n_cu = 256;
-        // lag groups of the full selection, workgroups resident at once
-        const int64_t slots = (int64_t)n_cu * sdc::wg_per_cu(sdc::sched_index(tu.schedule));
         try {
+            // lag groups of the full selection
             std::vector<int> lags((size_t)corr->n_lags);
             for (int t = 0; t < corr->n_lags; ++t) lags[t] = t;
             const int n_groups = (int)make_groups(lags, corr->origin_stride, sdc::lag_group(corr->precision)).size();
-            const int seg = sdc::fitted_segment(p->lay, n_groups, slots, sdc::max_fused_tasks(sdc::sched_index(tu.schedule)));
-            sdc::split_streams(&p->lay, seg);
+            sdc::split_streams(&p->lay, sdc::fitted_segment(p->lay, n_groups, n_cu, sdc::sched_index(tu.schedule)));
         } catch (const std::bad_alloc&) {
             delete p;
             return set_err(SDC_ERR_OOM, "host allocation failed");

@@ -162,11 +162,11 @@ sdc_status resolve_tuning(const sdc_tuning* given, int64_t n_sites, const sdc_bi
 // tile pairs.
 void split_streams(Layout* lay, int seg);
 // Tile pairs per task that suit a layout of whole streams run with n_groups
-// lag groups by `slots` workgroups at a time, at most max_tasks tasks where
-// segments of up to kLongestSegmentPeriodic pairs (radial: whole streams)
-// allow that.
+// lag groups in a schedule on n_cu compute units, as many as fit one launch
+// where segments of up to kLongestSegmentPeriodic pairs (radial: whole
+// streams) allow that.
 constexpr int kFittedSegmentPeriodic = 32, kFittedSegmentRadial = 64, kLongestSegmentPeriodic = 128;
-int fitted_segment(const Layout& lay, int n_groups, int64_t slots, int64_t max_tasks);
+int fitted_segment(const Layout& lay, int n_groups, int n_cu, int sched);
 // Tasks of one fused launch: 2^32 - 1 threads in whole rows of 8 workgroups.
 constexpr int64_t max_fused_tasks(int sched) { return (int64_t)UINT32_MAX / threads_per_wg(sched) / 8 * 8; }
 

@@ -381,23 +381,29 @@ void split_streams(Layout* lay, int seg) {
 }
 
 // A task's cost is its tile pairs plus about one more for clearing and
-// merging its histogram, so with Q tile pairs for every workgroup slot the
-// length near sqrt(Q) balances the merges against the half-empty last round
-// of tasks (and keeps the lag groups of a segment in step, see above).  For
-// few pairs per slot (Q < 32) the rounds are counted: the longest segments
-// of the least ceil(tasks / slots) (length + 1).  Fused launch, whole streams
-// or 96-pair segments against the length chosen: sc 8^3 x 64 lags 69 -> 30 us
-// (1 pair), sc 12^3 x 70 lags 283 -> 190 us (14), bcc 13x14x15 x 130 lags 7.63
-// -> 7.15 ms (18; with bricks), 3001 points x 100 lags 1.27 -> 0.89 ms (7), 20 011 points x
-// 128 lags 58.0 -> 56.1 ms (55).  Never above 32 pairs (radial 64): over
-// longer ones the lag groups lose step and their operand re-reads miss L2
-// (periodic samples of 25 000 to 100 000 sites with 32 pairs are up to 4%
-// faster than with 96 and at most 3% slower than with their best of 16, 32
-// and 48; 65 536 points in 1024 shells take 588 ms with 64 and 600 ms with
-// 181 or whole streams).
-int fitted_segment(const Layout& lay, int n_groups, int64_t slots, int64_t max_tasks) {
+// merging its histogram, so with q tile pairs for every workgroup slot the
+// length near sqrt(q) balances the merges against the half-empty last round
+// of tasks (and keeps the lag groups of a segment in step, see above).  The
+// rounds are counted instead, and the longest segments of the least
+// ceil(tasks / slots) (length + 1) taken, for few pairs per slot (q < 32), and
+// for streams of one length at one workgroup per CU, where nothing fills the
+// last round in.  Fused launch, whole streams or 96-pair segments against the
+// length chosen: sc 8^3 x 64 lags 69 -> 30 us (1 pair), sc 12^3 x 70 lags 283 ->
+// 190 us (14), bcc 13x14x15 x 130 lags 7.63 -> 7.15 ms (18; with bricks), 3001
+// points x 100 lags 1.27 -> 0.89 ms (7), 20 011 points x 128 lags 58.0 -> 56.1 ms
+// (55).  sqrt(q) against counted rounds at one workgroup per CU: BF16x3 sc 20^3
+// x 8 lags 867 (8 pairs) / 789 us (32), FP32 sc 20^3 x 20 lags 4.92 / 4.58 ms,
+// FP32 8000 points x 8 lags 1.41 / 1.21 ms; at two workgroups per CU, or with
+// streams of all lengths (box order), counting loses up to 6%.  Never above 32 pairs (radial
+// 64): over longer ones the lag groups lose step and their operand re-reads
+// miss L2 (periodic samples of 25 000 to 100 000 sites with 32 pairs are up to
+// 4% faster than with 96 and at most 3% slower than with their best of 16, 32
+// and 48; 65 536 points in 1024 shells take 588 ms with 64 and 600 ms with 181
+// or whole streams).
+int fitted_segment(const Layout& lay, int n_groups, int n_cu, int sched) {
     const bool radial = lay.kind == SDC_BINS_RADIAL;
     const int cap = radial ? kFittedSegmentRadial : kFittedSegmentPeriodic;
+    const int64_t slots = (int64_t)n_cu * wg_per_cu(sched);
     int64_t pairs = 0;
     int longest = 1;
     for (const KStream& s : lay.streams) {
@@ -418,7 +424,8 @@ int fitted_segment(const Layout& lay, int n_groups, int64_t slots, int64_t max_t
     };
     const double q = (double)pairs * n_groups / (double)slots;
     int best = std::min(longest, cap);
-    if (q >= 32.0) {
+    const bool count = q < 32.0 || (wg_per_cu(sched) == 1 && !lay.linear && q < (double)cap * cap);
+    if (!count) {
         best = std::max(1, (int)std::min((double)cap, std::sqrt(q) + 0.5));
     } else {
         double best_cost = -1.0;
@@ -434,7 +441,7 @@ int fitted_segment(const Layout& lay, int n_groups, int64_t slots, int64_t max_t
     }
     // a sample whose tasks would not fit one launch takes longer segments
     const int limit = radial ? longest : std::min(longest, kLongestSegmentPeriodic);
-    while (best < limit && cut(best, nullptr) * n_groups > max_tasks) best = std::min(limit, best + std::max(1, best / 8));
+    while (best < limit && cut(best, nullptr) * n_groups > max_fused_tasks(sched)) best = std::min(limit, best + std::max(1, best / 8));
     return best;
 }
 

@@ -27,7 +27,7 @@ int main(int argc, char** argv) {
         lay.streams.push_back(s);
     }
     const long most = (long)sdc::max_fused_tasks(sched);
-    const int seg = sdc::fitted_segment(lay, groups, 256 * sdc::wg_per_cu(sched), most);
+    const int seg = sdc::fitted_segment(lay, groups, 256, sched);
     std::printf("%d %ld %ld\n", seg, n * ((len + seg - 1) / seg), most);
 }
 """
@@ -78,3 +78,21 @@ def test_sample_beyond_one_launch_keeps_its_subsets(prog):
 def test_ordinary_samples(prog, tiles, groups, sched, kind, seg):
     """sc 36^3 x 256 lags, sc 8^3 x 64 lags, 65 536 points x 128 lags."""
     assert prog(kind, tiles, tiles, groups, sched)[0] == seg
+
+
+@pytest.mark.parametrize("kind,tiles,groups,sched", [
+    ("periodic", 125, 1, ONE), ("periodic", 125, 2, ONE), ("periodic", 64, 4, ONE), ("periodic", 64, 8, ONE),
+    ("periodic", 27, 9, TWO), ("radial", 125, 1, ONE), ("radial", 313, 8, ONE), ("periodic", 128, 8, SPLIT)])
+def test_rounds_are_counted(prog, kind, tiles, groups, sched):
+    """The length has the least rounds x (pairs + 1) of all up to the cap; sc 20^3 x
+    8 lags in BF16x3 (125 tiles, one group) took segments of 8, 10% over 32."""
+    slots = 256 * (2 if sched == TWO else 1)
+
+    def cost(seg):
+        k = -(-tiles // seg)
+        return -(-tiles * k * groups // slots) * (-(-tiles // k) + 1)
+
+    seg, _, _ = prog(kind, tiles, tiles, groups, sched)
+    cap = min(tiles, 64 if kind == "radial" else 32)
+    assert tiles * tiles * groups < cap * cap * slots  # few enough pairs per slot
+    assert seg <= cap and cost(seg) == min(cost(s) for s in range(1, cap + 1))
