@@ -388,7 +388,7 @@ sdc_status sdc_layout_keys(const float* positions_host, int64_t n_sites, const s
     std::string err;
     sdc_status s;
     try {
-        s = sdc::build_layout(positions_host, n_sites, bins, sdc::default_segment_pairs(bins->kind), &lay, &err);
+        s = sdc::build_layout(positions_host, n_sites, bins, -1, sdc::default_segment_pairs(bins->kind), &lay, &err);
     } catch (const std::bad_alloc&) {
         return set_err(SDC_ERR_OOM, "host allocation failed");
     }
@@ -462,8 +462,8 @@ sdc_status sdc_plan_create_tuned(const float* positions_host, int64_t n_sites, c
         p->corr = *corr;
         p->tuning = tu;
         std::string err;
-        s = sdc::build_layout(positions_host, n_sites, bins, default_segment ? sdc::kMaxSegmentPairs : tu.segment_pairs,
-                              &p->lay, &err);
+        s = sdc::build_layout(positions_host, n_sites, bins, corr->precision,
+                              default_segment ? sdc::kMaxSegmentPairs : tu.segment_pairs, &p->lay, &err);
         if (s != SDC_OK) {
             delete p;
             return set_err(s, err);

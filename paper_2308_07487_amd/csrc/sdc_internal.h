@@ -12,8 +12,8 @@ namespace sdc {
 
 // Sites are grouped in tiles of 64.  Periodic lattices: a tile is a brick of
 // at most 64 cells of one sublattice, slot (o0 s1 + o1) s2 + o2, or, where
-// bricks would leave more tiles, 64 consecutive cells in box order (see
-// layout_linear).  Radial: 64 consecutive points in Morton order.  Unused
+// bricks would leave clearly more tiles, 64 consecutive cells in box order (see
+// build_periodic).  Radial: 64 consecutive points in Morton order.  Unused
 // slots are padding (zero spins, no counts).
 constexpr int kTile = 64;
 // Lags handled together by one fused task (consecutive lag indices u): 8
@@ -138,8 +138,10 @@ struct Layout {
 sdc_status set_error(sdc_status s, const std::string& msg);
 
 // Builds the tile layout of a sample, streams cut into segments of at most
-// segment_pairs tile pairs.  Returns SDC_OK or an error with text.
-sdc_status build_layout(const float* pos, int64_t n, const sdc_bin_spec* spec, int segment_pairs,
+// segment_pairs tile pairs.  precision: the product's, which weighs the tile
+// shapes against each other (-1: the fewest tiles).  Returns SDC_OK or an error
+// with text.
+sdc_status build_layout(const float* pos, int64_t n, const sdc_bin_spec* spec, int precision, int segment_pairs,
                         Layout* out, std::string* err);
 
 // Default tile pairs per fused task: periodic streams cut into segments of

@@ -260,16 +260,31 @@ void layout_bricks(int64_t n, int nsub, const int nb[3], const std::vector<int32
                     }
 }
 
-// Bricks or box order: whichever needs fewer tiles (the product costs
-// O(tiles^2)); on a tie bricks, whose windows are smaller.  Bricks fill their
+// Tiles of a thousand that box order has to save to be taken (see below).
+int box_order_margin(int precision) {
+    switch (precision) {
+        case SDC_PREC_SPLIT_BF16:
+        case SDC_PREC_SPLIT_FP16: return 6;
+        case SDC_PREC_FP32: return 10;
+        case SDC_PREC_BF16X3: return 22;
+        default: return 0;
+    }
+}
+
+// Bricks or box order: the one with fewer tiles (the product costs
+// O(tiles^2)), bricks where box order saves too little.  Bricks fill their
 // slots when the edges have divisors that multiply to 64; the box order always
-// does but for the last tile, at the price of two compares per element and a
-// window of 508 bins.  Fused launch with bricks only / this rule: bcc 13x14x15
-// (98 / 86 tiles) 7.2 / 5.7 ms, bcc 9x10x11 with stride 3 0.77 / 0.40 ms, sc 30^3
-// x 100 lags 147 / 122 ms, ten samples of edges 10 to 22 in one batch 290 / 218
-// ms, 90 x 90 (130 / 127 tiles) 8.3 / 8.1 ms, 200 x 200 102 / 101 ms (before
-// the split packs' planes, which take another 1 to 3%).
-sdc_status build_periodic(const float* pos, int64_t n, const sdc_bin_spec* spec, int seg, Layout* lay,
+// does but for the last tile, at the price of two compares per element, a
+// window of 508 bins and streams of all lengths, which the product hides best
+// at two workgroups per CU (the hi/lo splits) and least where a step is short
+// on other vector work (BF16x3).  Fused ms with bricks / box order (tiles), 50
+// origins x 64 lags: BF16 121x191 (363 / 362) 31.0 / 31.5, 112x142 (252 / 249)
+// 15.6 / 15.1, 27^3 (324 / 308) 25.6 / 23.6; FP32 94x191 (282 / 281) 53.3 / 55.4,
+// 12x18x28 (96 / 95) 6.74 / 6.92, 111x175 (308 / 304) 67.1 / 64.6; BF16x3 34x94
+// (51 / 50) 1.22 / 1.34, 21^3 (147 / 145) 10.2 / 10.8, 90x90 (130 / 127) 8.02 /
+// 7.93, 27^3 47.9 / 46.2.  The margins lie where 37 such boxes break even: below
+// 0.6, 1 and 2.2% they lose 1, 2 and 4% on average.
+sdc_status build_periodic(const float* pos, int64_t n, const sdc_bin_spec* spec, int precision, int seg, Layout* lay,
                           std::string* err) {
     const bool bcc = spec->kind == SDC_BINS_PERIODIC_BCC;
     const int nsub = bcc ? 2 : 1;
@@ -289,7 +304,8 @@ sdc_status build_periodic(const float* pos, int64_t n, const sdc_bin_spec* spec,
     if (s != SDC_OK) return s;
     int nb[3];
     choose_bricks(L, nb);
-    if ((cells + kTile - 1) / kTile < (int64_t)nb[0] * nb[1] * nb[2])
+    const int64_t bricks = (int64_t)nb[0] * nb[1] * nb[2], saved = bricks - (cells + kTile - 1) / kTile;
+    if (saved * 1000 > bricks * box_order_margin(precision))
         layout_linear(n, nsub, cell, sub, lay);
     else
         layout_bricks(n, nsub, nb, cell, sub, lay);
@@ -445,8 +461,8 @@ int fitted_segment(const Layout& lay, int n_groups, int n_cu, int sched) {
     return best;
 }
 
-sdc_status build_layout(const float* pos, int64_t n, const sdc_bin_spec* spec, int segment_pairs, Layout* lay,
-                        std::string* err) {
+sdc_status build_layout(const float* pos, int64_t n, const sdc_bin_spec* spec, int precision, int segment_pairs,
+                        Layout* lay, std::string* err) {
     if (!pos || !spec || !lay) return fail(err, SDC_ERR_INVALID_ARG, "null pointer");
     if (segment_pairs < 1) return fail(err, SDC_ERR_INVALID_ARG, "segment_pairs must be >= 1");
     if (n < 1) return fail(err, SDC_ERR_INVALID_ARG, "n_sites must be >= 1");
@@ -456,7 +472,7 @@ sdc_status build_layout(const float* pos, int64_t n, const sdc_bin_spec* spec, i
     lay->n = n;
     sdc_status s;
     if (spec->kind == SDC_BINS_PERIODIC_SC || spec->kind == SDC_BINS_PERIODIC_BCC)
-        s = build_periodic(pos, n, spec, segment_pairs, lay, err);
+        s = build_periodic(pos, n, spec, precision, segment_pairs, lay, err);
     else if (spec->kind == SDC_BINS_RADIAL)
         s = build_radial(pos, n, spec, segment_pairs, lay, err);
     else
