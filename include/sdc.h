@@ -161,10 +161,12 @@ typedef struct {
     int32_t schedule;      /* sdc_schedule                                     */
     int32_t segment_pairs; /* tile pairs per fused task (pairs that share one  */
                            /* LDS histogram; one merge into the global bins    */
-                           /* per task): 0 = default (at most 96 for periodic  */
-                           /* kinds and all pairs of an i-tile for radial, cut */
-                           /* to fit the sample and the device), else          */
-                           /* [1, 2^20]                                        */
+                           /* per task), [1, 2^20].  0 = default, which a plan */
+                           /* reports as 96 for periodic kinds and 2^20 for    */
+                           /* radial: the length is fitted to the sample and   */
+                           /* the device (at most 32, radial 64, unless the    */
+                           /* tasks would not fit one launch).  Other values   */
+                           /* are taken as they are.                           */
 } sdc_tuning;
 
 typedef struct sdc_plan sdc_plan;
@@ -203,9 +205,15 @@ sdc_status sdc_plan_create_tuned(const float* positions_host, int64_t n_sites,
                                  const sdc_bin_spec* bins, const sdc_corr_spec* corr,
                                  const sdc_tuning* tuning, int device, sdc_plan** out);
 
-/* The tuning a plan runs with (fields resolved, never 0).
+/* The tuning a plan was made with (fields resolved, never 0); given to
+ * sdc_plan_create_tuned it makes the same work list again.
  * Errors: INVALID_ARG. */
 sdc_status sdc_plan_get_tuning(const sdc_plan* plan, sdc_tuning* tuning);
+
+/* Tile pairs of the longest task of the plan (of the length fitted for a
+ * default segment_pairs; streams shorter than the length asked for are one
+ * task each).  Errors: INVALID_ARG. */
+sdc_status sdc_plan_segment_pairs(const sdc_plan* plan, int32_t* segment_pairs);
 
 /*
  * Autotuner: for one sample shape, times candidate tunings on the device
@@ -218,7 +226,8 @@ sdc_status sdc_plan_get_tuning(const sdc_plan* plan, sdc_tuning* tuning);
  *  candidates   : n_candidates tunings with every field set, or NULL for the
  *                 built-in list (sdc_autotune_candidates: every schedule the
  *                 precision has x segment lengths {16, 32, 48, 96, 192} for
- *                 periodic kinds, {64, 256, all} for radial).
+ *                 periodic kinds, {64, 256, 2^20} for radial; 96 and 2^20 are
+ *                 the default, fitted length).
  *  cache_path   : JSON tuning file; when not NULL the winner is written under
  *                 the plan's size-class key with every candidate's time
  *                 (other entries are kept; the file is replaced atomically),

@@ -643,6 +643,15 @@ sdc_status sdc_plan_get_tuning(const sdc_plan* plan, sdc_tuning* tuning) {
     return SDC_OK;
 }
 
+sdc_status sdc_plan_segment_pairs(const sdc_plan* plan, int32_t* segment_pairs) {
+    g_err.clear();
+    if (!plan || !segment_pairs) return set_err(SDC_ERR_INVALID_ARG, "null pointer");
+    int32_t longest = 0;
+    for (const KStream& s : plan->lay.streams) longest = std::max(longest, s.p1 - s.p0);
+    *segment_pairs = longest;
+    return SDC_OK;
+}
+
 sdc_status sdc_plan_n_bins(const sdc_plan* plan, int64_t* n_bins) {
     g_err.clear();
     if (!plan || !n_bins) return set_err(SDC_ERR_INVALID_ARG, "null pointer");

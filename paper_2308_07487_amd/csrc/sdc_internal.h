@@ -144,8 +144,8 @@ sdc_status set_error(sdc_status s, const std::string& msg);
 sdc_status build_layout(const float* pos, int64_t n, const sdc_bin_spec* spec, int precision, int segment_pairs,
                         Layout* out, std::string* err);
 
-// Default tile pairs per fused task: periodic streams cut into segments of
-// 96 pairs, radial streams (all j-tiles of an i-tile) whole.
+// What the default segment length is called (sdc_tuning::segment_pairs): plans
+// and tuning files hold these values, and the length is fitted_segment()'s.
 constexpr int kDefaultSegmentPeriodic = 96;
 constexpr int kMaxSegmentPairs = 1 << 20;
 constexpr int default_segment_pairs(int kind) {
@@ -155,8 +155,8 @@ constexpr int default_segment_pairs(int kind) {
 // Tuning a plan runs with (sdc_tune.cpp): the caller's fields where set,
 // else the entry of the tuning file named by SDC_TUNING_FILE for the plan's
 // size class, else the defaults.  Every field of *out is set (no zeros).
-// *default_segment (may be null): the segment length is the default one,
-// below which fitted_segment() may go.
+// *default_segment (may be null): the segment length is the default one, for
+// fitted_segment() to choose.
 sdc_status resolve_tuning(const sdc_tuning* given, int64_t n_sites, const sdc_bin_spec* bins,
                           const sdc_corr_spec* corr, int device, sdc_tuning* out, bool* default_segment = nullptr);
 

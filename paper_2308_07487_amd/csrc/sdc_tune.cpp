@@ -205,7 +205,6 @@ sdc_status resolve_tuning(const sdc_tuning* given, int64_t n_sites, const sdc_bi
                           const sdc_corr_spec* corr, int device, sdc_tuning* out, bool* default_segment) {
     sdc_tuning t{};
     if (given) t = *given;
-    if (default_segment) *default_segment = false;
     if (t.schedule < SDC_SCHED_DEFAULT || t.schedule > SDC_SCHED_FOLD)
         return set_error(SDC_ERR_INVALID_ARG, "unknown schedule");
     if (t.segment_pairs < 0 || t.segment_pairs > kMaxSegmentPairs)
@@ -228,10 +227,10 @@ sdc_status resolve_tuning(const sdc_tuning* given, int64_t n_sites, const sdc_bi
         return set_error(SDC_ERR_INVALID_ARG, "unknown schedule in the tuning file");
     if (!sched_valid(corr->precision, sched_index(t.schedule)))
         return set_error(SDC_ERR_UNSUPPORTED, "schedule not available for this precision");
-    if (t.segment_pairs <= 0 || t.segment_pairs > kMaxSegmentPairs) {
-        t.segment_pairs = default_segment_pairs(bins->kind);
-        if (default_segment) *default_segment = true;
-    }
+    if (t.segment_pairs <= 0 || t.segment_pairs > kMaxSegmentPairs) t.segment_pairs = default_segment_pairs(bins->kind);
+    // by its name too: what a plan reports, and what the tuner timed and wrote
+    // to its file, is the same work list again
+    if (default_segment) *default_segment = t.segment_pairs == default_segment_pairs(bins->kind);
     *out = t;
     return SDC_OK;
 }

@@ -82,7 +82,7 @@ EXPORTS = ("sdc_plan_create", "sdc_plan_n_bins", "sdc_accumulate", "sdc_finalize
            "sdc_batch_destroy", "sdc_plan_structure_factor", "sdc_sq_create", "sdc_sq_accumulate",
            "sdc_sq_finalize", "sdc_sq_timings", "sdc_sq_reset", "sdc_sq_destroy", "sdc_mc_n_sweeps",
            "sdc_mc_anneal", "sdc_mc_create", "sdc_mc_run", "sdc_mc_timings", "sdc_mc_uses_stencil",
-           "sdc_mc_destroy", "sdc_plan_create_tuned", "sdc_plan_get_tuning", "sdc_autotune",
+           "sdc_mc_destroy", "sdc_plan_create_tuned", "sdc_plan_get_tuning", "sdc_plan_segment_pairs", "sdc_autotune",
            "sdc_tuning_lookup", "sdc_batch_create_tuned", "sdc_batch_schedule",
            "sdc_plan_structure_factor_static", "sdc_mfma_peak", "sdc_mfma_probe",
            "sdc_autotune_candidates")
@@ -110,6 +110,7 @@ def lib():
         L.sdc_plan_create_tuned.argtypes = [P, i64, ctypes.POINTER(BinSpec), ctypes.POINTER(CorrSpec),
                                             ctypes.POINTER(Tuning), ctypes.c_int, ctypes.POINTER(P)]
         L.sdc_plan_get_tuning.argtypes = [P, ctypes.POINTER(Tuning)]
+        L.sdc_plan_segment_pairs.argtypes = [P, ctypes.POINTER(i32)]
         L.sdc_autotune.argtypes = [P, i64, ctypes.POINTER(BinSpec), ctypes.POINTER(CorrSpec), ctypes.c_int,
                                    i32, P, i32, ctypes.c_char_p, ctypes.POINTER(Tuning),
                                    ctypes.POINTER(ctypes.c_double), P]
@@ -333,10 +334,19 @@ class Plan:
 
     @property
     def tuning(self):
-        """{"schedule", "segment_pairs"} the plan runs with."""
+        """{"schedule", "segment_pairs"} the plan was made with: Plan(..., **plan.tuning)
+        makes the same work list.  96 pairs (radial 2^20) stand for the default,
+        whose length is fitted (segment_pairs below)."""
         t = Tuning()
         _check(lib().sdc_plan_get_tuning(self._h, ctypes.byref(t)), "sdc_plan_get_tuning")
         return _tuning_dict(t)
+
+    @property
+    def segment_pairs(self):
+        """Tile pairs of the plan's longest task."""
+        v = ctypes.c_int32()
+        _check(lib().sdc_plan_segment_pairs(self._h, ctypes.byref(v)), "sdc_plan_segment_pairs")
+        return int(v.value)
 
     def accumulate(self, spins, lags=None, stream=None):
         """spins: contiguous float32 device tensor [T][N][3]."""
