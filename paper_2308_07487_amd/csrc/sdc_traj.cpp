@@ -388,8 +388,10 @@ struct sdc_mc {
 
 namespace {
 
-// Sweeps of one launch of the small-sample kernel (a few milliseconds).
-constexpr int64_t kSmallStretch = 1024;
+// Classes that one launch of the small-sample kernel updates: 2 to 5 us each
+// with six bonds per site, about 20 with 80 (open sc 15^3 within 2.5, 31 classes,
+// 625 us per sweep), so a launch ends within a few to 45 ms.
+constexpr int64_t kSmallClassUpdates = 2048;
 
 uint32_t float_bits(float f) {
     uint32_t u;
@@ -612,7 +614,7 @@ extern "C" sdc_status sdc_mc_run(sdc_mc* m, const sdc_mc_spec* schedule, const f
     double T_last = schedule->T_start;
     long long* hist = accepted_host ? m->d_hist : nullptr;
     if (sdc::mc_is_small(m->n, m->start.data(), m->n_col)) {
-        // stretches of at most kSmallStretch sweeps per launch
+        const int64_t stretch = std::max<int64_t>(1, kSmallClassUpdates / m->n_col);
         sdc::McSmall sm{};
         sm.T = schedule->T_start;
         sm.T_end = schedule->T_end;
@@ -628,7 +630,7 @@ extern "C" sdc_status sdc_mc_run(sdc_mc* m, const sdc_mc_spec* schedule, const f
                 next.T *= next.cool;
                 next.done = 0;
             }
-            if (next.count == kSmallStretch) {
+            if (next.count == stretch) {
                 sm.count = next.count;
                 if (le == 0) le = sdc::launch_mc_small(ma, sm, hist, stream);
                 sm.T = next.T;
