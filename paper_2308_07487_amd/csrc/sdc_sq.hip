@@ -338,7 +338,8 @@ __global__ __launch_bounds__(256) void sq_corr_kernel(SqCorrArgs a) {
     }
     for (int t = threadIdx.x; t < a.n_lags; t += 256) {
         double re = 0.0, im = 0.0;
-#pragma unroll(LDS ? 2 : 1)
+        constexpr int kTurn = LDS ? 2 : 1;  // origins per turn
+#pragma unroll kTurn
         for (int o = 0; o < a.n_origins; ++o) {
             const int64_t f0 = (int64_t)o * a.stride, f1 = f0 + t;
 #pragma unroll
