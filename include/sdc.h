@@ -210,9 +210,10 @@ sdc_status sdc_plan_create_tuned(const float* positions_host, int64_t n_sites,
  * Errors: INVALID_ARG. */
 sdc_status sdc_plan_get_tuning(const sdc_plan* plan, sdc_tuning* tuning);
 
-/* Tile pairs of the longest task of the plan (of the length fitted for a
- * default segment_pairs; streams shorter than the length asked for are one
- * task each).  Errors: INVALID_ARG. */
+/* Tile pairs of the longest task of the plan accumulated alone (of the length
+ * fitted for a default segment_pairs, which a batch fits again; streams
+ * shorter than the length asked for are one task each).
+ * Errors: INVALID_ARG. */
 sdc_status sdc_plan_segment_pairs(const sdc_plan* plan, int32_t* segment_pairs);
 
 /*
@@ -394,7 +395,7 @@ typedef struct sdc_batch sdc_batch;
  *  out     : receives the batch; it refers to the plans, which must outlive
  *            it (sdc_plan_destroy refuses a plan still in a batch).
  * Uploads the per-plan kernel arguments once.  Errors: INVALID_ARG,
- * UNSUPPORTED (more than 2^30 tasks), STATE (a plan failed earlier), OOM,
+ * UNSUPPORTED (more than 4e9 tasks), STATE (a plan failed earlier), OOM,
  * HIP.
  */
 sdc_status sdc_batch_create(sdc_plan* const* plans, int32_t n_plans, int32_t flags, sdc_batch** out);
@@ -422,7 +423,8 @@ sdc_status sdc_batch_accumulate(sdc_batch* batch, const float* const* spins_dev,
 sdc_status sdc_batch_timings(sdc_batch* batch, double* ms);
 
 /* sdc_batch_create with the schedule of its one launch given: tuning->schedule
- * (segment_pairs is ignored: each plan keeps its own layout).  tuning == NULL
+ * (segment_pairs is ignored: each plan keeps its own layout and segment
+ * length; default lengths are fitted to the batch's share of the device).  tuning == NULL
  * or SDC_SCHED_DEFAULT takes the schedule that the plans' own tunings give
  * the most work (sum of n_sites^2 * n_lags * n_origins).  The launch's task
  * list takes the plans in order of decreasing task length (K-steps times tile

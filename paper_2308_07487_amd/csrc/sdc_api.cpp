@@ -147,6 +147,7 @@ struct sdc_plan {
     size_t bytes_A = 0, bytes_B = 0;
     std::map<std::vector<int>, LagSel> sels;
     sdc_tuning tuning{};  // resolved: schedule (never SDC_SCHED_DEFAULT) and segment length
+    std::vector<KStream> whole;  // default segment length: the streams before they were cut
     bool failed = false;
     int batch_refs = 0;  // batches that hold this plan
     hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
@@ -487,7 +488,10 @@ sdc_status sdc_plan_create_tuned(const float* positions_host, int64_t n_sites, c
             std::vector<int> lags((size_t)corr->n_lags);
             for (int t = 0; t < corr->n_lags; ++t) lags[t] = t;
             const int n_groups = (int)make_groups(lags, corr->origin_stride, sdc::lag_group(corr->precision)).size();
-            sdc::split_streams(&p->lay, sdc::fitted_segment(p->lay, n_groups, n_cu, sdc::sched_index(tu.schedule)));
+            const int sched = sdc::sched_index(tu.schedule);
+            p->whole.swap(p->lay.streams);
+            p->lay.streams = sdc::split_streams(
+                p->whole, sdc::fitted_segment(p->lay, p->whole, n_groups, (int64_t)n_cu * sdc::wg_per_cu(sched), sched, true));
         } catch (const std::bad_alloc&) {
             delete p;
             return set_err(SDC_ERR_OOM, "host allocation failed");
@@ -1045,20 +1049,6 @@ sdc_status sdc_batch_create_tuned(sdc_plan* const* plans, int32_t n_plans, int32
             }
         }
     }
-    // The launch's task list takes the plans in order of decreasing task
-    // length (K-steps times tile pairs per segment), so the workgroups finish
-    // on the short tasks of the small samples and the launch's tail is short;
-    // the plans keep the caller's order everywhere else.
-    std::vector<int> order((size_t)n_plans);
-    for (int k = 0; k < n_plans; ++k) order[k] = k;
-    auto task_len = [&](int k) {
-        const sdc_plan* p = plans[k];
-        return (double)p->nk * (double)p->lay.pairs.size() / (double)std::max<size_t>(1, p->lay.streams.size());
-    };
-    std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return task_len(x) > task_len(y); });
-    std::vector<sdc::FusedArgs> args((size_t)n_plans);
-    std::vector<int64_t> start((size_t)n_plans + 1, 0);
-    int lds = 0;
     for (int k = 0; k < n_plans; ++k) {
         sdc_plan* p = plans[k];
         const LagSel* sel = nullptr;
@@ -1071,6 +1061,53 @@ sdc_status sdc_batch_create_tuned(sdc_plan* const* plans, int32_t n_plans, int32
         ++p->batch_refs;
         b->sels.push_back(sel);
     }
+    // Streams of default length are cut for the plan's share of the device, by
+    // work (see the ranges below).  Cut as for a plan alone, the small samples'
+    // tasks were mostly merges: fused launch cut alone / by share, split-BF16,
+    // 48 samples sc 8^3 x 64 lags 1144 / 690 us, 16 bcc 8^3 x 8 lags 279 / 158, FP32
+    // 48 sc 8^3 x 64 lags 2360 / 1714 (in segments of at most 96 pairs, with the
+    // earlier histogram layout, 749, 167 and 1836).
+    std::vector<std::vector<KStream>> cuts((size_t)n_plans);
+    auto streams_of = [&](int k) -> const std::vector<KStream>& {
+        return cuts[k].empty() ? plans[k]->lay.streams : cuts[k];
+    };
+    if (n_plans > 1) {
+        int n_cu = 0;
+        if (hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || n_cu < 1)
+            n_cu = 256;
+        const int sched = sdc::sched_index(schedule);
+        auto work = [&](int k) {
+            return (double)plans[k]->lay.pairs.size() * (double)(plans[k]->nk + 4) * (double)b->sels[k]->n_groups;
+        };
+        double total = 0.0;
+        for (int k = 0; k < n_plans; ++k) total += work(k);
+        try {
+            for (int k = 0; k < n_plans; ++k) {
+                const sdc_plan* p = plans[k];
+                if (p->whole.empty()) continue;
+                const double share = (double)n_cu * sdc::wg_per_cu(sched) * work(k) / total;
+                cuts[k] = sdc::split_streams(p->whole, sdc::fitted_segment(p->lay, p->whole, b->sels[k]->n_groups,
+                                                                           std::max<int64_t>(1, (int64_t)share), sched, false));
+            }
+        } catch (const std::bad_alloc&) {
+            delete b;
+            return set_err(SDC_ERR_OOM, "host allocation failed");
+        }
+    }
+    // The launch's task list takes the plans in order of decreasing task
+    // length (K-steps times tile pairs per segment), so the workgroups finish
+    // on the short tasks of the small samples and the launch's tail is short;
+    // the plans keep the caller's order everywhere else.
+    std::vector<int> order((size_t)n_plans);
+    for (int k = 0; k < n_plans; ++k) order[k] = k;
+    auto task_len = [&](int k) {
+        const sdc_plan* p = plans[k];
+        return (double)p->nk * (double)p->lay.pairs.size() / (double)std::max<size_t>(1, streams_of(k).size());
+    };
+    std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return task_len(x) > task_len(y); });
+    std::vector<sdc::FusedArgs> args((size_t)n_plans);
+    std::vector<int64_t> start((size_t)n_plans + 1, 0);
+    int lds = 0;
     for (int k = 0; k < n_plans; ++k) {
         const int q = order[k];
         sdc_status s = fused_args(plans[q], *b->sels[q], &args[k]);
@@ -1079,6 +1116,18 @@ sdc_status sdc_batch_create_tuned(sdc_plan* const* plans, int32_t n_plans, int32
             return s;
         }
         args[k].sched = sdc::sched_index(schedule);
+        if (!cuts[q].empty()) {
+            args[k].n_streams = (int)cuts[q].size();
+            KStream* d = nullptr;
+            s = dalloc(&d, cuts[q].size(), &b->owned);
+            if (s == SDC_OK && hipMemcpy(d, cuts[q].data(), cuts[q].size() * sizeof(KStream), hipMemcpyHostToDevice) != hipSuccess)
+                s = set_err(SDC_ERR_HIP, "upload batch streams");
+            if (s != SDC_OK) {
+                delete b;
+                return s;
+            }
+            args[k].streams = d;
+        }
         start[k + 1] = start[k] + (int64_t)args[k].n_groups * args[k].n_streams;
         lds = std::max(lds, sdc::fused_lds_bytes(args[k].win, prec));
     }
@@ -1097,8 +1146,9 @@ sdc_status sdc_batch_create_tuned(sdc_plan* const* plans, int32_t n_plans, int32
         double w = 0.0;
         for (int k = 0; k < n_plans; ++k) {
             const sdc_plan* p = plans[order[k]];
-            for (size_t st = 0; st < p->lay.streams.size(); ++st) {
-                const KStream& ks = p->lay.streams[st];
+            const std::vector<KStream>& streams = streams_of(order[k]);
+            for (size_t st = 0; st < streams.size(); ++st) {
+                const KStream& ks = streams[st];
                 w += (double)(ks.p1 - ks.p0) * (double)(p->nk + 4) * (double)args[k].n_groups;
                 cut.push_back(start[k] + (int64_t)(st + 1) * args[k].n_groups);
                 cum.push_back(w);

@@ -162,13 +162,14 @@ sdc_status resolve_tuning(const sdc_tuning* given, int64_t n_sites, const sdc_bi
 
 // Cuts every stream into consecutive, about equal segments of at most seg
 // tile pairs.
-void split_streams(Layout* lay, int seg);
-// Tile pairs per task that suit a layout of whole streams run with n_groups
-// lag groups in a schedule on n_cu compute units, as many as fit one launch
-// where segments of up to kLongestSegmentPeriodic pairs (radial: whole
-// streams) allow that.
+std::vector<KStream> split_streams(const std::vector<KStream>& streams, int seg);
+// Tile pairs per task that suit the whole streams of a layout run with
+// n_groups lag groups by `slots` workgroups of a schedule at a time, as many as
+// fit one launch where segments of up to kLongestSegmentPeriodic pairs
+// (radial: whole streams) allow that.  alone: nothing else fills the slots.
 constexpr int kFittedSegmentPeriodic = 32, kFittedSegmentRadial = 64, kLongestSegmentPeriodic = 128;
-int fitted_segment(const Layout& lay, int n_groups, int n_cu, int sched);
+int fitted_segment(const Layout& lay, const std::vector<KStream>& whole, int n_groups, int64_t slots, int sched,
+                   bool alone);
 // Tasks of one fused launch: 2^32 - 1 threads in whole rows of 8 workgroups.
 constexpr int64_t max_fused_tasks(int sched) { return (int64_t)UINT32_MAX / threads_per_wg(sched) / 8 * 8; }
 

@@ -309,7 +309,7 @@ sdc_status build_periodic(const float* pos, int64_t n, const sdc_bin_spec* spec,
         layout_linear(n, nsub, cell, sub, lay);
     else
         layout_bricks(n, nsub, nb, cell, sub, lay);
-    split_streams(lay, seg);
+    lay->streams = split_streams(lay->streams, seg);
     return SDC_OK;
 }
 
@@ -369,7 +369,7 @@ sdc_status build_radial(const float* pos, int64_t n, const sdc_bin_spec* spec, i
         s.p1 = (int32_t)lay->pairs.size();
         lay->streams.push_back(s);
     }
-    split_streams(lay, seg);
+    lay->streams = split_streams(lay->streams, seg);
     return SDC_OK;
 }
 
@@ -381,9 +381,9 @@ sdc_status build_radial(const float* pos, int64_t n, const sdc_bin_spec* spec, i
 // a whole stream (up to ~1000 pairs) they drift apart and the operand
 // re-reads miss L2.  Shorter segments keep them in step at the price of
 // more histogram merges (one per segment, lag group and window bin).
-void split_streams(Layout* lay, int seg) {
+std::vector<KStream> split_streams(const std::vector<KStream>& streams, int seg) {
     std::vector<KStream> out;
-    for (const KStream& s : lay->streams) {
+    for (const KStream& s : streams) {
         const int len = s.p1 - s.p0;
         const int nseg = (len + seg - 1) / seg;
         for (int k = 0; k < nseg; ++k) {
@@ -393,7 +393,7 @@ void split_streams(Layout* lay, int seg) {
             out.push_back(t);
         }
     }
-    lay->streams.swap(out);
+    return out;
 }
 
 // A task's cost is its tile pairs plus about one more for clearing and
@@ -416,13 +416,13 @@ void split_streams(Layout* lay, int seg) {
 // 4% faster than with 96 and at most 3% slower than with their best of 16, 32
 // and 48; 65 536 points in 1024 shells take 588 ms with 64 and 600 ms with 181
 // or whole streams).
-int fitted_segment(const Layout& lay, int n_groups, int n_cu, int sched) {
+int fitted_segment(const Layout& lay, const std::vector<KStream>& whole, int n_groups, int64_t slots, int sched,
+                   bool alone) {
     const bool radial = lay.kind == SDC_BINS_RADIAL;
     const int cap = radial ? kFittedSegmentRadial : kFittedSegmentPeriodic;
-    const int64_t slots = (int64_t)n_cu * wg_per_cu(sched);
     int64_t pairs = 0;
     int longest = 1;
-    for (const KStream& s : lay.streams) {
+    for (const KStream& s : whole) {
         pairs += s.p1 - s.p0;
         longest = std::max(longest, s.p1 - s.p0);
     }
@@ -430,7 +430,7 @@ int fitted_segment(const Layout& lay, int n_groups, int n_cu, int sched) {
     auto cut = [&](int seg, int* len) {
         int64_t tasks = 0;
         int l = 1;
-        for (const KStream& s : lay.streams) {
+        for (const KStream& s : whole) {
             const int n = s.p1 - s.p0, k = (n + seg - 1) / seg;
             tasks += k;
             l = std::max(l, (n + k - 1) / k);
@@ -440,7 +440,7 @@ int fitted_segment(const Layout& lay, int n_groups, int n_cu, int sched) {
     };
     const double q = (double)pairs * n_groups / (double)slots;
     int best = std::min(longest, cap);
-    const bool count = q < 32.0 || (wg_per_cu(sched) == 1 && !lay.linear && q < (double)cap * cap);
+    const bool count = q < 32.0 || (alone && wg_per_cu(sched) == 1 && !lay.linear && q < (double)cap * cap);
     if (!count) {
         best = std::max(1, (int)std::min((double)cap, std::sqrt(q) + 0.5));
     } else {

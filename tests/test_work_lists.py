@@ -41,7 +41,7 @@ int main(int argc, char** argv) {
         lay.streams.push_back(s);
     }
     const long most = (long)sdc::max_fused_tasks(sched);
-    const int seg = sdc::fitted_segment(lay, groups, 256, sched);
+    const int seg = sdc::fitted_segment(lay, lay.streams, groups, 256 * sdc::wg_per_cu(sched), sched, true);
     std::printf("%d %ld %ld\n", seg, n * ((len + seg - 1) / seg), most);
 }
 """
