@@ -30,10 +30,10 @@ using PackElem = typename std::conditional<PREC == SDC_PREC_BF16X3, Chunk3, Chun
 // The packs of the two-piece splits hold a plane of hi and a plane of lo
 // halves: the pass over the hi halves alone then fetches no lo halves in its
 // cache lines.  The other forms multiply all pieces of an element at once and
-// keep them side by side.  Fused time side by side / in planes: BF16 sc 36^3 x
-// 500 origins 1028 / 1018 ms, sc 30^3 x 100 origins 124.6 / 120.6, ball of
-// 20011 sites 53.1 / 52.6; FP32 sc 21x20x19 20.9 / 21.3, BF16x3 sq 90x90
-// 8.10 / 8.20.
+// keep them side by side.  Fused ms side by side / in planes (origins x lags):
+// BF16 sc 36^3 128 x 256 1028 / 1018, sc 30^3 100 x 100 122.3 / 119.0, ball of
+// 20 011 points 64 x 128 53.1 / 52.6; FP32 sc 21x20x19 50 x 100 20.9 / 21.3,
+// BF16x3 90x90 50 x 64 8.10 / 8.20.
 __host__ __device__ constexpr bool pack_planes(int prec) {
     return prec == SDC_PREC_SPLIT_BF16 || prec == SDC_PREC_SPLIT_FP16;
 }

@@ -550,7 +550,10 @@ size_t mc_counter_bytes();
 // LDS.  Per sweep of two classes, one workgroup against one launch per class:
 // 512 sites per class 5.0 / 9.1 us, 648: 6.5 / 9.2, 800: 8.7 / 9.1, 1024:
 // 8.5 / 9.1, 1408: 12.4 / 9.0; the line leaves room for couplings that cost
-// more per site (with DMI 800 sites take 10.1 / 9.5).
+// more per site (with DMI 800 sites take 10.1 / 9.5).  Open samples with more
+// bonds, read one by one, gain as well, also where a class takes two turns:
+// sc 13^3 within 1.5 (18 bonds, four classes of about 550 sites) 38.6 / 43.1, 14^3
+// (690 sites) 40.8 / 44.5, sc 15^3 within 2.5 (80 bonds, 31 classes) 625 / 983.
 constexpr int kMcSmallSites = 4096, kMcSmallClassSites = 768, kMcSmallClasses = 32;
 // A stretch of the annealing schedule: `count` sweeps from number `sweep` on,
 // the first at temperature T after `done` of its per_T sweeps.

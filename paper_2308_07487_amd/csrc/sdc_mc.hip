@@ -313,11 +313,12 @@ __global__ __launch_bounds__(256) void mc_colour_kernel(McArgs a, int64_t k0, in
 }
 
 // `count` sweeps of a small sample by one workgroup, the state in LDS.  Bound:
-// the latency of one update (about 700 dependent instructions).  A class of a
-// 32 x 32 lattice is eight waves, so a launch per class and sweep end is
-// mostly launch and memory latency: 14.4 us per sweep, 9.1 without the launch
-// of the sweep's end, 4.9 in one workgroup (a whole annealing of 310 sweeps
-// 4.5 -> 1.5 ms).
+// issue on its one CU.  A class of a 32 x 32 lattice is eight waves, two per
+// SIMD, of about 700 instructions each, most of them FP64 at four cycles: 5600
+// cycles, 2.3 of the 2.4 us that a class takes.  A launch per class and sweep
+// end is mostly launch and memory latency: 14.4 us per sweep, 9.1 without the
+// launch of the sweep's end, 4.9 in one workgroup (a whole annealing of 310
+// sweeps 4.5 -> 1.5 ms).
 // T and `done` (sweeps made at T) follow the schedule of the host:
 // T_k = T_start cool^k while T_k > T_end, sweeps_per_T each, then T_end.
 template <int STENCIL, int Z>
