@@ -8,11 +8,13 @@ workloads gets one sdc_autotune run on its first sample shape, with seeded
 unit spins; classes already in the file are kept.  The single-sample
 workloads (sc 36^3 in split-BF16 and split-FP16, sc 32^3, sc 8^3, the 420^2
 square lattice, the 65536-point ball) run over all their lags with every
-schedule of the precision and the segment lengths 16, 32, 48 and 96 (the
-ball: the built-in radial candidates); the 48 batch samples with the
-two-pass schedule (the batch's work-weighted vote) and segments of 16, 32
-and 48 pairs, over all their lags by default (--batch-lags N: the first N;
-the segment choice depends on the number of lag groups that run together).
+schedule of the precision and segments of 16, 32, 48 and the default 96
+pairs, whose length the plan fits, and of 1 and 4 pairs below 4096 sites
+(the ball: the built-in radial candidates, the default among them); the 48
+batch samples with the two-pass schedule (the batch's work-weighted vote)
+and segments of 16, 32, 48 and the default, over all their lags by default
+(--batch-lags N: the first N; the segment choice depends on the number of
+lag groups that run together).
 Each class's winner and every candidate's median time go to the file, and
 the library prints every candidate's time as it is measured.
 """
@@ -68,11 +70,12 @@ def main():
         if full and kind == sdc.BINS_RADIAL:
             best, ms, cands = sdc.autotune(pos, kind, n_o, n_L, prec, max_lags=0, cache_path=args.out, **spec)
         elif full:
-            cands = [(sch, seg) for sch in ("one_pass", "two_pass", "lag_split", "fold") for seg in (16, 32, 48, 96)]
+            segs = ((1, 4) if pos.shape[0] < 4096 else ()) + (16, 32, 48, 96)
+            cands = [(sch, seg) for sch in ("one_pass", "two_pass", "lag_split", "fold") for seg in segs]
             best, ms, cands = sdc.autotune(pos, kind, n_o, n_L, prec, max_lags=0, candidates=cands,
                                            cache_path=args.out, **spec)
         else:
-            cands = [("two_pass", seg) for seg in (16, 32, 48)]
+            cands = [("two_pass", seg) for seg in (16, 32, 48, 96)]
             best, ms, cands = sdc.autotune(pos, kind, n_o, n_L, prec, max_lags=args.batch_lags, candidates=cands,
                                            cache_path=args.out, **spec)
         times = " ".join(f"{c['schedule'][:4]}/{c['segment_pairs']}:{t:.2f}" for c, t in cands)
