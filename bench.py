@@ -233,7 +233,7 @@ def time_run(torch, sdc, samples, prec, steps, warmup):
     return dict(ms_per_step=ms, fused_ms=float(np.mean(fused)), fused_ms_min=float(np.min(fused)), plan_ms=plan_ms,
                 wall_ms_per_step=wall_ms / steps, schedule=(batch.schedule if batch is not None
                                                             else plans[0].tuning["schedule"]),
-                segment_pairs=plans[0].segment_pairs), plans, batch
+                segment_pairs=plans[0].segment_pairs if batch is None else None), plans, batch
 
 
 def graph_run(torch, sdc, samples, prec, replays=10, warmup=2):
