@@ -1068,6 +1068,8 @@ sdc_status sdc_batch_create_tuned(sdc_plan* const* plans, int32_t n_plans, int32
     // 48 sc 8^3 x 64 lags 2360 / 1714 (in segments of at most 96 pairs, with the
     // earlier histogram layout, 749, 167 and 1836).
     std::vector<std::vector<KStream>> cuts((size_t)n_plans);
+    std::vector<KStream> all;  // of every plan, one upload
+    std::vector<size_t> cut_start((size_t)n_plans, 0);
     auto streams_of = [&](int k) -> const std::vector<KStream>& {
         return cuts[k].empty() ? plans[k]->lay.streams : cuts[k];
     };
@@ -1088,10 +1090,24 @@ sdc_status sdc_batch_create_tuned(sdc_plan* const* plans, int32_t n_plans, int32
                 const double share = (double)n_cu * sdc::wg_per_cu(sched) * work(k) / total;
                 cuts[k] = sdc::split_streams(p->whole, sdc::fitted_segment(p->lay, p->whole, b->sels[k]->n_groups,
                                                                            std::max<int64_t>(1, (int64_t)share), sched, false));
+                cut_start[k] = all.size();
+                all.insert(all.end(), cuts[k].begin(), cuts[k].end());
             }
         } catch (const std::bad_alloc&) {
             delete b;
             return set_err(SDC_ERR_OOM, "host allocation failed");
+        }
+    }
+    KStream* d_cuts = nullptr;
+    if (!all.empty()) {
+        sdc_status s = dalloc(&d_cuts, all.size(), &b->owned);
+        if (s == SDC_OK) {
+            const hipError_t he = hipMemcpy(d_cuts, all.data(), all.size() * sizeof(KStream), hipMemcpyHostToDevice);
+            if (he != hipSuccess) s = hip_err((int)he, "upload batch streams");
+        }
+        if (s != SDC_OK) {
+            delete b;
+            return s;
         }
     }
     // The launch's task list takes the plans in order of decreasing task
@@ -1118,15 +1134,7 @@ sdc_status sdc_batch_create_tuned(sdc_plan* const* plans, int32_t n_plans, int32
         args[k].sched = sdc::sched_index(schedule);
         if (!cuts[q].empty()) {
             args[k].n_streams = (int)cuts[q].size();
-            KStream* d = nullptr;
-            s = dalloc(&d, cuts[q].size(), &b->owned);
-            if (s == SDC_OK && hipMemcpy(d, cuts[q].data(), cuts[q].size() * sizeof(KStream), hipMemcpyHostToDevice) != hipSuccess)
-                s = set_err(SDC_ERR_HIP, "upload batch streams");
-            if (s != SDC_OK) {
-                delete b;
-                return s;
-            }
-            args[k].streams = d;
+            args[k].streams = d_cuts + cut_start[q];
         }
         start[k + 1] = start[k] + (int64_t)args[k].n_groups * args[k].n_streams;
         lds = std::max(lds, sdc::fused_lds_bytes(args[k].win, prec));
