@@ -589,11 +589,15 @@ __device__ __forceinline__ void fused_task(const FusedArgs& a, int task, double*
             const double v = hist[w * PITCH + m];
             const unsigned long long vq = reinterpret_cast<const unsigned long long*>(hist)[w * PITCH + m];
             if (vq != 0ull && ((grp.mask >> m) & 1)) {
-                const int64_t at = ((int64_t)a.stride * (grp.u0 + m) + grp.phase) * a.n_bins + w;
+                const int64_t b = w;
+                const int64_t t = (int64_t)a.stride * (grp.u0 + m) + grp.phase;
+                // the address per branch: taken before them, the compiler's
+                // schedule of the whole kernel changes (6 FP32 samples of 5000
+                // points, 64 lags: 19.6 -> 20.3 ms)
                 if (a.det)
-                    atomicAdd(&a.Hq[at], vq);
+                    atomicAdd(&a.Hq[t * a.n_bins + b], vq);
                 else
-                    unsafeAtomicAdd(&a.H[at], v);
+                    unsafeAtomicAdd(&a.H[t * a.n_bins + b], v);
             }
         }
     } else {
