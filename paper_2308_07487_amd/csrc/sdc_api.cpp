@@ -1066,7 +1066,8 @@ sdc_status sdc_batch_create_tuned(sdc_plan* const* plans, int32_t n_plans, int32
     // tasks were mostly merges: fused launch cut alone / by share, split-BF16,
     // 48 samples sc 8^3 x 64 lags 1144 / 690 us, 16 bcc 8^3 x 8 lags 279 / 158, FP32
     // 48 sc 8^3 x 64 lags 2360 / 1714 (in segments of at most 96 pairs, with the
-    // earlier histogram layout, 749, 167 and 1836).
+    // earlier histogram layout, 749, 167 and 1836; by share with a bin worked
+    // out once in the merge 660, 154 and 1640).
     std::vector<std::vector<KStream>> cuts((size_t)n_plans);
     std::vector<KStream> all;  // of every plan, one upload
     std::vector<size_t> cut_start((size_t)n_plans, 0);
